@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -16,9 +17,10 @@
 
 #include "../../include/elb.h"
 #include "closure_kernels.h"
-#include "elb_kernels.h"
 #include "host_math.h"
 #include "readout_kernels.h"
+#include "stage_table.h"
+#include "state_kernels.h"
 
 using namespace elb;
 
@@ -129,6 +131,8 @@ struct elb_ctx {
     bool has_state = false;
     bool closure_on = false;     // learned correction applied in every stage
     bool closure_fused = true;   // evaluated inside the stage kernel (else two kernels before it)
+    const StageKernel *kernel = nullptr;     // the stage kernel's tile shape for this problem
+    const StageKernel *kernel_cl = nullptr;  // and with the learned closure inside (closure = 1)
     int fm_J = -1;               // chi_RET-FM: stencil half-width of the ball average
     std::vector<double> fm_w;    // and its weights
     // a captured chunk of GRAPH_STEPS steps (elb_step), replayed on `stream`; dropped when
@@ -245,10 +249,31 @@ double host_tau(const elb_ctx *c, double n, double T)
     return c->mu_ref * (1.0 + 0.8 * y + cm * y * y) / (n * chi * std::sqrt(T));
 }
 
-template <typename R, int Q, int MODE>
+StageTable stage_table(int precision, int fixup)
+{
+    switch (precision) {
+        case ELB_FP64: return stage_table_f64();
+        case ELB_FP32: return stage_table_f32();
+        default: return fixup ? stage_table_fixup() : stage_table_mixed();
+    }
+}
+
+// The stage kernel of a problem: its first compiled tile whose number of blocks is at most the
+// tile's cap (stage_kernels.hip has the caps and what they were measured on).
+const StageKernel *pick_stage(const elb_params *p, int ret, int closure)
+{
+    const StageTable t = stage_table(p->precision, p->moment_fixup);
+    for (int i = 0; i < t.stages; ++i) {
+        const StageKernel *k = &t.stage[i];
+        if (k->q == p->q && k->ret == ret && k->closure == closure && (p->nx + k->cells() - 1) / k->cells() <= k->cap)
+            return k;
+    }
+    return nullptr;  // not reached: the large-problem tile takes any number of blocks
+}
+
+template <typename R>
 void launch_stage_t(const elb_ctx *c, int s_in, int s_out, double an, double as, double aL)
 {
-    using G = Geometry<R, Q>;
     StageArgs<R> a{};
     a.psi_s = c->dev<R>(c->L.psi[s_in]);
     a.psi_n = c->dev<R>(c->L.psi[0]);
@@ -297,31 +322,9 @@ void launch_stage_t(const elb_ctx *c, int s_in, int s_out, double an, double as,
         a.seed = c->launches++;
         a.seed_base = nullptr;
     }
-    int blocks = (c->P.nx + G::W - 1) / G::W;
-    if constexpr (Q <= MLP_OUT) {
-        if (fused) {  // the learned closure inside the stage (chi_SET only)
-            hipLaunchKernelGGL((k_stage<R, Q, MODE, false, true>), dim3(blocks), dim3(G::NT), 0, c->stream, a);
-            return;
-        }
-    }
-    if (c->fm_J >= 0)
-        hipLaunchKernelGGL((k_stage<R, Q, MODE, true>), dim3(blocks), dim3(G::NT),
-                           fm_lds_bytes(c->fm_J, G::ROWS), c->stream, a);
-    else
-        hipLaunchKernelGGL((k_stage<R, Q, MODE, false>), dim3(blocks), dim3(G::NT), 0, c->stream, a);
-}
-
-template <int Q>
-void launch_stage_q(const elb_ctx *c, int s_in, int s_out, double an, double as, double aL)
-{
-    switch (c->P.precision) {
-        case ELB_FP64: launch_stage_t<double, Q, MODE_FP64>(c, s_in, s_out, an, as, aL); break;
-        case ELB_FP32: launch_stage_t<float, Q, MODE_FP32>(c, s_in, s_out, an, as, aL); break;
-        default:
-            if (c->P.moment_fixup) launch_stage_t<float, Q, MODE_FP32_FIXUP>(c, s_in, s_out, an, as, aL);
-            else launch_stage_t<float, Q, MODE_FP32_MIXED>(c, s_in, s_out, an, as, aL);
-            break;
-    }
+    const StageKernel *k = fused ? c->kernel_cl : c->kernel;
+    const int blocks = (c->P.nx + k->cells() - 1) / k->cells();
+    k->launch(&a, blocks, k->ret ? fm_lds_bytes(c->fm_J, k->rows) : 0, c->stream);
 }
 
 // Moments of every row of level s (ghost or wrapped halo rows included) into rows5.
@@ -371,20 +374,8 @@ void launch_stage(const elb_ctx *c, int s_in, int s_out, double an, double as, d
                                closure_const(c), nx, c->Q, c->dev<float>(c->L.corr),
                                c->dev<unsigned long long>(c->L.outside));
     }
-    switch (c->Q) {
-        case 8: launch_stage_q<8>(c, s_in, s_out, an, as, aL); break;
-        case 12: launch_stage_q<12>(c, s_in, s_out, an, as, aL); break;
-        case 16: launch_stage_q<16>(c, s_in, s_out, an, as, aL); break;
-        case 20: launch_stage_q<20>(c, s_in, s_out, an, as, aL); break;
-        case 24: launch_stage_q<24>(c, s_in, s_out, an, as, aL); break;
-        case 32: launch_stage_q<32>(c, s_in, s_out, an, as, aL); break;
-        case 40: launch_stage_q<40>(c, s_in, s_out, an, as, aL); break;
-        case 48: launch_stage_q<48>(c, s_in, s_out, an, as, aL); break;
-        case 64: launch_stage_q<64>(c, s_in, s_out, an, as, aL); break;
-        case 96: launch_stage_q<96>(c, s_in, s_out, an, as, aL); break;
-        case 200: launch_stage_q<200>(c, s_in, s_out, an, as, aL); break;
-        default: break;
-    }
+    if (c->P.precision == ELB_FP64) launch_stage_t<double>(c, s_in, s_out, an, as, aL);
+    else launch_stage_t<float>(c, s_in, s_out, an, as, aL);
 }
 
 // Drops the captured step graph of a context (after draining its stream).
@@ -553,6 +544,8 @@ int elb_create(const elb_params *p, void *dev_workspace, int64_t workspace_bytes
     if (((uintptr_t)dev_workspace) & 255) { g_create_error = "workspace not 256-byte aligned"; delete c; return ELB_EINVAL; }
     c->ws = (char *)dev_workspace;
     c->stream = (hipStream_t)hip_stream;
+    c->kernel = pick_stage(p, fm_reach(p) >= 0, 0);
+    if (p->closure) c->kernel_cl = pick_stage(p, 0, 1);
     int Q = c->Q, N = c->N;
     c->w.resize(Q);
     gauss_hermite(Q, c->p.data(), c->w.data());
@@ -930,117 +923,12 @@ int elb_destroy(elb_ctx *c)
 // ======================================================================================
 namespace {
 
-typedef void (*BatchLaunchFn)(const BatchStage &, int, size_t, hipStream_t);
-
-struct BatchKernel {
-    int q, S, L, precision, ret, nt, rows;
-    BatchLaunchFn launch;
-    const void *func;
-};
-
-template <typename R, int Q, int S, int L, int MODE, bool RET>
-void launch_batch(const BatchStage &bs, int grid, size_t shm, hipStream_t st)
-{
-    hipLaunchKernelGGL((k_stage_batch<R, Q, S, L, MODE, RET>), dim3(grid), dim3(Geometry<R, Q, S, L>::NT), shm, st, bs);
-}
-
-#define ELB_BKX(RT, QV, SV, LV, MODE, PREC, RET) \
-    {QV, SV, LV, PREC, RET, Geometry<RT, QV, SV, LV>::NT, Geometry<RT, QV, SV, LV>::ROWS, \
-     &launch_batch<RT, QV, SV, LV, MODE, RET>, \
-     reinterpret_cast<const void *>(&k_stage_batch<RT, QV, SV, LV, MODE, RET>)}
-#define ELB_BK(RT, QV, SV, LV, MODE, PREC) ELB_BKX(RT, QV, SV, LV, MODE, PREC, false)
-#define ELB_BKR(RT, QV, SV, LV, MODE, PREC) ELB_BKX(RT, QV, SV, LV, MODE, PREC, true)
-
-// Compiled batch variants.  Variant 0 of every Q is the single-problem shape; the FP32 modes
-// also have the 16-cell strips in blocks of up to 384 threads, between which the tuner
-// chooses.
-const BatchKernel kBatchKernels[] = {
-    ELB_BK(double, 8, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 12, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 16, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 20, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 24, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 32, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 40, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 48, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 64, 2, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 96, 2, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(double, 200, 2, 8, MODE_FP64, ELB_FP64),
-    ELB_BK(float, 8, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 12, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 16, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 16, 16, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 20, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 24, 16, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 24, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 32, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 32, 4, 16, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 40, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 48, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 48, 4, 16, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 64, 6, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 96, 4, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 200, 2, 8, MODE_FP32, ELB_FP32),
-    ELB_BK(float, 8, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 12, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 16, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 16, 16, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 20, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 24, 16, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 24, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 32, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 32, 4, 16, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 40, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 48, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 48, 4, 16, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 64, 6, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 96, 4, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 96, 2, 16, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BK(float, 200, 2, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    // chi_RET-FM: the single-problem shape of every Q
-    ELB_BKR(double, 8, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 12, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 16, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 20, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 24, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 32, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 40, 8, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 48, 4, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 64, 2, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 96, 2, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(double, 200, 2, 8, MODE_FP64, ELB_FP64),
-    ELB_BKR(float, 8, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 12, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 16, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 20, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 24, 16, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 32, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 40, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 48, 8, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 64, 6, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 96, 4, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 200, 2, 8, MODE_FP32, ELB_FP32),
-    ELB_BKR(float, 8, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 12, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 16, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 20, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 24, 16, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 32, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 40, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 48, 8, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 64, 6, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 96, 4, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-    ELB_BKR(float, 200, 2, 8, MODE_FP32_MIXED, ELB_FP32_MIXED),
-};
-#undef ELB_BK
-#undef ELB_BKR
-#undef ELB_BKX
-
 std::vector<const BatchKernel *> batch_variants(int q, int precision, int ret)
 {
     std::vector<const BatchKernel *> v;
-    for (const auto &k : kBatchKernels)
-        if (k.q == q && k.precision == precision && k.ret == ret) v.push_back(&k);
+    const StageTable t = stage_table(precision, 0);
+    for (int i = 0; i < t.batches; ++i)
+        if (t.batch[i].q == q && t.batch[i].ret == ret) v.push_back(&t.batch[i]);
     return v;
 }
 
@@ -1119,8 +1007,6 @@ std::vector<std::pair<int, int>> batch_specs(const elb_params *p, int count)
     return v;
 }
 
-int tile_cells(const BatchKernel *k) { return k->S * k->L; }
-
 // dynamic LDS of a group's launch (the chi_RET-FM phase of the stage kernel)
 size_t group_lds(const BatchGroup &g, int v) { return g.ret ? fm_lds_bytes(g.fm_J, g.variants[v]->rows) : 0; }
 
@@ -1142,7 +1028,7 @@ int batch_layout(const elb_params *p, int count, BatchLayout *L, std::string *ms
             size_t n = 0;
             for (int i = 0; i < count; ++i)
                 if (p[i].q == spec.first && inst_ret(p[i]) == spec.second)
-                    n += (p[i].nx + tile_cells(k) - 1) / tile_cells(k);
+                    n += (p[i].nx + k->cells() - 1) / k->cells();
             L->item_off.push_back(take(sizeof(int2) * n));
         }
     L->ctx.resize(count);
@@ -1401,7 +1287,7 @@ int elb_batch_create(const elb_params *params, int32_t count, void *dev_workspac
         for (const BatchKernel *k : g.variants) {
             std::vector<int2> items;
             for (int i : g.inst) {
-                int tiles = (params[i].nx + tile_cells(k) - 1) / tile_cells(k);
+                int tiles = (params[i].nx + k->cells() - 1) / k->cells();
                 for (int t = 0; t < tiles; ++t) items.push_back(make_int2(i, t));
             }
             int2 *d = reinterpret_cast<int2 *>(b->ws + L.item_off[vi++]);
@@ -1415,6 +1301,13 @@ int elb_batch_create(const elb_params *params, int32_t count, void *dev_workspac
             g.nitems.push_back((int)items.size());
             g.grid.push_back((int)items.size());  // one block per (instance, tile) item
         }
+        // before any tuning: the smallest tile whose items fit its cap, as for a single problem;
+        // else the large-problem tile
+        for (int v = 1, cells_v = INT_MAX; v < (int)g.variants.size(); ++v)
+            if (g.variants[v]->cap != INT_MAX && g.nitems[v] <= g.variants[v]->cap && g.variants[v]->cells() < cells_v) {
+                g.chosen = v;
+                cells_v = g.variants[v]->cells();
+            }
         b->groups.push_back(g);
     }
     if (hipError_t e = hipStreamSynchronize(b->stream); e != hipSuccess) {

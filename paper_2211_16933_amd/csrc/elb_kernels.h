@@ -1,4 +1,4 @@
-// Device kernels of the FDLB step (gfx950).  Included by elb.hip only.
+// Device code of the FDLB step (gfx950).
 //
 // Layout in HBM: a distribution level is (nx + 6) rows of 2Q values, row r = cell r - 3,
 // each row [phi_0 .. phi_{Q-1}, theta_0 .. theta_{Q-1}] with the node index fastest.
@@ -67,7 +67,8 @@ constexpr int MAXQP = 208;
 
 // Launch shape of the stage kernel for storage type R and Q nodes:
 //   S strips of L cells per block (W = S L cells), 2Q columns (phi and theta of every node),
-//   one thread per (column, strip) -> 2Q S threads.  W is a multiple of 16 (MFMA tiles).
+//   one thread per (column, strip) -> 2Q S threads.
+// Shape<R, Q> is the tile of large problems.
 template <typename R, int Q> struct Shape;
 #define ELB_SHAPE(RT, QV, SV, LV) \
     template <> struct Shape<RT, QV> { static constexpr int S = SV, L = LV; };
@@ -103,7 +104,7 @@ ELB_SHAPE(double, 96, 2, 8)
 ELB_SHAPE(double, 200, 2, 8)
 #undef ELB_SHAPE
 
-template <typename R, int Q, int S_ = Shape<R, Q>::S, int L_ = Shape<R, Q>::L>
+template <typename R, int Q, int S_, int L_>
 struct Geometry {
     static constexpr int S = S_, L = L_;
     static constexpr int W = S * L;             // cells per block
@@ -115,8 +116,11 @@ struct Geometry {
     static constexpr int HW = (H + 63) / 64 * 64;
     static constexpr int NT = 2 * HW;
     // occupancy the register allocation is held to (waves per SIMD): two blocks of 10 or 12
-    // waves (3 per SIMD each), three of 8 or three of 6 per CU; 1 = no constraint
-    static constexpr int WV = (NT == 768 || NT == 640 || NT == 512) ? 6 : NT == 384 ? 5 : 1;
+    // waves (3 per SIMD each), three of 8 or three of 6 per CU; 1 = no constraint.  Tiles
+    // smaller than the large-problem one run about one block per CU, where registers cost
+    // nothing (FP64 Q = 64, 128 cells, 4 x 4 held to six waves per SIMD: spills, 9.6 us).
+    static constexpr int WD = Shape<R, Q>::S * Shape<R, Q>::L;  // cells of the large-problem tile
+    static constexpr int WV = W < WD ? 1 : (NT == 768 || NT == 640 || NT == 512) ? 6 : NT == 384 ? 5 : 1;
     // with the learned closure inside (Q <= 16): at least two blocks per CU, and four waves
     // per SIMD for blocks of up to four waves (four or more blocks per CU)
     static constexpr int WVCL0 = NT <= 256 ? 4 : (2 * NT / 64 + 3) / 4;
@@ -125,10 +129,18 @@ struct Geometry {
     // which the (cell, segment) items fit in the waves after those of the per-cell phase;
     // 16 when that still fits and takes at most four waves (16-cell tiles: shorter segments
     // for one more scan step; with more cells the extra waves cost more than they save)
-    static constexpr int WC = (W + 63) / 64 * 64;
-    static constexpr int RG = 16 * W <= 256 && 16 * W + WC <= NT ? 16
-                            : 8 * W + WC <= NT ? 8 : 4 * W + WC <= NT ? 4 : 2 * W + WC <= NT ? 2 : 1;
+    // Smaller tiles of the same Q take the lane count of the large-problem tile, so that the
+    // segments, and with them the rounding of the coefficients, do not depend on the tile.
+    static constexpr int lanes(int w, int nt)
+    {
+        const int wc = (w + 63) / 64 * 64;
+        return 16 * w <= 256 && 16 * w + wc <= nt ? 16
+             : 8 * w + wc <= nt ? 8 : 4 * w + wc <= nt ? 4 : 2 * w + wc <= nt ? 2 : 1;
+    }
+    static constexpr int RGD = lanes(WD, 2 * ((Shape<R, Q>::S * Q + 63) / 64 * 64));
+    static constexpr int RG = RGD * W + (W + 63) / 64 * 64 <= NT ? RGD : lanes(W, NT);
     static constexpr int ROWS = W + 2 * NG;     // staged rows
+    static constexpr int WM = (W + 15) / 16 * 16;  // rows of the MFMA tiles that cover the cells
     static constexpr int QP = (Q + 15) / 16 * 16;  // padded node count (MFMA tiles)
     // The nodes are symmetric (p_{Q-1-k} = -p_k, equal weights) and He_l has the parity of
     // l, so when Q/2 fills whole 16-wide MFMA tiles the projection splits into even and odd
@@ -142,7 +154,10 @@ struct Geometry {
     // Every wave holds items of one velocity sign, so the upwind direction of the march is
     // uniform per wave (Q = 200: 400 items per sign in 7 waves each, the last one a quarter
     // full).
-    static_assert(W % 16 == 0, "tile width must be a multiple of 16");
+    // a tile narrower than 16 cells takes one MFMA tile, whose rows past W hold no cell: they
+    // are computed from stale LDS values (a row of the product depends on its own row only)
+    // and never read
+    static_assert(W % 16 == 0 || W < 16, "tile width: a multiple of 16, or less than 16");
     static_assert(Q % 2 == 0, "even node counts only (no zero node)");
     static_assert(NT <= 1024, "block too large");
 };
@@ -525,7 +540,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
 {
     using G = Geometry<R, Q, S_, L_>;
     constexpr int W = G::W, C2 = G::C2, NT = G::NT, ROWS = G::ROWS, QP = G::QP, GS = G::GS;
-    constexpr int QH = G::QH;
+    constexpr int QH = G::QH, WM = G::WM;
     constexpr bool SPLIT = G::SPLIT;
     constexpr int RG = G::RG;
     constexpr int S = G::S, L = G::L, H = G::H;
@@ -544,11 +559,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     constexpr int FB = BOOK ? (W + 1) * FS : 0;              // flux values (bookkeeping)
     // CL: the fused learned closure, whose activation tiles (one per wave) take the
     // coefficient buffer once the projection has read it
-    static_assert(!CL || Q <= MLP_OUT, "the learned closure takes Q <= 16");
+    static_assert(!CL || (Q <= MLP_OUT && W % 16 == 0), "the learned closure takes Q <= 16, 16-cell tiles");
     constexpr int CLA = CL ? (NWAVE * 16 * AS * 2 + (int)sizeof(R) - 1) / (int)sizeof(R) : 0;
-    constexpr int CB0 = W * GS > FB ? W * GS : FB;
+    constexpr int CB0 = WM * GS > FB ? WM * GS : FB;
     constexpr int CB = CB0 > CLA ? CB0 : CLA;                // coefficients, later fluxes
-    constexpr int AREA = ROWS * TS > CB + W * GS ? ROWS * TS : CB + W * GS;
+    constexpr int AREA = ROWS * TS > CB + WM * GS ? ROWS * TS : CB + WM * GS;
     constexpr int RL = Q % 8 == 0 ? 8 : 4;  // lanes per row of the moment pass
     static_assert(Q % RL == 0, "phi and theta columns split evenly over the row lanes");
 
@@ -562,7 +577,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     __shared__ double rec_s[2 * QP];  // 1/sqrt(l) and sqrt(l/(l+1)), l < QP
     __shared__ double cref_s[DEV ? QP : 1];
     __shared__ double gref_s[DEV ? Q : 1];   // n_r g_k(u_r, T_r), read by the march
-    __shared__ __attribute__((aligned(16))) double red[ROWS * 6];
+    __shared__ __attribute__((aligned(16))) double red[ROWS * 6 > 128 ? ROWS * 6 : 128];
     __shared__ double r_n[ROWS], r_u[ROWS], r_T[ROWS], r_q[ROWS], r_lnn[ROWS], r_lnT[ROWS];
     __shared__ __attribute__((aligned(16))) R cellv[W * 16];
     __shared__ double jm[BOOK ? 2 * W : 1];
@@ -582,7 +597,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     __shared__ double cst_s[CL ? CLP + (CL_NB + 1) / 2 : 1];
     // phase 0 sends the stores of threads with nothing to store to a 64-slot sink in red,
     // which is filled only in phase A
-    static_assert(sizeof(double) * ROWS * 6 >= 64 * 16, "the sink fits in red");
+    static_assert(sizeof(red) >= 64 * 16, "the sink fits in red");
     floatx4 *const sink = reinterpret_cast<floatx4 *>(red);
 
     // Wave priority: the phases before and after the march run chains of dependent
@@ -881,8 +896,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     }
 
     // ---- phase R (chi_RET-FM only): the density of the J cells beyond each side of the
-    // staged rows (one wave per cell, FP64 sums; with bookkeeping the tracked n), then per
-    // staged row nbar = sum_{|m|<=J} w_m n_{c+m}, chi = chi_SET(b nbar / 4) and ln chi.
+    // staged rows (RL lanes per cell and the additions in the order of phase A, so that a
+    // cell's density does not depend on the tile that reads it; with bookkeeping the tracked
+    // n), then per staged row nbar = sum_{|m|<=J} w_m n_{c+m}, chi = chi_SET(b nbar / 4) and ln chi.
     // Dynamic LDS: w[2J+1], n over the cells i0-3-J .. i0+wcount+2+J, chi[ROWS], ln chi[ROWS].
     double *rchi = nullptr, *rlnchi = nullptr;
     if constexpr (RET) {
@@ -894,21 +910,32 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         rlnchi = rchi + ROWS;
         for (int idx = tid; idx <= 2 * J; idx += NT) wts[idx] = a.fm_w[idx];
         for (int j = tid; j < rows; j += NT) next[J + j] = r_n[j];
-        for (int e = wave; e < 2 * J; e += NWAVE) {
-            const bool left = e < J;
-            const int c = left ? i0 - NG - J + e : i0 + wcount + NG + (e - J);
-            const int r = a.periodic ? row_of(c, nx, 1) : min(max(c, -NG), nx + NG - 1) + NG;
-            double v = 0.0;
-            if constexpr (BOOK) {
-                v = a.U_s[3 * (size_t)r];
-            } else {
-                const R *ph = a.psi_s + (size_t)r * C2;
-                for (int k = lane; k < Q; k += 64) v += (double)ph[k];
-#pragma unroll
-                for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-                if constexpr (DEV) v += a.ref_sum[0];
+        auto beyond = [&](int e) {  // storage row of the e-th of the 2J cells beyond
+            const int c = e < J ? i0 - NG - J + e : i0 + wcount + NG + (e - J);
+            return a.periodic ? row_of(c, nx, 1) : min(max(c, -NG), nx + NG - 1) + NG;
+        };
+        auto slot = [&](int e) { return e < J ? e : rows + e; };
+        if constexpr (BOOK) {
+            for (int e = tid; e < 2 * J; e += NT) next[slot(e)] = a.U_s[3 * (size_t)beyond(e)];
+        } else {
+            for (int base = 0; base < 2 * J * RL; base += NT) {
+                const int t = base + tid, e = t / RL, m = t % RL;
+                double v = 0.0;
+                if (e < 2 * J) {
+                    const R *ph = a.psi_s + (size_t)beyond(e) * C2;
+                    if constexpr ((Q / 2) % RL == 0) {
+#pragma unroll 4
+                        for (int kk = m; kk < Q / 2; kk += RL) v += (double)ph[kk] + (double)ph[Q - 1 - kk];
+                    } else {
+#pragma unroll 4
+                        for (int kk = m; kk < Q; kk += RL) v += (double)ph[kk];
+                    }
+                }
+                if constexpr (RL == 8) v += dpp_f64<DPP_MIR8>(v);
+                v += dpp_f64<DPP_X2>(v);
+                v += dpp_f64<DPP_X1>(v);
+                if (e < 2 * J && m == 0) next[slot(e)] = DEV ? v + a.ref_sum[0] : v;
             }
-            if (lane == 0) next[left ? e : J + rows + (e - J)] = v;
         }
         __syncthreads();
         for (int j = tid; j < rows; j += NT) {
@@ -1128,7 +1155,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     {
         typedef typename Acc4<R>::type A4;
         constexpr int KD = SPLIT ? QH : QP;          // contraction length of one tile
-        constexpr int TM = W / 16, TN = KD / 16, KS = KD / 4, NP = SPLIT ? 2 : 1;
+        constexpr int TM = WM / 16, TN = KD / 16, KS = KD / 4, NP = SPLIT ? 2 : 1;
         constexpr int VB = 16 / (int)sizeof(R);      // values per 16-byte load
         static_assert(KS % VB == 0, "k-steps in whole 16-byte loads");
         const int kk = lane >> 4;
@@ -1468,11 +1495,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
 // LDS) instead of chi_SET of the cell; a separate instantiation, so the chi_SET kernel
 // carries none of it.  CL: the learned closure evaluated inside the stage (phase L), also
 // an instantiation of its own (Q <= 16).
-template <typename R, int Q, int MODE, bool RET, bool CL = false>
-__global__ __launch_bounds__((Geometry<R, Q>::NT))
-__attribute__((amdgpu_waves_per_eu(CL ? Geometry<R, Q>::WVCL : Geometry<R, Q>::WV))) void k_stage(StageArgs<R> a)
+template <typename R, int Q, int S_, int L_, int MODE, bool RET, bool CL = false>
+__global__ __launch_bounds__((Geometry<R, Q, S_, L_>::NT))
+__attribute__((amdgpu_waves_per_eu(CL ? Geometry<R, Q, S_, L_>::WVCL : Geometry<R, Q, S_, L_>::WV))) void k_stage(StageArgs<R> a)
 {
-    stage_tile<R, Q, Geometry<R, Q>::S, Geometry<R, Q>::L, MODE, RET, CL>(a, blockIdx.x);
+    stage_tile<R, Q, S_, L_, MODE, RET, CL>(a, blockIdx.x);
 }
 
 // Batched form: per-instance description (device array) and the (instance, tile) items of
@@ -1544,139 +1571,6 @@ __attribute__((amdgpu_waves_per_eu(Geometry<R, Q, S_, L_>::WV))) void k_stage_ba
         a.seed = bs.seed;
         a.seed_base = bs.seed_base;
         stage_tile<R, Q, S_, L_, MODE, RET>(a, it.y);
-    }
-}
-
-// Base of the stochastic rounding stream for the next replay of a captured graph.
-__global__ void k_set_seed(unsigned *base, unsigned value)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) *base = value;
-}
-
-// --------------------------------------------------------------------------------------
-// Equilibrium initialisation of rows [0, rows): phi_k = n g_k(u,T), theta_k = 2 T n g_k,
-// g_k = sum_l Bt[l][k] c_l(u, T) in FP64 (QP-strided table), minus the per-column reference
-// (zero in FP64 storage).  One thread per (row, node).  With U != NULL also the conserved
-// densities (n, n u, (n u^2 + 3 n T)/2) of every row.
-// --------------------------------------------------------------------------------------
-template <typename R>
-__global__ void k_init_equilibrium(R *psi, double *U, const double *nrow, const double *urow,
-                                   const double *Trow, const double *Bt, const double *sq,
-                                   const double *rsq, const double *ref, int rows, int Q, int QP,
-                                   int N)
-{
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;  // rows * Q may pass 2^31
-    if (idx >= (size_t)rows * Q) return;
-    const int r = (int)(idx / Q), k = (int)(idx - (size_t)r * Q);
-    double n = nrow[r], u = urow[r], T = Trow[r];
-    double cm = 1.0, cc = u;
-    double g = Bt[k] * cm;
-    if (N >= 1) g += Bt[QP + k] * cc;
-    for (int l = 1; l < N; ++l) {
-        double cn = (u * cc + (T - 1.0) * sq[l] * cm) * rsq[l + 1];
-        cm = cc;
-        cc = cn;
-        g += Bt[(l + 1) * QP + k] * cc;
-    }
-    psi[(size_t)r * 2 * Q + k] = (R)(n * g - ref[k]);
-    psi[(size_t)r * 2 * Q + Q + k] = (R)(2.0 * T * n * g - ref[Q + k]);
-    if (U && k == 0) {
-        U[3 * (size_t)r + 0] = n;
-        U[3 * (size_t)r + 1] = n * u;
-        U[3 * (size_t)r + 2] = 0.5 * (n * u * u + 3.0 * n * T);
-    }
-}
-
-// Conserved densities of every row from the stored distributions plus reference (FP64 sums).
-template <typename R>
-__global__ void k_conserved_from_psi(const R *psi, const double *ref, double *U, const double *p,
-                                     int rows, int Q)
-{
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= rows) return;
-    const R *ph = psi + (size_t)r * 2 * Q;
-    double n = 0, j = 0, e = 0;
-    for (int k = 0; k < Q; ++k) {
-        double v = (double)ph[k] + ref[k];
-        n += v;
-        j += p[k] * v;
-        e += 0.5 * (p[k] * p[k] * v + (double)ph[Q + k] + ref[Q + k]);
-    }
-    U[3 * (size_t)r] = n;
-    U[3 * (size_t)r + 1] = j;
-    U[3 * (size_t)r + 2] = e;
-}
-
-// Per interior cell: n, u, T, q_x, P_xx (Sec. II.D) in FP64, two passes over the nodes, and
-// the conserved densities (n, n u, E).  With U != NULL (bookkeeping) n, u, T and the
-// conserved densities are the tracked ones; q_x and P_xx use that u.  `ref` is added to the
-// stored values (deviation storage; zero for FP64).
-//
-// 16 lanes per cell (MOM_LANES), so a wave reads four rows as 64-byte segments: lane m
-// takes the nodes m, m + 16, ... of phi and theta, and each pass ends with 4 exchange steps
-// inside the 16-lane group.  The second pass re-reads the row from cache.
-constexpr int MOM_LANES = 16;
-
-__device__ inline double sum16(double v)
-{
-#pragma unroll
-    for (int m = MOM_LANES / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, MOM_LANES);
-    return v;
-}
-
-template <typename R>
-__global__ void k_moments(const R *psi, const double *ref, const double *U, const double *p,
-                          int nx, int Q, double *out_n, double *out_u, double *out_T,
-                          double *out_q, double *out_pxx, double *out_cons)
-{
-    const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t i = gid / MOM_LANES;           // one cell per 16-lane group
-    const int part = (int)(gid % MOM_LANES);
-    // every lane of a group shares i, so a group is live or idle as a whole; idle groups
-    // still run the exchanges (on zeros) and store nothing
-    const bool live = i < (size_t)nx;
-    const R *ph = psi + (live ? i + NG : (size_t)NG) * 2 * Q;
-    const R *th = ph + Q;
-    double n = 0, j = 0, e2 = 0;
-    if (live)
-        for (int k = part; k < Q; k += MOM_LANES) {
-            const double v = (double)ph[k] + ref[k];
-            n += v;
-            j += p[k] * v;
-            e2 += 0.5 * (p[k] * p[k] * v + (double)th[k] + ref[Q + k]);
-        }
-    n = sum16(n);
-    j = sum16(j);
-    e2 = sum16(e2);
-    if (U && live) {
-        const double *Ui = U + 3 * (i + NG);
-        n = Ui[0];
-        j = Ui[1];
-        e2 = Ui[2];
-    }
-    const double u = live ? j / n : 0.0;
-    double pxx = 0, e = 0, q = 0;
-    if (live)
-        for (int k = part; k < Q; k += MOM_LANES) {
-            const double xi = p[k] - u;
-            const double vp = (double)ph[k] + ref[k], vt = (double)th[k] + ref[Q + k];
-            const double ek = 0.5 * xi * xi * vp + 0.5 * vt;
-            pxx += xi * xi * vp;
-            e += ek;
-            q += xi * ek;
-        }
-    pxx = sum16(pxx);
-    e = sum16(e);
-    q = sum16(q);
-    if (live && part == 0) {
-        out_n[i] = n;
-        out_u[i] = u;
-        out_T[i] = U ? (2.0 * e2 / n - u * u) / 3.0 : e / (1.5 * n);
-        out_q[i] = q;
-        out_pxx[i] = pxx;
-        out_cons[3 * i + 0] = n;
-        out_cons[3 * i + 1] = j;
-        out_cons[3 * i + 2] = e2;
     }
 }
 
