@@ -249,6 +249,9 @@ double host_tau(const elb_ctx *c, double n, double T)
     return c->mu_ref * (1.0 + 0.8 * y + cm * y * y) / (n * chi * std::sqrt(T));
 }
 
+// SSP-RK3 weights of level n and of the right-hand side, per stage
+const double RK_AN[3] = {0.0, 0.75, 1.0 / 3.0}, RK_AL[3] = {1.0, 0.25, 2.0 / 3.0};
+
 StageTable stage_table(int precision, int fixup)
 {
     switch (precision) {
@@ -272,7 +275,7 @@ const StageKernel *pick_stage(const elb_params *p, int ret, int closure)
 }
 
 template <typename R>
-void launch_stage_t(const elb_ctx *c, int s_in, int s_out, double an, double as, double aL)
+void launch_stage_t(const elb_ctx *c, int s_in, int s_out, double an, double aL)
 {
     StageArgs<R> a{};
     a.psi_s = c->dev<R>(c->L.psi[s_in]);
@@ -292,14 +295,13 @@ void launch_stage_t(const elb_ctx *c, int s_in, int s_out, double an, double as,
     a.N = c->N;
     a.periodic = c->P.bc == ELB_BC_PERIODIC;
     a.pr_enskog = c->P.pr_mode == ELB_PR_ENSKOG;
-    a.dx = c->dx;
-    a.dt = c->dt;
     a.b = c->b;
-    a.mu_ref = c->mu_ref;
     a.pr = c->P.pr;
+    a.inv_dx = 1.0 / c->dx;
+    a.inv_mu = 1.0 / c->mu_ref;
     a.a_n = an;
-    a.a_s = as;
-    a.a_L = aL;
+    a.w_rhs = aL * c->dt;
+    a.w_flux = aL * c->dt / (6.0 * c->dx);
     a.T_ref = c->T_ref;
     for (int m = 0; m < 6; ++m) a.ref_sum[m] = c->ref_sum[m];
     const bool fused = c->closure_on && c->closure_fused;
@@ -354,7 +356,7 @@ ClosureConst closure_const(const elb_ctx *c)
     return cc;
 }
 
-void launch_stage(const elb_ctx *c, int s_in, int s_out, double an, double as, double aL)
+void launch_stage(const elb_ctx *c, int s_in, int s_out, double an, double aL)
 {
     if (c->closure_on && !c->closure_fused) {
         // separate form: correction of L[phi] for the stage input, then the stage adds it
@@ -374,8 +376,8 @@ void launch_stage(const elb_ctx *c, int s_in, int s_out, double an, double as, d
                                closure_const(c), nx, c->Q, c->dev<float>(c->L.corr),
                                c->dev<unsigned long long>(c->L.outside));
     }
-    if (c->P.precision == ELB_FP64) launch_stage_t<double>(c, s_in, s_out, an, as, aL);
-    else launch_stage_t<float>(c, s_in, s_out, an, as, aL);
+    if (c->P.precision == ELB_FP64) launch_stage_t<double>(c, s_in, s_out, an, aL);
+    else launch_stage_t<float>(c, s_in, s_out, an, aL);
 }
 
 // Drops the captured step graph of a context (after draining its stream).
@@ -748,10 +750,11 @@ namespace {
 
 void launch_steps(elb_ctx *c, int64_t nsteps)
 {
+    // stage s: psi_out = a_n psi + (1 - a_n) psi^(s) + a_L dt L[psi^(s)]
     for (int64_t s = 0; s < nsteps; ++s) {
-        launch_stage(c, 0, 1, 0.0, 1.0, 1.0);                   // psi1 = psi + dt L[psi]
-        launch_stage(c, 1, 2, 0.75, 0.25, 0.25);                // psi2 = 3/4 psi + 1/4 psi1 + 1/4 dt L[psi1]
-        launch_stage(c, 2, 0, 1.0 / 3.0, 2.0 / 3.0, 2.0 / 3.0); // psi' = 1/3 psi + 2/3 psi2 + 2/3 dt L[psi2]
+        launch_stage(c, 0, 1, RK_AN[0], RK_AL[0]);  // psi1 = psi + dt L[psi]
+        launch_stage(c, 1, 2, RK_AN[1], RK_AL[1]);  // psi2 = 3/4 psi + 1/4 psi1 + 1/4 dt L[psi1]
+        launch_stage(c, 2, 0, RK_AN[2], RK_AL[2]);  // psi' = 1/3 psi + 2/3 psi2 + 2/3 dt L[psi2]
     }
 }
 
@@ -1065,11 +1068,14 @@ InstDesc describe(const elb_ctx *c)
     d.N = c->N;
     d.periodic = c->P.bc == ELB_BC_PERIODIC;
     d.pr_enskog = c->P.pr_mode == ELB_PR_ENSKOG;
-    d.dx = c->dx;
-    d.dt = c->dt;
     d.b = c->b;
-    d.mu_ref = c->mu_ref;
     d.pr = c->P.pr;
+    d.inv_dx = 1.0 / c->dx;
+    d.inv_mu = 1.0 / c->mu_ref;
+    for (int s = 0; s < 3; ++s) {
+        d.w_rhs[s] = RK_AL[s] * c->dt;
+        d.w_flux[s] = RK_AL[s] * c->dt / (6.0 * c->dx);
+    }
     d.T_ref = c->T_ref;
     for (int m = 0; m < 6; ++m) d.ref_sum[m] = c->ref_sum[m];
     d.fm_w = c->fm_J >= 0 ? c->dev<double>(c->L.chiw) : nullptr;
@@ -1099,8 +1105,7 @@ void drop_graph(elb_batch *b)
 // One stage of every group.  With fork (graph capture), groups 1.. run on side streams that
 // wait for the stage's start on st and are joined back into st at its end, so the captured
 // graph holds them as parallel branches.
-void enqueue_stage(elb_batch *b, hipStream_t st, int s_in, int s_out, double an, double as, double aL,
-                   bool fork)
+void enqueue_stage(elb_batch *b, hipStream_t st, int s_in, int s_out, bool fork)
 {
     const size_t G = b->groups.size();
     fork = fork && G > 1 && b->side.size() + 1 >= G;
@@ -1119,9 +1124,7 @@ void enqueue_stage(elb_batch *b, hipStream_t st, int s_in, int s_out, double an,
         bs.nitems = g.nitems[v];
         bs.s_in = s_in;
         bs.s_out = s_out;
-        bs.a_n = an;
-        bs.a_s = as;
-        bs.a_L = aL;
+        bs.a_n = RK_AN[s_in];
         bs.seed = b->capturing ? b->cap_seed : b->launches;
         bs.seed_base = b->capturing ? b->seed_dev : nullptr;
         g.variants[v]->launch(bs, g.grid[v], group_lds(g, v), gs);
@@ -1136,9 +1139,9 @@ void enqueue_stage(elb_batch *b, hipStream_t st, int s_in, int s_out, double an,
 void enqueue_steps(elb_batch *b, hipStream_t st, int64_t nsteps, bool fork)
 {
     for (int64_t s = 0; s < nsteps; ++s) {
-        enqueue_stage(b, st, 0, 1, 0.0, 1.0, 1.0, fork);
-        enqueue_stage(b, st, 1, 2, 0.75, 0.25, 0.25, fork);
-        enqueue_stage(b, st, 2, 0, 1.0 / 3.0, 2.0 / 3.0, 2.0 / 3.0, fork);
+        enqueue_stage(b, st, 0, 1, fork);
+        enqueue_stage(b, st, 1, 2, fork);
+        enqueue_stage(b, st, 2, 0, fork);
     }
 }
 
@@ -1423,9 +1426,7 @@ int elb_batch_tune(elb_batch *b, const char *cache_path, int32_t force)
             bs.nitems = g.nitems[v];
             bs.s_in = 0;
             bs.s_out = 1;
-            bs.a_n = 0.0;
-            bs.a_s = 1.0;
-            bs.a_L = 1.0;
+            bs.a_n = RK_AN[0];
             g.variants[v]->launch(bs, g.grid[v], group_lds(g, v), b->stream);  // warm-up
             float tmin = 1e30f;
             for (int rep = 0; rep < 5; ++rep) {
@@ -1581,7 +1582,7 @@ int rhs_into_level2(elb_ctx *c)
     const uint32_t launches = c->launches;
     c->dt = 1.0;
     c->closure_on = false;
-    launch_stage(c, 0, 1, 0.0, 1.0, 1.0);
+    launch_stage(c, 0, 1, 0.0, 1.0);
     c->dt = dt;
     c->closure_on = on;
     c->launches = launches;
@@ -1872,7 +1873,7 @@ int elb_closure_sample(elb_ctx *teacher, elb_ctx *student, float *x, float *y)
     const bool on = s->closure_on;
     s->dt = 1.0;
     s->closure_on = false;
-    launch_stage(s, 0, 1, 0.0, 1.0, 1.0);
+    launch_stage(s, 0, 1, 0.0, 1.0);
     s->dt = dt;
     s->closure_on = on;
     const size_t n = (size_t)nx * 2 * QS;

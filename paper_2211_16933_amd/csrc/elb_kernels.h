@@ -42,8 +42,10 @@ struct StageArgs {
     const double *rec;    // [2][Qp]: 1/sqrt(l) and sqrt(l/(l+1)) (recurrence constants)
     int *flag;            // set to 1 when a cell has n <= 0, T <= 0 or non-finite moments
     int nx, N, periodic, pr_enskog;
-    double dx, dt, b, mu_ref, pr;
-    double a_n, a_s, a_L; // psi_out = a_n psi^n + a_s psi^(s) + a_L dt L[psi^(s)], a_n + a_s = 1
+    double b, pr;
+    double inv_dx, inv_mu;  // 1 / dx, 1 / mu_ref
+    double a_n;             // psi_out = a_n psi^n + a_s psi^(s) + a_L dt L[psi^(s)], a_n + a_s = 1
+    double w_rhs, w_flux;   // a_L dt, a_L dt / (6 dx)
     double T_ref;         // deviation storage: reference temperature
     double ref_sum[6];    // deviation storage: S_0..S_3 and R_0, R_1 of psi_ref
     const R *corr;        // learned closure: [nx][Q] added to L[phi] (NULL: none)
@@ -178,16 +180,20 @@ __device__ inline double inv_tau(double mu_ref, double n, double T, double chi, 
     return n * chi * sqrt(T) / (mu_ref * (1.0 + 0.8 * y + cm * y * y));
 }
 
-// reciprocal and ratio: IEEE division in FP64, the hardware reciprocal (1 ulp) in FP32
-__device__ inline double recip(double x) { return 1.0 / x; }
+// reciprocal: FP32 the hardware's (1 ulp); FP64 the hardware's refined by two Newton steps (to
+// about 1 ulp; x normal, which spares the scaling and fix-up instructions of IEEE division)
+__device__ inline double recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
 __device__ inline float recip(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ inline double ratio(double a, double b) { return a / b; }
-__device__ inline float ratio(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
-// added to every scaled smoothness indicator: FP32 keeps indicators that vanish or underflow
-// from producing infinite ratios; FP64 tests for exact zeros instead
+// added to every scaled smoothness indicator: keeps indicators that vanish or underflow from
+// producing infinite ratios
 template <typename R> struct IndFloor;
 template <> struct IndFloor<float> { static constexpr float value = 1e-30f; };
-template <> struct IndFloor<double> { static constexpr double value = 0.0; };
+template <> struct IndFloor<double> { static constexpr double value = 1e-307; };
 
 // Storage row of cell `cell` (may lie in the halo): periodic wrap or the ghost rows.
 __device__ inline int row_of(int cell, int nx, int periodic)
@@ -407,10 +413,9 @@ __device__ inline void closure_tile(const StageArgs<R> &a, const unsigned short 
 // enters per step.
 //
 // Weights (eq. weno5_omega): (delta_q / varphi_q^2) / sum, evaluated as delta_q r_q^2 / sum
-// with r_q = min_s varphi_s / varphi_q.  FP64: r_q = 1 where varphi_q == 0, which gives the
-// Table III limits exactly.  FP32: each e_q carries 1e-30, which leaves every weight
-// unchanged to FP32 precision when the indicators are representable and yields the Table
-// III limits when some of them underflow.
+// with r_q = min_s varphi_s / varphi_q.  Each e_q carries a floor (FP32 1e-30, FP64 1e-307),
+// which leaves every weight unchanged to the type's precision when the indicators are
+// representable and yields the Table III limits when some of them underflow or vanish.
 // --------------------------------------------------------------------------------------
 // two floats in the bytes of one double (float x at the lower address)
 __device__ inline double pack_f2(float x, float y)
@@ -483,19 +488,17 @@ struct WenoMarch {
             R r1 = mn * recip(s1), r2 = mn * recip(s2), r3 = mn * recip(s3);
             t1 = R(0.1) * r1 * r1; t2 = R(0.6) * r2 * r2; t3 = R(0.3) * r3 * r3;
         } else {
-            // FP64 with one division: with g_q = varphi_q / min varphi >= 1, the weights
-            // delta_q / g_q^2 are proportional to delta_q prod_{p != q} g_p^2.  g is clamped at
-            // 1e50: a weight 1e-100 below the largest is zero at FP64 precision, and the
-            // products stay below 1e200.  If some indicator vanishes, the weights are
-            // delta_q on the zero set and 0 elsewhere (Table III limits).
-            const R mn = fmin(s1, fmin(s2, s3));
-            const bool z = mn == R(0);
-            const R im = R(1) / (z ? R(1) : mn);
+            // FP64: with g_q = varphi_q / min varphi >= 1, the weights delta_q / g_q^2 are
+            // proportional to delta_q prod_{p != q} g_p^2.  The common factor 1 / min varphi
+            // cancels between them, so the hardware's unrefined reciprocal does.  g is
+            // clamped at 1e50: a weight 1e-100 below the largest is zero at FP64 precision,
+            // and the products stay below 1e200.
+            const R im = __builtin_amdgcn_rcp(fmin(s1, fmin(s2, s3)));
             const R g1 = fmin(s1 * im, R(1e50)), g2 = fmin(s2 * im, R(1e50)), g3 = fmin(s3 * im, R(1e50));
             const R q1 = g1 * g1, q2 = g2 * g2, q3 = g3 * g3;
-            t1 = z ? (s1 == R(0) ? R(0.1) : R(0)) : R(0.1) * (q2 * q3);
-            t2 = z ? (s2 == R(0) ? R(0.6) : R(0)) : R(0.6) * (q1 * q3);
-            t3 = z ? (s3 == R(0) ? R(0.3) : R(0)) : R(0.3) * (q1 * q2);
+            t1 = R(0.1) * (q2 * q3);
+            t2 = R(0.6) * (q1 * q3);
+            t3 = R(0.3) * (q1 * q2);
         }
     }
 };
@@ -574,6 +577,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     R *const cbuf = area;
     R *const gbuf = area + CB;
     __shared__ double pk_s[Q];
+    __shared__ R pk6_s[BOOK ? Q : 1];  // p_k / 6
     __shared__ double rec_s[2 * QP];  // 1/sqrt(l) and sqrt(l/(l+1)), l < QP
     __shared__ double cref_s[DEV ? QP : 1];
     __shared__ double gref_s[DEV ? Q : 1];   // n_r g_k(u_r, T_r), read by the march
@@ -700,6 +704,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
             *(idx < nv ? dst + (j * VTS + v) : sinkv) = buf[u];
         }
         *(tid < Q ? pk_s + tid : sinkd) = pkv;
+        if constexpr (BOOK) *(tid < Q ? pk6_s + tid : reinterpret_cast<R *>(sinkd)) = (R)pkv / R(6);
         *(tid < 2 * QP ? rec_s + tid : sinkd) = recv;
         if constexpr (DEV) {
             *(tid < QP ? cref_s + tid : sinkd) = crefv;
@@ -956,8 +961,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     // ---- phase B.  The cell's divisions are shared: one for chi_SET and d ln chi / d ln n,
     // one for 1/tau, Pr, 1/T and 1/n (the chain of dependent FP64 divisions is the
     // latency of this one-wave phase).
-    const double cdt = a.a_L * a.dt;  // RK weight of the right-hand side
-    const double idx = 1.0 / a.dx, imu = 1.0 / a.mu_ref;
+    const double cdt = a.w_rhs;  // RK weight of the right-hand side
+    const double idx = a.inv_dx, imu = a.inv_mu;
     for (int i = tid; i < wcount; i += NT) {
         const int j = i + NG;
         const double n = r_n[j], u = r_u[j], T = r_T[j], q = r_q[j];
@@ -1220,8 +1225,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         const R pk = (R)pk_s[k];
         const R gref = DEV ? (R)gref_s[k] : R(0);  // n_r g_k(u_r, T_r)
         const int kp = neg ? QH - 1 - k : k - QH;   // positive node of the pair (E, O index)
-        const R pidx = (R)(a.a_L * a.dt / (6.0 * a.dx)) * pk;  // RK weight x p_k / (6 dx)
-        const R pk6 = pk / R(6);                    // flux = interpolant x p_k / 6
+        const R pidx = (R)a.w_flux * pk;            // RK weight x p_k / (6 dx)
+        const R pk6 = BOOK ? pk6_s[BOOK ? k : 0] : R(0);  // flux = interpolant x p_k / 6
         const R a_n = (R)a.a_n;
         const bool has_n = a.a_n != 0.0;
         const int mlim = wcount - ib;               // cells of this strip inside the tile
@@ -1471,7 +1476,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         }
         __syncthreads();
         for (int i = tid; i < wcount; i += NT) {
-            const double idx = 1.0 / a.dx;
+            const double idx = a.inv_dx;
             const size_t r = (size_t)(i0 + i + NG);
             const double *Us = ucell + 3 * i;
             const double *Un = ucell + 3 * W + 3 * i;
@@ -1481,7 +1486,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
             d[2] = -(gsum[(i + 1) * 3 + 2] - gsum[i * 3 + 2]) * idx + jm[2 * i + 1];
             double outv[3];
             for (int m = 0; m < 3; ++m) {
-                double v = Us[m] + a.a_L * a.dt * d[m];
+                double v = Us[m] + a.w_rhs * d[m];
                 if (a.a_n != 0.0) v += a.a_n * (Un[m] - Us[m]);
                 outv[m] = v;
             }
@@ -1512,7 +1517,8 @@ struct InstDesc {
     const void *Bt;
     int *flag;
     int nx, N, periodic, pr_enskog;
-    double dx, dt, b, mu_ref, pr, T_ref;
+    double b, pr, inv_dx, inv_mu, T_ref;
+    double w_rhs[3], w_flux[3];  // per stage (StageArgs)
     double ref_sum[6];
     const double *fm_w;  // chi_RET-FM weights (RET kernels), half-width fm_J
     int fm_J;
@@ -1522,8 +1528,8 @@ struct BatchStage {
     const InstDesc *inst;
     const int2 *items;   // (instance, tile)
     int nitems;
-    int s_in, s_out;     // levels read (stage input) and written
-    double a_n, a_s, a_L;
+    int s_in, s_out;     // levels read (stage input; also the stage's number) and written
+    double a_n;
     unsigned seed;       // stochastic rounding stream (see StageArgs)
     const unsigned *seed_base;
 };
@@ -1555,14 +1561,13 @@ __attribute__((amdgpu_waves_per_eu(Geometry<R, Q, S_, L_>::WV))) void k_stage_ba
         a.N = d.N;
         a.periodic = d.periodic;
         a.pr_enskog = d.pr_enskog;
-        a.dx = d.dx;
-        a.dt = d.dt;
         a.b = d.b;
-        a.mu_ref = d.mu_ref;
         a.pr = d.pr;
+        a.inv_dx = d.inv_dx;
+        a.inv_mu = d.inv_mu;
         a.a_n = bs.a_n;
-        a.a_s = bs.a_s;
-        a.a_L = bs.a_L;
+        a.w_rhs = d.w_rhs[bs.s_in];
+        a.w_flux = d.w_flux[bs.s_in];
         a.T_ref = d.T_ref;
         for (int m = 0; m < 6; ++m) a.ref_sum[m] = d.ref_sum[m];
         a.corr = nullptr;
