@@ -180,20 +180,22 @@ __device__ inline double inv_tau(double mu_ref, double n, double T, double chi, 
     return n * chi * sqrt(T) / (mu_ref * (1.0 + 0.8 * y + cm * y * y));
 }
 
-// reciprocal: FP32 the hardware's (1 ulp); FP64 the hardware's refined by two Newton steps (to
-// about 1 ulp; x normal, which spares the scaling and fix-up instructions of IEEE division)
+// reciprocal: FP32 the hardware's (1 ulp); FP64 the refinement of the hardware's reciprocal
+// that IEEE division makes, without the scaling and fix-up instructions around it (7
+// instructions, not 11): the same bits wherever x and 1 / x are normal
 __device__ inline double recip(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
     r = fma(fma(-x, r, 1.0), r, r);
+    r = fma(fma(-x, r, 1.0), r, r);
     return fma(fma(-x, r, 1.0), r, r);
 }
 __device__ inline float recip(float x) { return __builtin_amdgcn_rcpf(x); }
-// added to every scaled smoothness indicator: keeps indicators that vanish or underflow from
-// producing infinite ratios
+// added to every scaled smoothness indicator: FP32 keeps indicators that vanish or underflow
+// from producing infinite ratios; FP64 tests for exact zeros instead
 template <typename R> struct IndFloor;
 template <> struct IndFloor<float> { static constexpr float value = 1e-30f; };
-template <> struct IndFloor<double> { static constexpr double value = 1e-307; };
+template <> struct IndFloor<double> { static constexpr double value = 0.0; };
 
 // Storage row of cell `cell` (may lie in the halo): periodic wrap or the ghost rows.
 __device__ inline int row_of(int cell, int nx, int periodic)
@@ -413,9 +415,10 @@ __device__ inline void closure_tile(const StageArgs<R> &a, const unsigned short 
 // enters per step.
 //
 // Weights (eq. weno5_omega): (delta_q / varphi_q^2) / sum, evaluated as delta_q r_q^2 / sum
-// with r_q = min_s varphi_s / varphi_q.  Each e_q carries a floor (FP32 1e-30, FP64 1e-307),
-// which leaves every weight unchanged to the type's precision when the indicators are
-// representable and yields the Table III limits when some of them underflow or vanish.
+// with r_q = min_s varphi_s / varphi_q.  FP64: r_q = 1 where varphi_q == 0, which gives the
+// Table III limits exactly.  FP32: each e_q carries 1e-30, which leaves every weight
+// unchanged to FP32 precision when the indicators are representable and yields the Table
+// III limits when some of them underflow.
 // --------------------------------------------------------------------------------------
 // two floats in the bytes of one double (float x at the lower address)
 __device__ inline double pack_f2(float x, float y)
@@ -488,17 +491,19 @@ struct WenoMarch {
             R r1 = mn * recip(s1), r2 = mn * recip(s2), r3 = mn * recip(s3);
             t1 = R(0.1) * r1 * r1; t2 = R(0.6) * r2 * r2; t3 = R(0.3) * r3 * r3;
         } else {
-            // FP64: with g_q = varphi_q / min varphi >= 1, the weights delta_q / g_q^2 are
-            // proportional to delta_q prod_{p != q} g_p^2.  The common factor 1 / min varphi
-            // cancels between them, so the hardware's unrefined reciprocal does.  g is
-            // clamped at 1e50: a weight 1e-100 below the largest is zero at FP64 precision,
-            // and the products stay below 1e200.
-            const R im = __builtin_amdgcn_rcp(fmin(s1, fmin(s2, s3)));
+            // FP64 with one reciprocal: with g_q = varphi_q / min varphi >= 1, the weights
+            // delta_q / g_q^2 are proportional to delta_q prod_{p != q} g_p^2.  g is clamped at
+            // 1e50: a weight 1e-100 below the largest is zero at FP64 precision, and the
+            // products stay below 1e200.  If some indicator vanishes, the weights are
+            // delta_q on the zero set and 0 elsewhere (Table III limits).
+            const R mn = fmin(s1, fmin(s2, s3));
+            const bool z = mn == R(0);
+            const R im = recip(z ? R(1) : mn);
             const R g1 = fmin(s1 * im, R(1e50)), g2 = fmin(s2 * im, R(1e50)), g3 = fmin(s3 * im, R(1e50));
             const R q1 = g1 * g1, q2 = g2 * g2, q3 = g3 * g3;
-            t1 = R(0.1) * (q2 * q3);
-            t2 = R(0.6) * (q1 * q3);
-            t3 = R(0.3) * (q1 * q2);
+            t1 = z ? (s1 == R(0) ? R(0.1) : R(0)) : R(0.1) * (q2 * q3);
+            t2 = z ? (s2 == R(0) ? R(0.6) : R(0)) : R(0.6) * (q1 * q3);
+            t3 = z ? (s3 == R(0) ? R(0.3) : R(0)) : R(0.3) * (q1 * q2);
         }
     }
 };
