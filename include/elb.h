@@ -18,7 +18,8 @@
  *  - Host arrays are caller-owned and copied before the call returns.
  *  - Device memory is caller-owned: the caller allocates elb_workspace_bytes() bytes of
  *    device memory (256-byte aligned) and passes it to elb_create; the library keeps no
- *    other device allocation.  The workspace must outlive the context.
+ *    other device allocation (a context or batch also holds up to 256 KB of pinned host memory
+ *    for its copies).  The workspace must outlive the context.
  *  - Work is enqueued on the HIP stream given to elb_create (NULL = default stream).
  *    elb_step is asynchronous; calls that return host data synchronise that stream.
  *  - A context is used from one host thread at a time.  Distinct contexts are
@@ -37,7 +38,7 @@ typedef struct elb_ctx elb_ctx;
 
 typedef enum {
     ELB_OK = 0,
-    ELB_EINVAL = 1,        /* invalid parameter or input; nothing was launched          */
+    ELB_EINVAL = 1,        /* invalid parameter or input; nothing was changed           */
     ELB_ENOMEM = 2,        /* workspace too small or host allocation failed             */
     ELB_EHIP = 3,          /* HIP runtime error (message in elb_last_error)             */
     ELB_ENONFINITE = 4,    /* a cell reached n <= 0, T <= 0 or a non-finite moment      */

@@ -31,7 +31,7 @@ const int kSupportedQ[] = {8, 12, 16, 20, 24, 32, 40, 48, 64, 96, 200};
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t p, btd, bpd, bpf, sq, rsq, rec, cref, gref, ref, flag, seedb, psi[3], U[3], rows, out, cons, amp;
+    size_t p, btd, bpd, bpf, sq, rsq, rec, cref, gref, ref, rows, check, flag, seedb, psi[3], U[3], out, cons, amp;
     // learned closure (params.closure = 1)
     size_t corr, rows5, mparams, mwb, mnorm, pc, proj, outside, sx, sy;
     // chi_RET-FM (params.chi_mode = ELB_CHI_RETFM): ball-average weights
@@ -71,19 +71,22 @@ Layout make_layout(int nx, int Q, int N, int precision, int closure, int chi_rea
     L.sq = take(sizeof(double) * (QP + 2));
     L.rsq = take(sizeof(double) * (QP + 2));
     L.rec = take(sizeof(double) * 2 * QP);
-    L.cref = take(sizeof(double) * QP);
-    L.gref = take(sizeof(double) * Q);
-    L.ref = take(sizeof(double) * 2 * Q);
-    L.flag = take(sizeof(int) * 4);
+    // uploaded together when a state is set: reference tables, then the fields n, u, T
+    L.cref = take(sizeof(double) * (QP + 3 * (size_t)Q + 3 * (size_t)nx));
+    L.gref = L.cref + sizeof(double) * QP;
+    L.ref = L.gref + sizeof(double) * Q;
+    L.rows = L.ref + sizeof(double) * 2 * Q;
+    L.check = take(sizeof(StateCheck) * CHECK_BLOCKS);
     L.seedb = take(sizeof(unsigned));
     size_t lvl = (size_t)(nx + 2 * NG) * 2 * Q * elem_size(precision);
     for (int s = 0; s < 3; ++s) L.psi[s] = take(lvl);
     size_t ul = precision == ELB_FP32_MIXED ? sizeof(double) * 3 * (size_t)(nx + 2 * NG) : 0;
     for (int s = 0; s < 3; ++s) L.U[s] = take(ul);
-    L.rows = take(sizeof(double) * 3 * (size_t)(nx + 2 * NG));
-    L.out = take(sizeof(double) * 5 * (size_t)nx);
+    // the moment fields and, right behind them, the failure flag: one copy brings both
+    L.out = take(sizeof(double) * (5 * (size_t)nx + 2));
+    L.flag = L.out + sizeof(double) * 5 * (size_t)nx;
     L.cons = take(sizeof(double) * 3 * (size_t)nx);
-    L.amp = take(sizeof(double) * 2);
+    L.amp = take(sizeof(double) * 3);
     if (closure) {
         L.corr = take((size_t)elem_size(precision) * nx * Q);
         L.rows5 = take(sizeof(double) * 5 * (size_t)(nx + 2 * NG));
@@ -116,6 +119,47 @@ bool q_supported(int q)
 
 }  // namespace
 
+// Pinned host memory that the small uploads and downloads of a context (or of a batch, whose
+// contexts share one stream) go through: taken piece by piece, given back as a whole once the
+// stream has been waited for.  Allocated when the context or batch is created (first use costs
+// 0.1 to 0.3 ms), at most STAGE_MAX bytes.  Measured, us per copy with its wait: 16 KB to the
+// host 26 pageable, 12 pinned; 256 KB 116 and 20 (with the copy out of the pinned buffer); from
+// 512 KB (COPY_DIRECT) the runtime pins the caller's pages itself and takes 29, as the pinned
+// buffer does.
+constexpr size_t STAGE_MIN = size_t(1) << 14, STAGE_MAX = size_t(1) << 18, COPY_DIRECT = size_t(1) << 19;
+
+struct HostStage {
+    char *p = nullptr;
+    size_t cap = 0, used = 0;
+    ~HostStage() { if (p) (void)hipHostFree(p); }
+    // a buffer of `n` bytes within the limits above (none: everything is copied directly)
+    void reserve(size_t n)
+    {
+        cap = STAGE_MIN;
+        while (cap < n && cap < STAGE_MAX) cap *= 2;
+        if (hipHostMalloc(reinterpret_cast<void **>(&p), cap, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+            cap = 0;
+            return;
+        }
+        std::memset(p, 0, cap);  // first touch
+    }
+    // n bytes that no enqueued copy uses; NULL: more than the buffer holds
+    char *take(size_t n, hipStream_t st)
+    {
+        n = align256(n);
+        if (n > cap) return nullptr;
+        if (used + n > cap) {
+            if (hipStreamSynchronize(st) != hipSuccess) return nullptr;
+            used = 0;
+        }
+        char *at = p + used;
+        used += n;
+        return at;
+    }
+};
+
 struct elb_ctx {
     elb_params P;
     int Q = 0, N = 0;
@@ -123,6 +167,8 @@ struct elb_ctx {
     hipStream_t stream = nullptr;
     char *ws = nullptr;
     Layout L{};
+    HostStage own_stage;
+    HostStage *stage = &own_stage;  // a batch's contexts share the batch's
     std::vector<double> p, w, Btd;
     // deviation storage (FP32): reference state and its per-column distribution
     double n_ref = 0, u_ref = 0, T_ref = 1;
@@ -261,6 +307,14 @@ StageTable stage_table(int precision, int fixup)
     }
 }
 
+// bytes a context uploads to set a state, and downloads as moments
+size_t stage_bytes(const elb_params *p)
+{
+    const size_t nx = p->nx;
+    return std::max(align256(sizeof(double) * (padded_q(p->q) + 3 * (size_t)p->q + 3 * nx)),
+                    align256(sizeof(double) * (5 * nx + 2)));
+}
+
 // The stage kernel of a problem: its first compiled tile whose number of blocks is at most the
 // tile's cap (stage_kernels.hip has the caps and what they were measured on).
 const StageKernel *pick_stage(const elb_params *p, int ret, int closure)
@@ -393,73 +447,108 @@ void drop_ctx_graph(elb_ctx *c)
 
 // Reference equilibrium of the deviation storage (FP32 modes): the mean state (n_r, u_r,
 // T_r) of the given cells; phi_ref_k = n_r g_k(u_r, T_r), theta_ref_k = 2 T_r phi_ref_k, the
-// coefficients n_r c_l(u_r, T_r) and the FP64 reference sums.  FP64 storage: all zero.
-int set_reference(elb_ctx *c, double n_r, double u_r, double T_r)
+// coefficients n_r c_l(u_r, T_r) and the FP64 reference sums.  FP64 storage: all zero.  Writes
+// the tables as they are uploaded: cref [QP], gref [Q], ref [2Q].
+void make_reference(elb_ctx *c, double n_r, double u_r, double T_r, double *tables)
 {
     drop_ctx_graph(c);  // the stage arguments carry the reference sums
     int Q = c->Q, QP = padded_q(Q), N = c->N;
-    std::vector<double> cref(QP, 0.0), gref(Q, 0.0);
+    double *cref = tables, *gref = tables + QP;
+    std::fill(tables, tables + QP + 3 * (size_t)Q, 0.0);
     c->ref.assign(2 * Q, 0.0);
     for (int m = 0; m < 6; ++m) c->ref_sum[m] = 0.0;
     c->n_ref = n_r; c->u_ref = u_r; c->T_ref = T_r;
-    if (c->P.precision != ELB_FP64) {
-        std::vector<double> cc(QP, 0.0);
-        cc[0] = 1.0;
-        if (N >= 1) cc[1] = u_r;
-        for (int l = 1; l < N; ++l)
-            cc[l + 1] = (u_r * cc[l] + (T_r - 1.0) * std::sqrt((double)l) * cc[l - 1]) / std::sqrt((double)(l + 1));
-        for (int l = 0; l <= N; ++l) cref[l] = n_r * cc[l];
-        for (int k = 0; k < Q; ++k) {
-            double g = 0.0;
-            for (int l = 0; l <= N; ++l) g += c->Btd[(size_t)l * QP + k] * cref[l];
-            gref[k] = g;
-            c->ref[k] = g;
-            c->ref[Q + k] = 2.0 * T_r * g;
-        }
-        for (int k = 0; k < Q; ++k) {
-            double pk = c->p[k];
-            c->ref_sum[0] += c->ref[k];
-            c->ref_sum[1] += pk * c->ref[k];
-            c->ref_sum[2] += pk * pk * c->ref[k];
-            c->ref_sum[3] += pk * pk * pk * c->ref[k];
-            c->ref_sum[4] += c->ref[Q + k];
-            c->ref_sum[5] += pk * c->ref[Q + k];
-        }
+    if (c->P.precision == ELB_FP64) return;
+    std::vector<double> cc(QP, 0.0);
+    cc[0] = 1.0;
+    if (N >= 1) cc[1] = u_r;
+    for (int l = 1; l < N; ++l)
+        cc[l + 1] = (u_r * cc[l] + (T_r - 1.0) * std::sqrt((double)l) * cc[l - 1]) / std::sqrt((double)(l + 1));
+    for (int l = 0; l <= N; ++l) cref[l] = n_r * cc[l];
+    for (int l = 0; l <= N; ++l)
+        for (int k = 0; k < Q; ++k) gref[k] += c->Btd[(size_t)l * QP + k] * cref[l];
+    for (int k = 0; k < Q; ++k) {
+        c->ref[k] = gref[k];
+        c->ref[Q + k] = 2.0 * T_r * gref[k];
     }
-    hipError_t e = hipMemcpyAsync(c->dev<double>(c->L.cref), cref.data(), sizeof(double) * QP, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.gref), gref.data(), sizeof(double) * Q, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.ref), c->ref.data(), sizeof(double) * 2 * Q, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    return hip_check(c, e, "reference upload");
+    std::copy(c->ref.begin(), c->ref.end(), tables + QP + Q);
+    for (int k = 0; k < Q; ++k) {
+        double pk = c->p[k];
+        c->ref_sum[0] += c->ref[k];
+        c->ref_sum[1] += pk * c->ref[k];
+        c->ref_sum[2] += pk * pk * c->ref[k];
+        c->ref_sum[3] += pk * pk * pk * c->ref[k];
+        c->ref_sum[4] += c->ref[Q + k];
+        c->ref_sum[5] += pk * c->ref[Q + k];
+    }
 }
 
-// Fill all three levels (every row, ghosts included) with the equilibrium of the row
-// fields held in the `rows` buffer.
-int init_levels_from_rows(elb_ctx *c)
+// Copies `bytes` from the host to the workspace in stream order: through the pinned buffer, or
+// directly (and then waiting) when they are many.  The source may change after the return.
+int upload(elb_ctx *c, size_t off, const void *src, size_t bytes)
 {
-    int R = c->P.nx + 2 * NG, Q = c->Q, QP = padded_q(Q);
-    const int threads = 256;
-    const unsigned blocks = (unsigned)(((size_t)R * Q + threads - 1) / threads);
-    const double *rn = c->dev<double>(c->L.rows);
-    const double *ru = rn + R, *rT = rn + 2 * R;
-    bool book = c->P.precision == ELB_FP32_MIXED;
+    for (size_t at = 0; at < bytes;) {
+        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap;
+        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap / 2);
+        char *st = direct ? nullptr : c->stage->take(n, c->stream);
+        if (st) std::memcpy(st, (const char *)src + at, n);
+        hipError_t e = hipMemcpyAsync(c->dev<char>(off + at), st ? st : (const char *)src + at, n, hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess && !st) e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return hip_check(c, e, "copy to the device");
+        at += n;
+    }
+    return ELB_OK;
+}
+
+// make_reference and its upload.
+int set_reference(elb_ctx *c, double n_r, double u_r, double T_r)
+{
+    std::vector<double> tables(padded_q(c->Q) + 3 * (size_t)c->Q);
+    make_reference(c, n_r, u_r, T_r, tables.data());
+    return upload(c, c->L.cref, tables.data(), sizeof(double) * tables.size());
+}
+
+// Sets level 0 and the ghost rows of every level to the equilibrium of the fields n, u, T held
+// in the `rows` buffer, and clears the failure flag.
+int init_levels(elb_ctx *c)
+{
+    InitArgs a{};
     for (int s = 0; s < 3; ++s) {
-        double *U = book ? c->dev<double>(c->L.U[s]) : nullptr;
-        if (c->P.precision == ELB_FP64)
-            hipLaunchKernelGGL(k_init_equilibrium<double>, dim3(blocks), dim3(threads), 0, c->stream,
-                               c->dev<double>(c->L.psi[s]), U, rn, ru, rT, c->dev<double>(c->L.btd),
-                               c->dev<double>(c->L.sq), c->dev<double>(c->L.rsq),
-                               c->dev<double>(c->L.ref), R, Q, QP, c->N);
-        else
-            hipLaunchKernelGGL(k_init_equilibrium<float>, dim3(blocks), dim3(threads), 0, c->stream,
-                               c->dev<float>(c->L.psi[s]), U, rn, ru, rT, c->dev<double>(c->L.btd),
-                               c->dev<double>(c->L.sq), c->dev<double>(c->L.rsq),
-                               c->dev<double>(c->L.ref), R, Q, QP, c->N);
+        a.psi[s] = c->ws + c->L.psi[s];
+        a.U[s] = c->P.precision == ELB_FP32_MIXED ? c->dev<double>(c->L.U[s]) : nullptr;
+    }
+    a.fields = c->dev<double>(c->L.rows);
+    a.Bt = c->dev<double>(c->L.btd);
+    a.sq = c->dev<double>(c->L.sq);
+    a.rsq = c->dev<double>(c->L.rsq);
+    a.ref = c->dev<double>(c->L.ref);
+    a.flag = c->dev<int>(c->L.flag);
+    for (int j = 0; j < 3; ++j) {
+        a.ghost[0][j] = c->P.ghost_left[j];
+        a.ghost[1][j] = c->P.ghost_right[j];
+    }
+    a.nx = c->P.nx;
+    a.Q = c->Q;
+    a.QP = padded_q(c->Q);
+    a.N = c->N;
+    a.periodic = c->P.bc == ELB_BC_PERIODIC;
+    const size_t R = (size_t)c->P.nx + 2 * NG;
+    const bool f64 = c->P.precision == ELB_FP64;
+    if ((double)R * c->Q * c->N >= INIT_TILES) {
+        const int rows = init_rows(c->Q);
+        const dim3 grid((unsigned)((R + rows - 1) / rows));
+        const size_t lds = sizeof(double) * (size_t)rows * (c->N + 1);
+        if (f64) hipLaunchKernelGGL(k_init_tiles<double>, grid, dim3(INIT_THREADS), lds, c->stream, a, rows);
+        else hipLaunchKernelGGL(k_init_tiles<float>, grid, dim3(INIT_THREADS), lds, c->stream, a, rows);
+    } else {
+        const dim3 grid((unsigned)((R * c->Q + INIT_THREADS - 1) / INIT_THREADS));
+        if (f64) hipLaunchKernelGGL(k_init_equilibrium<double>, grid, dim3(INIT_THREADS), 0, c->stream, a);
+        else hipLaunchKernelGGL(k_init_equilibrium<float>, grid, dim3(INIT_THREADS), 0, c->stream, a);
     }
     return hip_check(c, hipGetLastError(), "init kernel launch");
 }
 
-int run_moments(elb_ctx *c)
+int run_moments(elb_ctx *c, bool conserved = false)
 {
     int nx = c->P.nx, Q = c->Q;
     double *o = c->dev<double>(c->L.out);
@@ -470,12 +559,36 @@ int run_moments(elb_ctx *c)
     if (c->P.precision == ELB_FP64)
         hipLaunchKernelGGL(k_moments<double>, dim3(blocks), dim3(threads), 0, c->stream,
                            c->dev<double>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, o + nx,
-                           o + 2 * nx, o + 3 * nx, o + 4 * nx, c->dev<double>(c->L.cons));
+                           o + 2 * nx, o + 3 * nx, o + 4 * nx, conserved ? c->dev<double>(c->L.cons) : nullptr);
     else
         hipLaunchKernelGGL(k_moments<float>, dim3(blocks), dim3(threads), 0, c->stream,
                            c->dev<float>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, o + nx,
-                           o + 2 * nx, o + 3 * nx, o + 4 * nx, c->dev<double>(c->L.cons));
+                           o + 2 * nx, o + 3 * nx, o + 4 * nx, conserved ? c->dev<double>(c->L.cons) : nullptr);
     return hip_check(c, hipGetLastError(), "moments kernel launch");
+}
+
+// Copies `bytes` from the workspace to the host, waiting for the stream: through the pinned
+// buffer, or directly when they are many.
+int download(elb_ctx *c, void *dst, size_t off, size_t bytes)
+{
+    for (size_t at = 0; at < bytes;) {
+        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap;
+        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap);
+        char *st = direct ? nullptr : c->stage->take(n, c->stream);
+        hipError_t e = hipMemcpyAsync(st ? st : (char *)dst + at, c->dev<char>(off + at), n, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return hip_check(c, e, "copy to the host");
+        if (st) std::memcpy((char *)dst + at, st, n);
+        c->stage->used = 0;  // the stream has been waited for
+        at += n;
+    }
+    return ELB_OK;
+}
+
+int flag_status(elb_ctx *c, int flag)
+{
+    if (flag) return fail(c, ELB_ENONFINITE, "a cell reached n <= 0, T <= 0 or non-finite moments");
+    return ELB_OK;
 }
 
 int check_flag(elb_ctx *c)
@@ -486,8 +599,8 @@ int check_flag(elb_ctx *c)
     if (rc) return rc;
     rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
     if (rc) return rc;
-    if (flag) return fail(c, ELB_ENONFINITE, "a cell reached n <= 0, T <= 0 or non-finite moments");
-    return ELB_OK;
+    c->stage->used = 0;
+    return flag_status(c, flag);
 }
 
 }  // namespace
@@ -528,7 +641,12 @@ int64_t elb_workspace_bytes(const elb_params *p)
     return (int64_t)make_layout(p->nx, p->q, N, p->precision, p->closure, fm_reach(p)).total;
 }
 
-int elb_create(const elb_params *p, void *dev_workspace, int64_t workspace_bytes, void *hip_stream,
+}  // extern "C"
+
+namespace {
+
+// elb_create; `stage` is the pinned buffer of the batch that the context belongs to, or NULL.
+int create_ctx(const elb_params *p, void *dev_workspace, int64_t workspace_bytes, void *hip_stream, HostStage *stage,
                elb_ctx **out)
 {
     if (!out) return ELB_EINVAL;
@@ -607,54 +725,96 @@ int elb_create(const elb_params *p, void *dev_workspace, int64_t workspace_bytes
         delete c;
         return ELB_EHIP;
     }
+    if (stage) c->stage = stage;
+    else c->own_stage.reserve(stage_bytes(p));
     if (set_reference(c, 1.0, 0.0, 1.0) != ELB_OK) { g_create_error = c->err; delete c; return ELB_EHIP; }
     *out = c;
     return ELB_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int elb_create(const elb_params *p, void *dev_workspace, int64_t workspace_bytes, void *hip_stream, elb_ctx **out)
+{
+    return create_ctx(p, dev_workspace, workspace_bytes, hip_stream, nullptr, out);
 }
 
 int elb_set_state_moments(elb_ctx *c, const double *n, const double *u, const double *T)
 {
     if (!c) return ELB_EINVAL;
     if (!n || !u || !T) return fail(c, ELB_EINVAL, "NULL input array");
-    int nx = c->P.nx, R = nx + 2 * NG;
-    std::vector<double> rows(3 * (size_t)R);
-    double min_tau = 1e300;
-    for (int i = 0; i < nx; ++i) {
-        if (!(n[i] > 0) || !(T[i] > 0) || !std::isfinite(n[i]) || !std::isfinite(u[i]) || !std::isfinite(T[i]))
-            return fail(c, ELB_EINVAL, "cell %d: need finite n > 0, T > 0", i);
-        if (0.25 * c->b * n[i] >= 0.99) return fail(c, ELB_EINVAL, "cell %d: reduced density eta >= 0.99", i);
-        min_tau = std::fmin(min_tau, host_tau(c, n[i], T[i]));
+    const int nx = c->P.nx;
+    const size_t nb = sizeof(double) * nx, tables = sizeof(double) * (padded_q(c->Q) + 3 * (size_t)c->Q);
+    // the reference tables and the fields in one upload; fields too large for the pinned
+    // buffer are copied from the caller's arrays
+    char *up = c->stage->take(tables + 3 * nb, c->stream);
+    const bool staged = up != nullptr;
+    if (staged) {
+        std::memcpy(up + tables, n, nb);
+        std::memcpy(up + tables + nb, u, nb);
+        std::memcpy(up + tables + 2 * nb, T, nb);
     }
-    for (int r = 0; r < R; ++r) {
-        int cell = r - NG;
-        double vn, vu, vT;
-        if (cell >= 0 && cell < nx) { vn = n[cell]; vu = u[cell]; vT = T[cell]; }
-        else if (c->P.bc == ELB_BC_PERIODIC) {
-            int w = ((cell % nx) + nx) % nx;
-            vn = n[w]; vu = u[w]; vT = T[w];
-        } else {
-            const double *g = cell < 0 ? c->P.ghost_left : c->P.ghost_right;
-            vn = g[0]; vu = g[1]; vT = g[2];
-            min_tau = std::fmin(min_tau, host_tau(c, vn, vT));
-        }
-        rows[r] = vn; rows[R + r] = vu; rows[2 * R + r] = vT;
+    const double *src[3] = {n, u, T};
+    auto upload_fields = [&]() {
+        if (staged)
+            return hip_check(c, hipMemcpyAsync(c->dev<char>(c->L.rows), up + tables, 3 * nb, hipMemcpyHostToDevice, c->stream),
+                             "rows copy");
+        for (int f = 0; f < 3; ++f)
+            if (int rc = upload(c, c->L.rows + f * nb, src[f], nb)) return rc;
+        return (int)ELB_OK;
+    };
+    // Every cell is checked, and the smallest tau found, before the state is touched (the
+    // `rows` buffer is not part of it): on the host for few cells, on the GPU for many.  The
+    // host takes about 15 ns per cell (a square root and two divisions for tau), the GPU about
+    // 20 us more of launch and wait.  Meanwhile the host adds up the mean state, whose order
+    // of summation fixes the bits of the FP32 modes.
+    StateCheck sum{};
+    double sn = 0, su = 0, sT = 0;
+    auto mean_state = [&]() {
+        if (c->P.precision != ELB_FP64)  // FP64 storage has no reference state
+            for (int i = 0; i < nx; ++i) { sn += n[i]; su += u[i]; sT += T[i]; }
+    };
+    const bool on_gpu = nx > CHECK_HOST_CELLS;
+    if (on_gpu) {
+        int rc = upload_fields();
+        if (rc) return rc;
+        const int blocks = std::min(CHECK_BLOCKS, (nx + CHECK_THREADS - 1) / CHECK_THREADS);
+        hipLaunchKernelGGL(k_check_state, dim3(blocks), dim3(CHECK_THREADS), 0, c->stream, c->dev<double>(c->L.rows), nx, c->b,
+                           c->mu_ref, c->dev<StateCheck>(c->L.check));
+        rc = hip_check(c, hipGetLastError(), "check kernel launch");
+        if (rc) return rc;
+        mean_state();
+        StateCheck part[CHECK_BLOCKS];
+        rc = download(c, part, c->L.check, sizeof(StateCheck) * blocks);
+        if (rc) return rc;
+        sum = part[0];
+        for (int i = 1; i < blocks; ++i) sum.add(part[i]);
+    } else {
+        sum.clear();
+        for (int i = 0; i < nx; ++i) sum.cell(i, n[i], u[i], T[i], c->b, c->mu_ref);
+        mean_state();
     }
+    if (sum.bad < (unsigned)nx && sum.bad <= sum.dense)
+        return fail(c, ELB_EINVAL, "cell %u: need finite n > 0, T > 0", sum.bad);
+    if (sum.dense < (unsigned)nx) return fail(c, ELB_EINVAL, "cell %u: reduced density eta >= 0.99", sum.dense);
+    double min_tau = sum.min_tau;
+    if (c->P.bc == ELB_BC_EQUILIBRIUM)
+        for (const double *g : {c->P.ghost_left, c->P.ghost_right}) min_tau = std::fmin(min_tau, host_tau(c, g[0], g[2]));
     if (c->dt > 2.5 * min_tau)
         return fail(c, ELB_EINVAL, "dt = %g exceeds the RK3 stability limit 2.5 min tau = %g", c->dt, 2.5 * min_tau);
-    {
-        double sn = 0, su = 0, sT = 0;
-        for (int i = 0; i < nx; ++i) { sn += n[i]; su += u[i]; sT += T[i]; }
-        int rr = set_reference(c, sn / nx, su / nx, sT / nx);
-        if (rr) return rr;
+    const double n_r = sn / nx, u_r = su / nx, T_r = sT / nx;
+    int rc;
+    if (on_gpu || !staged) {
+        rc = set_reference(c, n_r, u_r, T_r);
+        if (!rc && !on_gpu) rc = upload_fields();
+    } else {
+        make_reference(c, n_r, u_r, T_r, reinterpret_cast<double *>(up));
+        rc = hip_check(c, hipMemcpyAsync(c->dev<char>(c->L.cref), up, tables + 3 * nb, hipMemcpyHostToDevice, c->stream),
+                       "state upload");
     }
-    int rc = hip_check(c, hipMemcpyAsync(c->dev<double>(c->L.rows), rows.data(), sizeof(double) * rows.size(),
-                                         hipMemcpyHostToDevice, c->stream), "rows copy");
-    if (rc) return rc;
-    rc = init_levels_from_rows(c);
-    if (rc) return rc;
-    rc = hip_check(c, hipMemsetAsync(c->dev<int>(c->L.flag), 0, sizeof(int) * 4, c->stream), "flag reset");
-    if (rc) return rc;
-    rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
+    if (!rc) rc = init_levels(c);
     if (rc) return rc;
     c->has_state = true;
     c->steps = 0;
@@ -800,8 +960,9 @@ int elb_step(elb_ctx *c, int64_t nsteps)
             if (rc) return rc;
         }
         for (; nsteps - done >= GRAPH_STEPS; done += GRAPH_STEPS) {
-            hipLaunchKernelGGL(k_set_seed, dim3(1), dim3(64), 0, c->stream, c->dev<unsigned>(c->L.seedb),
-                               c->launches);
+            if (c->P.precision != ELB_FP64)  // FP64 stores are not dithered
+                hipLaunchKernelGGL(k_set_seed, dim3(1), dim3(64), 0, c->stream, c->dev<unsigned>(c->L.seedb),
+                                   c->launches);
             hipError_t e = hipGraphLaunch(c->graph, c->stream);
             if (e != hipSuccess) return fail(c, ELB_EHIP, "graph launch: %s", hipGetErrorString(e));
             c->launches += 3 * GRAPH_STEPS;
@@ -826,15 +987,24 @@ int elb_get_moments(elb_ctx *c, double *n, double *u, double *T, double *qx, dou
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
     int rc = run_moments(c);
     if (rc) return rc;
-    int nx = c->P.nx;
+    const size_t nx = c->P.nx;
     double *dst[5] = {n, u, T, qx, pxx};
-    for (int f = 0; f < 5; ++f)
-        if (dst[f]) {
-            rc = hip_check(c, hipMemcpyAsync(dst[f], c->dev<double>(c->L.out) + (size_t)f * nx, sizeof(double) * nx,
-                                             hipMemcpyDeviceToHost, c->stream), "moments copy");
-            if (rc) return rc;
-        }
-    return check_flag(c);
+    // fields and flag in one copy when the pinned buffer holds them, else field by field
+    const size_t bytes = sizeof(double) * (5 * nx + 2);
+    if (char *st = c->stage->take(bytes, c->stream)) {
+        rc = hip_check(c, hipMemcpyAsync(st, c->dev<char>(c->L.out), bytes, hipMemcpyDeviceToHost, c->stream), "moments copy");
+        if (!rc) rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
+        if (rc) return rc;
+        c->stage->used = 0;
+        for (int f = 0; f < 5; ++f)
+            if (dst[f]) std::memcpy(dst[f], st + sizeof(double) * f * nx, sizeof(double) * nx);
+        int flag;
+        std::memcpy(&flag, st + sizeof(double) * 5 * nx, sizeof flag);
+        return flag_status(c, flag);
+    }
+    for (int f = 0; f < 5 && !rc; ++f)
+        if (dst[f]) rc = download(c, dst[f], c->L.out + sizeof(double) * f * nx, sizeof(double) * nx);
+    return rc ? rc : check_flag(c);
 }
 
 int elb_get_amplitudes(elb_ctx *c, double k, double out[2])
@@ -842,16 +1012,38 @@ int elb_get_amplitudes(elb_ctx *c, double k, double out[2])
     if (!c) return ELB_EINVAL;
     if (!out || !std::isfinite(k)) return fail(c, ELB_EINVAL, "NULL output or non-finite k");
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
-    int rc = run_moments(c);
+    const int nx = c->P.nx, Q = c->Q;
+    double *amp = c->dev<double>(c->L.amp);
+    const int *flag = c->dev<int>(c->L.flag);
+    const double *U = c->P.precision == ELB_FP32_MIXED ? c->dev<double>(c->L.U[0]) : nullptr;
+    const double *dens = c->dev<double>(c->L.out);
+    // With bookkeeping, and for few cells, one kernel forms the densities and projects them;
+    // else the moment kernel spreads the cells over the chip first.  The line: the one block
+    // takes about 0.8 us per 64 cells and 16 nodes, the extra launch 6 us.
+    const bool direct = U || (size_t)nx * ((Q + MOM_LANES - 1) / MOM_LANES) <= AMP_DIRECT;
+    if (!direct) {
+        int rc = run_moments(c);
+        if (rc) return rc;
+    }
+    if (U || !direct)
+        hipLaunchKernelGGL((k_amplitudes<double, true>), dim3(1), dim3(AMP_THREADS), 0, c->stream, (const double *)nullptr,
+                           (const double *)nullptr, U ? U + 3 * NG : dens, U ? 3 : 1, nx, Q, c->P.x0, c->dx, k, flag, amp);
+    else if (c->P.precision == ELB_FP64)
+        hipLaunchKernelGGL((k_amplitudes<double, false>), dim3(1), dim3(AMP_THREADS), 0, c->stream,
+                           c->dev<double>(c->L.psi[0]), c->dev<double>(c->L.ref), (const double *)nullptr, 0, nx, Q, c->P.x0, c->dx,
+                           k, flag, amp);
+    else
+        hipLaunchKernelGGL((k_amplitudes<float, false>), dim3(1), dim3(AMP_THREADS), 0, c->stream,
+                           c->dev<float>(c->L.psi[0]), c->dev<double>(c->L.ref), (const double *)nullptr, 0, nx, Q, c->P.x0, c->dx,
+                           k, flag, amp);
+    int rc = hip_check(c, hipGetLastError(), "amplitude kernel launch");
     if (rc) return rc;
-    hipLaunchKernelGGL(k_amplitudes, dim3(1), dim3(AMP_THREADS), 0, c->stream, c->dev<double>(c->L.out),
-                       c->P.nx, c->P.x0, c->dx, k, c->dev<double>(c->L.amp));
-    rc = hip_check(c, hipGetLastError(), "amplitude kernel launch");
+    double v[3];
+    rc = download(c, v, c->L.amp, sizeof v);
     if (rc) return rc;
-    rc = hip_check(c, hipMemcpyAsync(out, c->dev<double>(c->L.amp), 2 * sizeof(double), hipMemcpyDeviceToHost,
-                                     c->stream), "amplitude copy");
-    if (rc) return rc;
-    return check_flag(c);
+    out[0] = v[0];
+    out[1] = v[1];
+    return flag_status(c, v[2] != 0.0);
 }
 
 int elb_get_dist(elb_ctx *c, double *phi, double *theta)
@@ -878,7 +1070,7 @@ int elb_get_conserved(elb_ctx *c, double out[3])
 {
     if (!c || !out) return ELB_EINVAL;
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
-    int rc = run_moments(c);
+    int rc = run_moments(c, true);
     if (rc) return rc;
     int nx = c->P.nx;
     std::vector<double> cons(3 * (size_t)nx);
@@ -951,6 +1143,7 @@ struct BatchGroup {
 
 struct elb_batch {
     int count = 0, precision = 0;
+    HostStage stage;  // shared by the contexts (one stream)
     hipStream_t stream = nullptr;
     char *ws = nullptr;
     InstDesc *d_inst = nullptr;
@@ -1083,12 +1276,15 @@ InstDesc describe(const elb_ctx *c)
     return d;
 }
 
-int upload_descriptors(elb_batch *b)
+// Device descriptor of instance i.  A captured graph reads the descriptors from device memory
+// and stays valid.
+int upload_descriptor(elb_batch *b, int i)
 {
-    std::vector<InstDesc> h(b->count);
-    for (int i = 0; i < b->count; ++i) h[i] = describe(b->ctx[i]);
-    hipError_t e = hipMemcpyAsync(b->d_inst, h.data(), sizeof(InstDesc) * h.size(), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    const InstDesc d = describe(b->ctx[i]);
+    char *up = b->stage.take(sizeof d, b->stream);
+    if (up) std::memcpy(up, &d, sizeof d);
+    hipError_t e = hipMemcpyAsync(b->d_inst + i, up ? (const void *)up : &d, sizeof d, hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess && !up) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return bfail(b, ELB_EHIP, "descriptor upload: %s", hipGetErrorString(e));
     return ELB_OK;
 }
@@ -1259,9 +1455,12 @@ int elb_batch_create(const elb_params *params, int32_t count, void *dev_workspac
     b->d_inst = reinterpret_cast<InstDesc *>(b->ws + L.inst);
     b->seed_dev = reinterpret_cast<unsigned *>(b->ws + L.seedb);
     b->ctx.assign(count, nullptr);
+    size_t moved = 0;  // room for the uploads of several instances
+    for (int i = 0; i < count; ++i) moved = std::min(STAGE_MAX, moved + stage_bytes(&params[i]));
+    b->stage.reserve(moved);
     for (int i = 0; i < count; ++i) {
         int64_t bytes = elb_workspace_bytes(&params[i]);
-        rc = elb_create(&params[i], b->ws + L.ctx[i], bytes, hip_stream, &b->ctx[i]);
+        rc = create_ctx(&params[i], b->ws + L.ctx[i], bytes, hip_stream, &b->stage, &b->ctx[i]);
         if (rc) {
             g_batch_create_error = "instance " + std::to_string(i) + ": " + elb_last_error(nullptr);
             for (auto c : b->ctx) if (c) elb_destroy(c);
@@ -1329,8 +1528,7 @@ int elb_batch_set_state_moments(elb_batch *b, int32_t inst, const double *n, con
     int rc = elb_set_state_moments(b->ctx[inst], n, u, T);
     if (rc) return bfail(b, rc, "instance %d: %s", inst, elb_last_error(b->ctx[inst]));
     b->launches = 0;
-    drop_graph(b);  // the reference state of the instance may have changed
-    return upload_descriptors(b);
+    return upload_descriptor(b, inst);
 }
 
 int elb_batch_step(elb_batch *b, int64_t nsteps)
@@ -1347,7 +1545,8 @@ int elb_batch_step(elb_batch *b, int64_t nsteps)
             if (rc) return rc;
         }
         while (nsteps - done >= chunk) {
-            hipLaunchKernelGGL(k_set_seed, dim3(1), dim3(64), 0, b->stream, b->seed_dev, b->launches);
+            if (b->precision != ELB_FP64)  // FP64 stores are not dithered
+                hipLaunchKernelGGL(k_set_seed, dim3(1), dim3(64), 0, b->stream, b->seed_dev, b->launches);
             hipError_t e = hipGraphLaunch(b->graph, b->stream);
             if (e != hipSuccess) return bfail(b, ELB_EHIP, "graph launch: %s", hipGetErrorString(e));
             done += chunk;

@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "elb_kernels.h"
 
 namespace elb {
@@ -14,36 +16,226 @@ __global__ void k_set_seed(unsigned *base, unsigned value)
 }
 
 // --------------------------------------------------------------------------------------
-// Equilibrium initialisation of rows [0, rows): phi_k = n g_k(u,T), theta_k = 2 T n g_k,
-// g_k = sum_l Bt[l][k] c_l(u, T) in FP64 (QP-strided table), minus the per-column reference
-// (zero in FP64 storage).  One thread per (row, node).  With U != NULL also the conserved
-// densities (n, n u, (n u^2 + 3 n T)/2) of every row.
+// Check of the fields a state is set from: the first cell without finite n > 0, u, T > 0 and
+// the first with a reduced density of 0.99 or more (UINT_MAX: none) and the smallest relaxation
+// time.  One cell at a time on the host, or one partial result per block of k_check_state.
 // --------------------------------------------------------------------------------------
-template <typename R>
-__global__ void k_init_equilibrium(R *psi, double *U, const double *nrow, const double *urow,
-                                   const double *Trow, const double *Bt, const double *sq,
-                                   const double *rsq, const double *ref, int rows, int Q, int QP,
-                                   int N)
+constexpr int CHECK_THREADS = 256, CHECK_BLOCKS = 64, CHECK_HOST_CELLS = 2048;
+
+struct StateCheck {
+    double min_tau;
+    unsigned bad, dense;
+
+    __host__ __device__ void clear()
+    {
+        min_tau = 1e300;
+        bad = dense = 0xffffffffu;
+    }
+    __host__ __device__ void cell(unsigned i, double vn, double vu, double vT, double b, double mu_ref)
+    {
+        if (!(vn > 0) || !(vT > 0) || !(fabs(vn) < HUGE_VAL) || !(fabs(vu) < HUGE_VAL) || !(fabs(vT) < HUGE_VAL)) {
+            bad = i < bad ? i : bad;
+            return;
+        }
+        const double eta = 0.25 * b * vn;
+        if (eta >= 0.99) {
+            dense = i < dense ? i : dense;
+            return;
+        }
+        const double chi = 0.5 * (2.0 - eta) / ((1.0 - eta) * (1.0 - eta) * (1.0 - eta));
+        const double y = b * vn * chi;
+        const double cm = (4.0 / 25.0) * (1.0 + 12.0 / M_PI);
+        min_tau = fmin(min_tau, mu_ref * (1.0 + 0.8 * y + cm * y * y) / (vn * chi * sqrt(vT)));
+    }
+    __host__ __device__ void add(const StateCheck &o)
+    {
+        min_tau = fmin(min_tau, o.min_tau);
+        bad = o.bad < bad ? o.bad : bad;
+        dense = o.dense < dense ? o.dense : dense;
+    }
+};
+
+__global__ __launch_bounds__(CHECK_THREADS) void k_check_state(const double *fields, int nx, double b, double mu_ref,
+                                                               StateCheck *part)
 {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;  // rows * Q may pass 2^31
-    if (idx >= (size_t)rows * Q) return;
+    __shared__ StateCheck sh[CHECK_THREADS];
+    StateCheck s;
+    s.clear();
+    for (int i = blockIdx.x * CHECK_THREADS + threadIdx.x; i < nx; i += gridDim.x * CHECK_THREADS)
+        s.cell(i, fields[i], fields[(size_t)nx + i], fields[2 * (size_t)nx + i], b, mu_ref);
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = CHECK_THREADS / 2; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) sh[threadIdx.x].add(sh[threadIdx.x + h]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+}
+
+// --------------------------------------------------------------------------------------
+// Equilibrium initialisation: phi_k = n g_k(u,T), theta_k = 2 T n g_k, g_k = sum_l Bt[l][k]
+// c_l(u, T) in FP64 (QP-strided table), minus the per-column reference (zero in FP64 storage);
+// with bookkeeping also the conserved densities (n, n u, (n u^2 + 3 n T)/2).  Interior rows of
+// level 0 and the ghost rows (end states, or periodic images) of all three levels: the
+// interior of the other two is written by the first stages before anything reads it.
+//
+// Two forms with the same arithmetic.  k_init_equilibrium: a thread per (row, node), which runs
+// its row's coefficient chain beside the sum over l; a launch takes 5 to 50 us (Q = 8 to 200,
+// tables cold) until the chip is full, then 320 us at 65536 cells, Q = 96.  k_init_tiles, for rows Q N >= INIT_TILES: the chain of a row once, by one
+// thread, into LDS, then the product with Bt, each thread 8 rows of 4 nodes, so that a table
+// value serves 8 rows and a coefficient read 4 nodes.  65536 cells, Q = 96: 100 us (FP64 117);
+// Q = 12: 14 us against 16, below the line.  Setting a state took three launches of the first
+// form, one per level: 950 us at 65536 cells, Q = 96; 91 at 160 cells, Q = 200, now 51.
+// --------------------------------------------------------------------------------------
+constexpr double INIT_TILES = 1e8;
+constexpr int INIT_THREADS = 256, INIT_RJ = 8, INIT_KJ = 4;
+
+// rows per block of k_init_tiles, within 64 KB of coefficients
+inline int init_rows(int Q) { return Q >= 200 ? 32 : Q >= 64 ? 64 : 128; }
+
+struct InitArgs {
+    void *psi[3];
+    double *U[3];        // bookkeeping mode, else NULL
+    const double *fields;  // n [nx], u [nx], T [nx]
+    const double *Bt, *sq, *rsq, *ref;
+    int *flag;
+    double ghost[2][3];
+    int nx, Q, QP, N, periodic;
+};
+
+// n, u, T of storage row r (interior, periodic image or end state)
+__device__ inline void init_fields(const InitArgs &a, int r, double &n, double &u, double &T)
+{
+    const int cell = r - NG;
+    if (a.periodic || (cell >= 0 && cell < a.nx)) {
+        const int i = row_of(cell, a.nx, a.periodic) - NG;
+        n = a.fields[i];
+        u = a.fields[(size_t)a.nx + i];
+        T = a.fields[2 * (size_t)a.nx + i];
+    } else {
+        const double *g = a.ghost[cell < 0 ? 0 : 1];
+        n = g[0]; u = g[1]; T = g[2];
+    }
+}
+
+// the two distribution values of (row r, node k), and with k == 0 the conserved densities
+template <typename R>
+__device__ inline void init_store(const InitArgs &a, int r, int k, double n, double u, double T, double g)
+{
+    const bool ghost = r < NG || r >= a.nx + NG;
+    const R phi = (R)(n * g - a.ref[k]), theta = (R)(2.0 * T * n * g - a.ref[a.Q + k]);
+    auto put = [&](void *psi, double *U) {
+        R *o = static_cast<R *>(psi) + (size_t)r * 2 * a.Q + k;
+        o[0] = phi;
+        o[a.Q] = theta;
+        if (U && k == 0) {
+            U[3 * (size_t)r + 0] = n;
+            U[3 * (size_t)r + 1] = n * u;
+            U[3 * (size_t)r + 2] = 0.5 * (n * u * u + 3.0 * n * T);
+        }
+    };
+    put(a.psi[0], a.U[0]);
+    if (ghost) {
+        put(a.psi[1], a.U[1]);
+        put(a.psi[2], a.U[2]);
+    }
+}
+
+template <typename R>
+__global__ __launch_bounds__(INIT_THREADS) void k_init_equilibrium(InitArgs a)
+{
+    const size_t idx = (size_t)blockIdx.x * INIT_THREADS + threadIdx.x;  // rows * Q may pass 2^31
+    if (idx < 4) a.flag[idx] = 0;
+    const int Q = a.Q, QP = a.QP;
+    if (idx >= (size_t)(a.nx + 2 * NG) * Q) return;
     const int r = (int)(idx / Q), k = (int)(idx - (size_t)r * Q);
-    double n = nrow[r], u = urow[r], T = Trow[r];
+    double n, u, T;
+    init_fields(a, r, n, u, T);
     double cm = 1.0, cc = u;
-    double g = Bt[k] * cm;
-    if (N >= 1) g += Bt[QP + k] * cc;
-    for (int l = 1; l < N; ++l) {
-        double cn = (u * cc + (T - 1.0) * sq[l] * cm) * rsq[l + 1];
+    double g = a.Bt[k] * cm;
+    if (a.N >= 1) g += a.Bt[QP + k] * cc;
+    for (int l = 1; l < a.N; ++l) {
+        double cn = (u * cc + (T - 1.0) * a.sq[l] * cm) * a.rsq[l + 1];
         cm = cc;
         cc = cn;
-        g += Bt[(l + 1) * QP + k] * cc;
+        g += a.Bt[(l + 1) * QP + k] * cc;
     }
-    psi[(size_t)r * 2 * Q + k] = (R)(n * g - ref[k]);
-    psi[(size_t)r * 2 * Q + Q + k] = (R)(2.0 * T * n * g - ref[Q + k]);
-    if (U && k == 0) {
-        U[3 * (size_t)r + 0] = n;
-        U[3 * (size_t)r + 1] = n * u;
-        U[3 * (size_t)r + 2] = 0.5 * (n * u * u + 3.0 * n * T);
+    init_store<R>(a, r, k, n, u, T, g);
+}
+
+template <typename R>
+__global__ __launch_bounds__(INIT_THREADS) void k_init_tiles(InitArgs a, int rows)
+{
+    extern __shared__ double coef[];  // [N + 1][rows]
+    __shared__ double f_n[128], f_u[128], f_T[128], sq_s[MAXQP], rsq_s[MAXQP];
+    constexpr int RJ = INIT_RJ, KJ = INIT_KJ;
+    const int r0 = blockIdx.x * rows;
+    const int nr = min(rows, a.nx + 2 * NG - r0);
+    const int t = threadIdx.x;
+    if (blockIdx.x == 0 && t < 4) a.flag[t] = 0;
+    if (t <= a.N) {
+        sq_s[t] = a.sq[t];
+        rsq_s[t] = a.rsq[t];
+    }
+    __syncthreads();
+    if (t < rows) {
+        double n, u, T;
+        init_fields(a, r0 + min(t, nr - 1), n, u, T);
+        f_n[t] = n;
+        f_u[t] = u;
+        f_T[t] = T;
+        double cm = 1.0, cc = u;
+        coef[t] = cm;
+        coef[rows + t] = cc;
+        for (int l0 = 1; l0 < a.N; l0 += 8) {  // the constants of 8 steps are read together
+            double s8[8], r8[8];
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {
+                s8[d] = sq_s[min(l0 + d, a.N)];
+                r8[d] = rsq_s[min(l0 + d + 1, a.N)];
+            }
+#pragma unroll
+            for (int d = 0; d < 8; ++d)
+                if (l0 + d < a.N) {
+                    double cn = (u * cc + (T - 1.0) * s8[d] * cm) * r8[d];
+                    cm = cc;
+                    cc = cn;
+                    coef[(l0 + d + 1) * rows + t] = cc;
+                }
+        }
+    }
+    __syncthreads();
+    const int Q = a.Q, QK = Q / KJ;  // every compiled Q is a multiple of 4
+    for (int it = t; it < QK * (rows / RJ); it += INIT_THREADS) {
+        const int grp = it / QK, k = it - grp * QK;  // nodes k, k + QK, ...
+        const double *c = coef + grp * RJ;
+        double g[KJ][RJ];
+#pragma unroll
+        for (int m = 0; m < KJ; ++m)
+#pragma unroll
+            for (int j = 0; j < RJ; ++j) g[m][j] = 0.0;
+        constexpr int LB = 4;  // orders whose table values are in flight together
+        for (int l = 0; l <= a.N; l += LB) {
+            double b[LB][KJ];
+#pragma unroll
+            for (int d = 0; d < LB; ++d)
+#pragma unroll
+                for (int m = 0; m < KJ; ++m) b[d][m] = a.Bt[min(l + d, a.N) * a.QP + k + m * QK];
+#pragma unroll
+            for (int d = 0; d < LB; ++d)
+                if (l + d <= a.N)
+#pragma unroll
+                    for (int m = 0; m < KJ; ++m)
+#pragma unroll
+                        for (int j = 0; j < RJ; ++j) g[m][j] = fma(b[d][m], c[(l + d) * rows + j], g[m][j]);
+        }
+#pragma unroll
+        for (int j = 0; j < RJ; ++j) {
+            const int r = grp * RJ + j;
+            if (r >= nr) break;
+#pragma unroll
+            for (int m = 0; m < KJ; ++m) init_store<R>(a, r0 + r, k + m * QK, f_n[r], f_u[r], f_T[r], g[m][j]);
+        }
     }
 }
 
@@ -134,9 +326,11 @@ __global__ void k_moments(const R *psi, const double *ref, const double *U, cons
         out_T[i] = U ? (2.0 * e2 / n - u * u) / 3.0 : e / (1.5 * n);
         out_q[i] = q;
         out_pxx[i] = pxx;
-        out_cons[3 * i + 0] = n;
-        out_cons[3 * i + 1] = j;
-        out_cons[3 * i + 2] = e2;
+        if (out_cons) {
+            out_cons[3 * i + 0] = n;
+            out_cons[3 * i + 1] = j;
+            out_cons[3 * i + 2] = e2;
+        }
     }
 }
 
