@@ -113,43 +113,86 @@ __device__ inline void mlp_forward_rows(MlpSmem &s, int wave, int lane, float *z
 }
 
 // --------------------------------------------------------------------------------------
-// Training forward: rows b < batch of x[index[b]] (or x[b]), normalised, through the MLP.
-// y [batch][16] (normalised outputs); a0 [batch][32] bf16 inputs and z [3][batch][64]
-// pre-activations are kept for the backward pass.
+// Training.  A minibatch of a few thousand rows is too small to fill the chip, so its kernels
+// are bound by latency, and each is cut into as many short blocks as the shapes give: 16 rows
+// per block forward and backward, the 64 columns of a layer spread over four waves, every
+// weight a wave needs loaded from L2 at the start (no staging in LDS); weight gradients by
+// (128-row chunk, layer), from operands that the forward and backward kernels leave in the
+// layout the matrix cores read.  Batch 4096, us per launch before (64 rows per block with
+// staged weights; gradients one block per chunk, transposing through LDS) and now: forward
+// 17.8 / 6.9, backward 17.3 / 7.0, weight gradients 75.6 / 5.7, reduction 8.6 / 3.2.
 // --------------------------------------------------------------------------------------
+constexpr int TRAIN_ROWS = 16;  // batch rows per block, forward and backward
+
+// Transposed bf16 operands, by chunks of WGRAD_ROWS rows: [chunk][column][WGRAD_ROWS]; the
+// place of (row b, column c) of a matrix of `cols` columns.
+__device__ inline size_t chunk_at(int b, int c, int cols)
+{
+    return ((size_t)(b / WGRAD_ROWS) * cols + c) * WGRAD_ROWS + b % WGRAD_ROWS;
+}
+
+// Training forward: rows b < batch of x[index[b]] (or x[b]), normalised, through the MLP.
+// y [batch][16] (normalised outputs).  Kept for the backward pass: z [3][batch][64]
+// pre-activations, and transposed by chunk the bf16 layer inputs a0t (32 columns) and at
+// (64 columns, layers 2..4, lstride apart).
 __global__ __launch_bounds__(256) void k_mlp_forward(const unsigned short *wb, const float *params,
                                                      const float *norm, const float *x,
                                                      const int *index, int batch, float *y,
-                                                     unsigned short *a0_out, float *z)
+                                                     unsigned short *a0t, unsigned short *at, size_t astride,
+                                                     float *z)
 {
-    __shared__ MlpSmem s;
-    mlp_stage_weights(s, wb, params);
+    __shared__ __attribute__((aligned(16))) unsigned short act[2][TRAIN_ROWS * AS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int row0 = blockIdx.x * MLP_ROWS + wave * 16;
-    // inputs: lane l fills row l % 16, columns 8 (l / 16) .. + 7
-    {
-        const int r = lane & 15, c0 = 8 * (lane >> 4);
-        const int b = row0 + r;
-        for (int c = c0; c < c0 + 8; ++c) {
-            float v = 0.f;
-            if (b < batch && c < MLP_IN) {
-                const int src = index ? index[b] : b;
-                v = (x[(size_t)src * MLP_IN + c] - norm[NRM_IN_MEAN + c]) / norm[NRM_IN_STD + c];
-            }
-            unsigned short h = f2bf(v);
-            s.act[wave][0][r * AS + c] = h;
-            if (b < batch) a0_out[(size_t)b * MLP_K1 + c] = h;
+    const int row0 = blockIdx.x * TRAIN_ROWS;
+    const int col = lane & 15, rq = 4 * (lane >> 4), kq = 8 * (lane >> 4);
+    const int c = wave * 16 + col;  // this lane's output column of the hidden layers
+    const bf16x8 w1 = ld8(wb + OFF_W1 + c * MLP_K1 + kq);
+    bf16x8 w2[2], w3[2], w4[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        w2[kk] = ld8(wb + OFF_W2 + c * MLP_H + kk * 32 + kq);
+        w3[kk] = ld8(wb + OFF_W3 + c * MLP_H + kk * 32 + kq);
+        w4[kk] = ld8(wb + OFF_W4 + col * MLP_H + kk * 32 + kq);
+    }
+    const float bias[3] = {params[OFF_B1 + c], params[OFF_B2 + c], params[OFF_B3 + c]};
+    const float bias4 = params[OFF_B4 + col];
+    // inputs: 16 rows of 32 columns, two per thread
+    for (int j = threadIdx.x; j < TRAIN_ROWS * MLP_K1; j += 256) {
+        const int r = j / MLP_K1, k = j % MLP_K1, b = row0 + r;
+        float v = 0.f;
+        if (b < batch && k < MLP_IN) {
+            const int src = index ? index[b] : b;
+            v = (x[(size_t)src * MLP_IN + k] - norm[NRM_IN_MEAN + k]) / norm[NRM_IN_STD + k];
         }
+        const unsigned short h = f2bf(v);
+        act[0][r * AS + k] = h;
+        a0t[chunk_at(b, k, MLP_K1)] = h;
     }
     __syncthreads();
-    const int nvalid = batch - row0;
-    floatx4 o;
-    mlp_forward_rows(s, wave, lane, row0 < batch ? z + (size_t)row0 * MLP_H : nullptr,
-                     (size_t)batch * MLP_H, nvalid, o);
-    const int col = lane & 15, rq = 4 * (lane >> 4);
+    const size_t zstride = (size_t)batch * MLP_H;
+    floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(act[0] + col * AS + kq), w1, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        unsigned short *out = act[(l + 1) & 1];
+        ushort4 h4;
+        unsigned short *h = reinterpret_cast<unsigned short *>(&h4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float zz = acc[r] + bias[l];
+            if (row0 + rq + r < batch) z[l * zstride + (size_t)(row0 + rq + r) * MLP_H + c] = zz;
+            h[r] = f2bf(silu(zz));
+            out[(rq + r) * AS + c] = h[r];
+        }
+        *reinterpret_cast<ushort4 *>(at + l * astride + chunk_at(row0 + rq, c, MLP_H)) = h4;
+        __syncthreads();
+        if (l == 2 && wave > 0) return;  // 16 outputs: one wave
+        const bf16x8 *w = l == 0 ? w2 : l == 1 ? w3 : w4;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(out + col * AS + kq), w[0], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(out + col * AS + 32 + kq), w[1], acc, 0, 0, 0);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-        if (rq + r < nvalid) y[(size_t)(row0 + rq + r) * MLP_OUT + col] = o[r];
+        if (row0 + rq + r < batch) y[(size_t)(row0 + rq + r) * MLP_OUT + col] = acc[r] + bias4;
 }
 
 // Loss mean((y - t_norm)^2) over batch x q_out and its gradient dy (zero on padded outputs);
@@ -183,143 +226,190 @@ __global__ __launch_bounds__(256) void k_mlp_loss(const float *y, const float *t
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void k_sum_partials(const double *part, int n, double scale, double *out)
+// *out = scale * sum of n <= 256 partial sums, added in order; the loads are spread over the
+// block first (one thread walking them in memory took 13 us).
+__global__ __launch_bounds__(256) void k_sum_partials(const double *part, int n, double scale, double *out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+    __shared__ double sh[256];
+    sh[threadIdx.x] = (int)threadIdx.x < n ? part[threadIdx.x] : 0.0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int i = 0; i < n; ++i) s += part[i];
+#pragma unroll 16
+        for (int i = 0; i < n; ++i) s += sh[i];
         *out = s * scale;
     }
 }
 
-// --------------------------------------------------------------------------------------
 // Backward pass, per row: dz4 = dy; da_l = bf16(dz_{l+1}) W_{l+1}; dz_l = da_l SiLU'(z_l).
-// dz [3][batch][64] (layers 1..3).  Transposed weights in LDS: W4^T [64][32] (outputs
-// 16..31 zero), W3^T, W2^T [64][64].
-// --------------------------------------------------------------------------------------
-struct alignas(16) BwdSmem {
-    unsigned short w4t[MLP_H * WS1];
-    unsigned short w3t[MLP_H * WSH];
-    unsigned short w2t[MLP_H * WSH];
-    unsigned short act[4][16 * AS];
-};
-
+// dz [3][batch][64] (layers 1..3, FP32, for the bias gradients), and transposed by chunk in
+// bf16 gt (64 columns, layers 1..3, gstride apart) and g4t (16 columns, dy).
 __global__ __launch_bounds__(256) void k_mlp_backward(const unsigned short *wb, const float *dy,
-                                                      const float *z, int batch, float *dz)
+                                                      const float *z, int batch, float *dz, unsigned short *gt,
+                                                      size_t gstride, unsigned short *g4t)
 {
-    __shared__ BwdSmem s;
-    for (int j = threadIdx.x; j < MLP_H * MLP_K1; j += blockDim.x) {
-        const int n = j / MLP_K1, k = j % MLP_K1;   // W4^T[n][k] = W4[k][n]
-        s.w4t[n * WS1 + k] = k < MLP_OUT ? wb[OFF_W4 + k * MLP_H + n] : (unsigned short)0;
-    }
-    for (int j = threadIdx.x; j < MLP_H * MLP_H; j += blockDim.x) {
-        const int n = j / MLP_H, k = j % MLP_H;
-        s.w3t[n * WSH + k] = wb[OFF_W3 + k * MLP_H + n];
-        s.w2t[n * WSH + k] = wb[OFF_W2 + k * MLP_H + n];
-    }
+    __shared__ __attribute__((aligned(16))) unsigned short act[2][TRAIN_ROWS * AS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int row0 = blockIdx.x * MLP_ROWS + wave * 16;
+    const int row0 = blockIdx.x * TRAIN_ROWS;
     const int nvalid = batch - row0;
-    unsigned short *A = s.act[wave];
-    {
-        const int r = lane & 15, c0 = 8 * (lane >> 4);
-        for (int c = c0; c < c0 + 8; ++c) {
-            float v = (c < MLP_OUT && r < nvalid) ? dy[(size_t)(row0 + r) * MLP_OUT + c] : 0.f;
-            A[r * AS + c] = f2bf(v);
+    const int col = lane & 15, rq = 4 * (lane >> 4), kq = 8 * (lane >> 4);
+    const int c = wave * 16 + col;  // this lane's column (an input of layer l + 1)
+    const size_t lstride = (size_t)batch * MLP_H;
+    // W_{l+1} as B operands (row k of W is output k): layer 4 has 16 outputs, so only the lanes
+    // of k < 16 hold any
+    ushort8 w4 = {0, 0, 0, 0, 0, 0, 0, 0}, w3[2], w2[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if (kq < MLP_OUT) w4[i] = wb[OFF_W4 + (kq + i) * MLP_H + c];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            w3[kk][i] = wb[OFF_W3 + (kk * 32 + kq + i) * MLP_H + c];
+            w2[kk][i] = wb[OFF_W2 + (kk * 32 + kq + i) * MLP_H + c];
         }
     }
+    float zv[3][4];
+#pragma unroll
+    for (int l = 0; l < 3; ++l)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            zv[l][r] = rq + r < nvalid ? z[l * lstride + (size_t)(row0 + rq + r) * MLP_H + c] : 0.f;
+    for (int j = threadIdx.x; j < TRAIN_ROWS * MLP_K1; j += 256) {
+        const int r = j / MLP_K1, k = j % MLP_K1;
+        const float v = (k < MLP_OUT && r < nvalid) ? dy[(size_t)(row0 + r) * MLP_OUT + k] : 0.f;
+        const unsigned short h = f2bf(v);
+        act[0][r * AS + k] = h;
+        if (k < MLP_OUT) g4t[chunk_at(row0 + r, k, MLP_OUT)] = h;
+    }
     __syncthreads();
-    const int col = lane & 15, rq = 4 * (lane >> 4);
-    floatx4 acc[4];
-    const size_t lstride = (size_t)batch * MLP_H;
 #pragma unroll
     for (int l = 2; l >= 0; --l) {  // hidden layer l + 1
-        if (l == 2) mma_rows16<MLP_K1, 4>(A, AS, s.w4t, WS1, acc, lane);
-        else mma_rows16<MLP_H, 4>(A, AS, l == 1 ? s.w3t : s.w2t, WSH, acc, lane);
-        __syncthreads();
+        const unsigned short *in = act[l & 1];  // l = 2 reads dy from act[0]
+        unsigned short *out = act[(l + 1) & 1];
+        floatx4 acc;
+        if (l == 2) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(in + col * AS + kq), __builtin_bit_cast(bf16x8, w4),
+                                                          floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        } else {
+            const ushort8 *w = l == 1 ? w3 : w2;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(in + col * AS + kq), __builtin_bit_cast(bf16x8, w[0]),
+                                                          floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(in + col * AS + 32 + kq), __builtin_bit_cast(bf16x8, w[1]), acc,
+                                                          0, 0, 0);
+        }
+        ushort4 h4;
+        unsigned short *h = reinterpret_cast<unsigned short *>(&h4);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = rq + r, c = t * 16 + col;
-                float d = 0.f;
-                if (row < nvalid) {
-                    const size_t o = l * lstride + (size_t)(row0 + row) * MLP_H + c;
-                    d = acc[t][r] * dsilu(z[o]);
-                    dz[o] = d;
-                }
-                A[row * AS + c] = f2bf(d);
+        for (int r = 0; r < 4; ++r) {
+            float d = 0.f;
+            if (rq + r < nvalid) {
+                d = acc[r] * dsilu(zv[l][r]);
+                dz[l * lstride + (size_t)(row0 + rq + r) * MLP_H + c] = d;
             }
+            h[r] = f2bf(d);
+            out[(rq + r) * AS + c] = h[r];
+        }
+        *reinterpret_cast<ushort4 *>(gt + l * gstride + chunk_at(row0 + rq, c, MLP_H)) = h4;
         __syncthreads();
     }
 }
 
-// Weight gradients over a chunk of WGRAD_ROWS batch rows: partial dW_l = bf16(dz_l)^T a_{l-1}
-// and db_l = sum dz_l, written to part[blockIdx.x][MLP_PARAMS].  a_0 is the stored bf16
-// input, a_l = bf16(SiLU(z_l)).
-struct alignas(16) WgradSmem {
-    unsigned short gt[MLP_H * GS_T];   // dz^T [out][rows]
-    unsigned short at[MLP_H * GS_T];   // a^T  [in][rows]
-    float gf[WGRAD_ROWS * MLP_H];      // dz in FP32 [rows][out] (bias gradients)
-};
+// Weight gradients over a chunk of WGRAD_ROWS batch rows (blockIdx.x) of one layer
+// (4 - blockIdx.y): partial dW_l = bf16(dz_l)^T a_{l-1} and db_l = sum dz_l, written to
+// part[chunk][MLP_PARAMS].  Waves 0..3 take 16 outputs each (layer 4: 16 inputs each), wave 4
+// the bias sums, in row order.  Rows past the batch: the operands of a 16-row block that was
+// written are zero (g) there; blocks that were not written are not read.
+constexpr int WGRAD_THREADS = 320;
 
-__global__ __launch_bounds__(256) void k_mlp_wgrad(const float *dy, const float *dz, const float *z,
-                                                   const unsigned short *a0, int batch, float *part)
+__global__ __launch_bounds__(WGRAD_THREADS) void k_mlp_wgrad(const float *dy, const float *dz, const unsigned short *gt,
+                                                             size_t gstride, const unsigned short *g4t,
+                                                             const unsigned short *a0t, const unsigned short *at,
+                                                             size_t astride, int batch, float *part)
 {
-    __shared__ WgradSmem s;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int b0 = blockIdx.x * WGRAD_ROWS;
+    const int chunk = blockIdx.x, b0 = chunk * WGRAD_ROWS, layer = 4 - blockIdx.y;
     const int nrow = min(WGRAD_ROWS, batch - b0);
-    float *P = part + (size_t)blockIdx.x * MLP_PARAMS;
-    const size_t lstride = (size_t)batch * MLP_H;
-    for (int layer = 4; layer >= 1; --layer) {
+    float *P = part + (size_t)chunk * MLP_PARAMS;
+    if (wave == 4) {
         const int nout = layer == 4 ? MLP_OUT : MLP_H;
-        const int kin = layer == 1 ? MLP_K1 : MLP_H;
-        const float *g = layer == 4 ? dy : dz + (size_t)(layer - 1) * lstride;
-        __syncthreads();
-        for (int j = threadIdx.x; j < WGRAD_ROWS * nout; j += blockDim.x) {
-            const int b = j / nout, n = j - b * nout;
-            float v = b < nrow ? g[(size_t)(b0 + b) * nout + n] : 0.f;
-            s.gt[n * GS_T + b] = f2bf(v);
-            s.gf[b * nout + n] = v;
-        }
-        for (int j = threadIdx.x; j < WGRAD_ROWS * kin; j += blockDim.x) {
-            const int b = j / kin, k = j - b * kin;
-            unsigned short v = 0;
-            if (b < nrow) {
-                if (layer == 1) v = a0[(size_t)(b0 + b) * MLP_K1 + k];
-                else v = f2bf(silu(z[(size_t)(layer - 2) * lstride + (size_t)(b0 + b) * MLP_H + k]));
-            }
-            s.at[k * GS_T + b] = v;
-        }
-        __syncthreads();
-        // bias gradient: plain FP32 sums in row order, from the staged copy
+        const float *g = (layer == 4 ? dy : dz + (size_t)(layer - 1) * batch * MLP_H) + (size_t)b0 * nout;
         const int boff = layer == 1 ? OFF_B1 : layer == 2 ? OFF_B2 : layer == 3 ? OFF_B3 : OFF_B4;
-        for (int n = threadIdx.x; n < nout; n += blockDim.x) {
+        if (lane < nout) {
             float acc = 0.f;
-            for (int b = 0; b < nrow; ++b) acc += s.gf[b * nout + n];
-            P[boff + n] = acc;
-        }
-        const int woff = layer == 1 ? OFF_W1 : layer == 2 ? OFF_W2 : layer == 3 ? OFF_W3 : OFF_W4;
-        const int tn = nout / 16, tk = kin / 16;
-        for (int t = wave; t < tn * tk; t += 4) {
-            const int tm = t / tk, tc = t - tm * tk;
-            floatx4 acc[1];
-            mma_rows16<WGRAD_ROWS, 1>(s.gt + tm * 16 * GS_T, GS_T, s.at + tc * 16 * GS_T, GS_T, acc, lane);
-            const int c = tc * 16 + (lane & 15), rq = 4 * (lane >> 4);
+            int b = 0;
+            for (; b + 32 <= nrow; b += 32) {  // 32 loads in flight, added in row order
+                float v[32];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) P[woff + (tm * 16 + rq + r) * kin + c] = acc[0][r];
+                for (int i = 0; i < 32; ++i) v[i] = g[(size_t)(b + i) * nout + lane];
+#pragma unroll
+                for (int i = 0; i < 32; ++i) acc += v[i];
+            }
+            for (; b < nrow; ++b) acc += g[(size_t)b * nout + lane];
+            P[boff + lane] = acc;
         }
+        return;
     }
+    const int r = lane & 15, kq = 8 * (lane >> 4), rq = 4 * (lane >> 4);
+    const ushort8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    // 8 rows of column c of a transposed operand, from row kk 32 + kq of the chunk
+    auto op = [&](const unsigned short *m, int c, int cols, int kk) {
+        const int row = kk * 32 + kq;
+        const ushort8 v = row < nrow ? *reinterpret_cast<const ushort8 *>(m + ((size_t)chunk * cols + c) * WGRAD_ROWS + row) : zero;
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    auto tile = [&](const bf16x8 *A, const bf16x8 *B) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < WGRAD_ROWS / 32; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[kk], B[kk], acc, 0, 0, 0);
+        return acc;
+    };
+    constexpr int KK = WGRAD_ROWS / 32;
+    bf16x8 A[KK], B[4][KK];
+    if (layer == 4) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            A[kk] = op(g4t, r, MLP_OUT, kk);
+            B[0][kk] = op(at + 2 * astride, wave * 16 + r, MLP_H, kk);
+        }
+        const floatx4 acc = tile(A, B[0]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) P[OFF_W4 + (rq + i) * MLP_H + wave * 16 + r] = acc[i];
+        return;
+    }
+    const int kin = layer == 1 ? MLP_K1 : MLP_H;
+    const int woff = layer == 1 ? OFF_W1 : layer == 2 ? OFF_W2 : OFF_W3;
+    const unsigned short *am = layer == 1 ? a0t : at + (size_t)(layer - 2) * astride;
+    const unsigned short *gm = gt + (size_t)(layer - 1) * gstride;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) A[kk] = op(gm, wave * 16 + r, MLP_H, kk);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t * 16 < kin)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) B[t][kk] = op(am, t * 16 + r, kin, kk);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t * 16 < kin) {
+            const floatx4 acc = tile(A, B[t]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) P[woff + (wave * 16 + rq + i) * kin + t * 16 + r] = acc[i];
+        }
 }
 
 // grad[j] = sum over blocks of part[blk][j], in block order (deterministic)
-__global__ void k_mlp_reduce(const float *part, int nblk, float *grad)
+__global__ __launch_bounds__(64) void k_mlp_reduce(const float *part, int nblk, float *grad)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.x * 64 + threadIdx.x;
     if (j >= MLP_PARAMS) return;
     float s = 0.f;
-    for (int b = 0; b < nblk; ++b) s += part[(size_t)b * MLP_PARAMS + j];
+    int b = 0;
+    for (; b + 16 <= nblk; b += 16) {  // 16 loads in flight, added in order
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = part[(size_t)(b + i) * MLP_PARAMS + j];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += v[i];
+    }
+    for (; b < nblk; ++b) s += part[(size_t)b * MLP_PARAMS + j];
     grad[j] = s;
 }
 

@@ -1695,7 +1695,8 @@ int elb_batch_destroy(elb_batch *b)
 namespace {
 
 struct MlpWs {
-    size_t a0, z, dz, part, lpart, total;
+    size_t a0t, at, g4t, gt, z, dz, part, lpart, total;
+    size_t lstride;  // elements from layer to layer of at and gt
     int nblk_w, nblk_l;
 };
 
@@ -1706,7 +1707,13 @@ MlpWs mlp_ws(int64_t batch)
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
     w.nblk_w = (int)((batch + WGRAD_ROWS - 1) / WGRAD_ROWS);
     w.nblk_l = (int)std::min<int64_t>(256, (batch * MLP_OUT + 255) / 256);
-    w.a0 = take(sizeof(unsigned short) * MLP_K1 * (size_t)batch);
+    // transposed bf16 operands of the weight gradients, in whole chunks
+    const size_t rows = (size_t)w.nblk_w * WGRAD_ROWS;
+    w.lstride = rows * MLP_H;
+    w.a0t = take(sizeof(unsigned short) * MLP_K1 * rows);
+    w.at = take(sizeof(unsigned short) * 3 * w.lstride);
+    w.g4t = take(sizeof(unsigned short) * MLP_OUT * rows);
+    w.gt = take(sizeof(unsigned short) * 3 * w.lstride);
     w.z = take(sizeof(float) * 3 * MLP_H * (size_t)batch);
     w.dz = take(sizeof(float) * 3 * MLP_H * (size_t)batch);
     w.part = take(sizeof(float) * MLP_PARAMS * (size_t)w.nblk_w);
@@ -1851,9 +1858,10 @@ int elb_mlp_forward(const float *params, const uint16_t *wb, const float *norm, 
     if (!params || !wb || !norm || !x || !y || !ws || batch < 1 || batch > kMaxBatch) return ELB_EINVAL;
     MlpWs w = mlp_ws(batch);
     char *base = (char *)ws;
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((batch + MLP_ROWS - 1) / MLP_ROWS)), dim3(256), 0,
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((batch + TRAIN_ROWS - 1) / TRAIN_ROWS)), dim3(256), 0,
                        (hipStream_t)stream, (const unsigned short *)wb, params, norm, x, (const int *)index,
-                       (int)batch, y, (unsigned short *)(base + w.a0), (float *)(base + w.z));
+                       (int)batch, y, (unsigned short *)(base + w.a0t), (unsigned short *)(base + w.at), w.lstride,
+                       (float *)(base + w.z));
     return hipGetLastError() == hipSuccess ? ELB_OK : ELB_EHIP;
 }
 
@@ -1867,7 +1875,7 @@ int elb_mlp_loss(const float *y, const float *t, const int32_t *index, const flo
     double *lp = (double *)((char *)ws + w.lpart);
     hipLaunchKernelGGL(k_mlp_loss, dim3(w.nblk_l), dim3(256), 0, (hipStream_t)stream, y, t, (const int *)index,
                        norm, (int)batch, q_out, dy, lp);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, (hipStream_t)stream, lp, w.nblk_l,
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, (hipStream_t)stream, lp, w.nblk_l,
                        1.0 / ((double)batch * q_out), loss);
     return hipGetLastError() == hipSuccess ? ELB_OK : ELB_EHIP;
 }
@@ -1893,7 +1901,7 @@ int elb_mlp_loss_noalloc(const float *y, const float *t, const int32_t *index, c
     }
     hipLaunchKernelGGL(k_mlp_loss, dim3(nblk), dim3(256), 0, (hipStream_t)stream, y, t, (const int *)index,
                        norm, (int)batch, q_out, dy, lp);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, (hipStream_t)stream, lp, nblk,
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, (hipStream_t)stream, lp, nblk,
                        1.0 / ((double)batch * q_out), loss);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -1911,11 +1919,14 @@ int elb_mlp_backward(const uint16_t *wb, const float *dy, int64_t batch, float *
     hipStream_t st = (hipStream_t)stream;
     const float *z = (const float *)(base + w.z);
     float *dz = (float *)(base + w.dz);
-    hipLaunchKernelGGL(k_mlp_backward, dim3((unsigned)((batch + MLP_ROWS - 1) / MLP_ROWS)), dim3(256), 0, st,
-                       (const unsigned short *)wb, dy, z, (int)batch, dz);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3(w.nblk_w), dim3(256), 0, st, dy, (const float *)dz, z,
-                       (const unsigned short *)(base + w.a0), (int)batch, (float *)(base + w.part));
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_PARAMS + 255) / 256), dim3(256), 0, st,
+    unsigned short *gt = (unsigned short *)(base + w.gt), *g4t = (unsigned short *)(base + w.g4t);
+    hipLaunchKernelGGL(k_mlp_backward, dim3((unsigned)((batch + TRAIN_ROWS - 1) / TRAIN_ROWS)), dim3(256), 0, st,
+                       (const unsigned short *)wb, dy, z, (int)batch, dz, gt, w.lstride, g4t);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(w.nblk_w, 4), dim3(WGRAD_THREADS), 0, st, dy, (const float *)dz,
+                       (const unsigned short *)gt, w.lstride, (const unsigned short *)g4t,
+                       (const unsigned short *)(base + w.a0t), (const unsigned short *)(base + w.at), w.lstride, (int)batch,
+                       (float *)(base + w.part));
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_PARAMS + 63) / 64), dim3(64), 0, st,
                        (const float *)(base + w.part), w.nblk_w, grad);
     return hipGetLastError() == hipSuccess ? ELB_OK : ELB_EHIP;
 }

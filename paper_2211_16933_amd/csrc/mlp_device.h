@@ -25,7 +25,6 @@ constexpr int AS = MLP_H + 8;      // LDS row stride (bf16) of an activation til
 constexpr int WS1 = MLP_K1 + 8;    // LDS row stride of W1
 constexpr int WSH = MLP_H + 8;     // LDS row stride of W2, W3, W4 and of transposed weights
 constexpr int WGRAD_ROWS = 128;    // batch rows per block of the weight-gradient kernel
-constexpr int GS_T = WGRAD_ROWS + 8;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short ushort8 __attribute__((ext_vector_type(8)));
