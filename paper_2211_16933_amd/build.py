@@ -10,8 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libelb.so")
 SOURCES = ["elb.hip", "host_math.cpp", "stage_kernels.hip"]
-HEADERS = ["closure_kernels.h", "elb_kernels.h", "host_math.h", "mlp_device.h", "readout_kernels.h",
-           "stage_table.h", "state_kernels.h"]
+HEADERS = ["closure_kernels.h", "elb_kernels.h", "host_math.h", "mlp_device.h", "node_tables.h",
+           "readout_kernels.h", "stage_table.h", "state_kernels.h"]
 # stage_kernels.hip is compiled once per mode of the stage kernel
 STAGE_MODES = {"f64": 0, "f32": 1, "mixed": 2, "fixup": 3}
 

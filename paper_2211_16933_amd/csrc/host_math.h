@@ -7,6 +7,7 @@ namespace elb {
 
 void hermite_orthonormal(int lmax, double x, double *h);
 int gauss_hermite(int Q, double *p, double *w);
+int gauss_hermite_nodes(int Q, double *p);  // the nodes alone
 double chi_set(double eta);
 double eta_of_denseness(double El);
 void map_units(double El, double kn, double kn_length, double n_ref, double *b, double *mu_ref,
