@@ -583,10 +583,10 @@ __global__ __launch_bounds__(256) void k_closure_apply(const unsigned short *wb,
 }
 
 // Training sample of every cell: x[i] = the 12 inputs, y[i][j] = (Lt[i][j] - Ls[i][j]) tau / n
-// for j < Q (Lt: the projected teacher right-hand side, Ls: the student's; both rows of
-// stride ls).
+// for j < Q; Lt: the projected teacher right-hand side, Ls = psi1 - psi0 the student's (all
+// rows of stride ls).
 __global__ void k_closure_sample(const double *rows5, ClosureConst cc, int nx, int Q,
-                                 const double *Lt, const double *Ls, int ls, float *x_out,
+                                 const double *Lt, const double *psi1, const double *psi0, int ls, float *x_out,
                                  float *y_out)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -594,27 +594,84 @@ __global__ void k_closure_sample(const double *rows5, ClosureConst cc, int nx, i
     double x[MLP_IN], sd;
     closure_features(rows5, i, cc, x, &sd);
     for (int c = 0; c < MLP_IN; ++c) x_out[(size_t)i * MLP_IN + c] = (float)x[c];
-    for (int j = 0; j < Q; ++j)
-        y_out[(size_t)i * Q + j] = (float)((Lt[(size_t)i * ls + j] - Ls[(size_t)i * ls + j]) / sd);
+    for (int j = 0; j < Q; ++j) {
+        const size_t o = (size_t)i * ls + j;
+        y_out[(size_t)i * Q + j] = (float)((Lt[o] - (psi1[o] - psi0[o])) / sd);
+    }
 }
 
-// out[r][j] = sum_k P[j][k] in[r][k] for rows r < nrows (FP64), j < qo, k < qi.
-__global__ void k_project_rows(const double *P, const double *in, int in_stride, int qi, double *out,
-                               int out_stride, int qo, int nrows)
+// Projection of a fine state onto QO <= 16 nodes: out[r][j] = sum_k P[k][j] in[r][k] for rows
+// r < nrows (FP64), P [qi][MLP_OUT].  blockIdx.y: 0 phi, 1 theta of psi0, 2 the right-hand
+// side of phi, psi1 - psi0 (rows of 2 qi values; out rows of 2 QO).  One thread per row, its QO
+// sums in registers and P in scalar registers, so that a value read serves QO sums: bound by
+// reading the rows.  65536 cells, 96 -> 12 nodes: the three fields 59 us; 3 x 198 us with a
+// thread per sum, and 49 us for the difference as a pass of its own.
+constexpr int PROJ_THREADS = 64;
+
+template <int QO>
+__global__ __launch_bounds__(PROJ_THREADS) void k_project_rows(const double *__restrict__ P, const double *__restrict__ psi0,
+                                                               const double *__restrict__ psi1, int qi,
+                                                               double *__restrict__ state, double *__restrict__ rhs, int nrows)
 {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)nrows * qo) return;
-    const int r = (int)(t / qo), j = (int)(t - (size_t)r * qo);
-    double s = 0.0;
-    for (int k = 0; k < qi; ++k) s += P[(size_t)j * qi + k] * in[(size_t)r * in_stride + k];
-    out[(size_t)r * out_stride + j] = s;
+    const int r = blockIdx.x * PROJ_THREADS + threadIdx.x;
+    if (r >= nrows) return;
+    const int field = blockIdx.y;
+    const double *in = psi0 + (size_t)r * 2 * qi + (field == 1 ? qi : 0);
+    const double *in1 = psi1 + (size_t)r * 2 * qi;
+    double acc[QO];
+#pragma unroll
+    for (int j = 0; j < QO; ++j) acc[j] = 0.0;
+    for (int k = 0; k < qi; k += 4) {  // every compiled node count is a multiple of 4
+        double v[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = in[k + d];
+        if (field == 2)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) v[d] = in1[k + d] - v[d];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int j = 0; j < QO; ++j) acc[j] = fma(P[(k + d) * MLP_OUT + j], v[d], acc[j]);
+    }
+    double *out = (field == 2 ? rhs : state) + (size_t)r * 2 * QO + (field == 1 ? QO : 0);
+#pragma unroll
+    for (int j = 0; j < QO; ++j) out[j] = acc[j];
 }
 
-// d[r][c] = a[r][c] - b[r][c] over rows r < nrows of width w (FP64).
-__global__ void k_diff_rows(const double *a, const double *b, double *d, int w, int nrows)
+// Lift of a state on QS <= 16 nodes onto qo: out[r][k] = sum_j Lam[k][j] in[r][j] for phi
+// (blockIdx.y = 0) and theta (1), rows of 2 QS and 2 qo values.  One thread per node, its row
+// of Lam in registers, over LIFT_ROWS rows whose inputs come in scalar registers: bound by
+// writing the rows.  65536 cells, 12 -> 96 nodes: 59 us, 2 x 198 with a thread per sum.
+constexpr int LIFT_ROWS = 32;
+
+template <int QS>
+__global__ __launch_bounds__(256) void k_lift_rows(const double *__restrict__ Lam, const double *__restrict__ in, int qo,
+                                                   double *__restrict__ out, int nrows)
+{
+    const int k = threadIdx.x;
+    const int r0 = blockIdx.x * LIFT_ROWS, r1 = min(r0 + LIFT_ROWS, nrows);
+    double lam[QS];
+#pragma unroll
+    for (int j = 0; j < QS; ++j) lam[j] = Lam[min(k, qo - 1) * QS + j];
+    const double *src = in + (blockIdx.y ? QS : 0);
+    double *dst = out + (blockIdx.y ? qo : 0);
+    for (int r = r0; r < r1; ++r) {
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < QS; ++j) s = fma(lam[j], src[(size_t)r * 2 * QS + j], s);
+        if (k < qo) dst[(size_t)r * 2 * qo + k] = s;
+    }
+}
+
+// The right-hand side psi1 - psi0 of the interior rows as two planes, phi [nx][Q] and theta
+// [nx][Q] (FP64).
+__global__ void k_rhs_planes(const double *psi1, const double *psi0, int nx, int Q, double *phi, double *theta)
 {
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < (size_t)nrows * w) d[t] = a[t] - b[t];
+    if (t >= (size_t)nx * Q) return;
+    const size_t i = t / Q, o = i * 2 * Q + (t - i * Q);
+    phi[t] = psi1[o] - psi0[o];
+    theta[t] = psi1[o + Q] - psi0[o + Q];
 }
 
 }  // namespace elb

@@ -13,6 +13,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/elb.h"
@@ -36,6 +37,7 @@ struct Layout {
     size_t corr, rows5, mparams, mwb, mnorm, pc, proj, outside, sx, sy;
     // chi_RET-FM (params.chi_mode = ELB_CHI_RETFM): ball-average weights
     size_t chiw;
+    size_t tables;
     size_t total;
 };
 
@@ -71,6 +73,8 @@ Layout make_layout(int nx, int Q, int N, int precision, int closure, int chi_rea
     L.sq = take(sizeof(double) * (QP + 2));
     L.rsq = take(sizeof(double) * (QP + 2));
     L.rec = take(sizeof(double) * 2 * QP);
+    L.chiw = chi_reach >= 0 ? take(sizeof(double) * (2 * (size_t)chi_reach + 1)) : o;
+    L.tables = o;  // up to here uploaded at creation
     // uploaded together when a state is set: reference tables, then the fields n, u, T
     L.cref = take(sizeof(double) * (QP + 3 * (size_t)Q + 3 * (size_t)nx));
     L.gref = L.cref + sizeof(double) * QP;
@@ -98,9 +102,6 @@ Layout make_layout(int nx, int Q, int N, int precision, int closure, int chi_rea
         L.outside = take(sizeof(unsigned long long));
         L.sx = take(sizeof(float) * MLP_IN * (size_t)nx);
         L.sy = take(sizeof(float) * MLP_OUT * (size_t)nx);
-    }
-    if (chi_reach >= 0) {
-        L.chiw = take(sizeof(double) * (2 * (size_t)chi_reach + 1));
     }
     L.total = o;
     return L;
@@ -268,8 +269,8 @@ int derive(const elb_params *p, int *N, double *dx, double *dt, double *b, doubl
                 return ELB_EINVAL;
             }
     }
-    std::vector<double> pk(p->q), wk(p->q);
-    if (gauss_hermite(p->q, pk.data(), wk.data()) != 0) { *msg = "quadrature failed"; return ELB_EINVAL; }
+    std::vector<double> pk(p->q);
+    if (gauss_hermite_nodes(p->q, pk.data()) != 0) { *msg = "quadrature failed"; return ELB_EINVAL; }
     double pmax = pk.back();
     *N = n;
     *dx = p->length / p->nx;
@@ -594,13 +595,8 @@ int flag_status(elb_ctx *c, int flag)
 int check_flag(elb_ctx *c)
 {
     int flag = 0;
-    int rc = hip_check(c, hipMemcpyAsync(&flag, c->dev<int>(c->L.flag), sizeof(int),
-                                         hipMemcpyDeviceToHost, c->stream), "flag copy");
-    if (rc) return rc;
-    rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
-    if (rc) return rc;
-    c->stage->used = 0;
-    return flag_status(c, flag);
+    int rc = download(c, &flag, c->L.flag, sizeof flag);
+    return rc ? rc : flag_status(c, flag);
 }
 
 }  // namespace
@@ -684,7 +680,12 @@ int create_ctx(const elb_params *p, void *dev_workspace, int64_t workspace_bytes
     //   KS = QP/4.  Both fill QP x QP values.
     const bool split = (Q / 2) % 16 == 0;
     const int KD = split ? Q / 2 : QP, KS = KD / 4, TN = KD / 16, NP = split ? 2 : 1;
-    std::vector<double> bpd((size_t)QP * QP, 0.0);
+    // every table in an image of its part of the workspace, uploaded at once
+    std::vector<double> image(c->L.tables / sizeof(double), 0.0);
+    auto table = [&](size_t off) { return image.data() + off / sizeof(double); };
+    std::copy(c->p.begin(), c->p.end(), table(c->L.p));
+    std::copy(c->Btd.begin(), c->Btd.end(), table(c->L.btd));
+    double *bpd = table(c->L.bpd);
     for (int par = 0; par < NP; ++par)
         for (int tn = 0; tn < TN; ++tn)
             for (int ln = 0; ln < 64; ++ln)
@@ -694,28 +695,21 @@ int create_ctx(const elb_params *p, void *dev_workspace, int64_t workspace_bytes
                     const int k = split ? Q / 2 + cl : cl;
                     bpd[(((size_t)par * TN + tn) * 64 + ln) * KS + ks] = c->Btd[(size_t)l * QP + k];
                 }
-    std::vector<float> bpf(bpd.begin(), bpd.end());
-    std::vector<double> sq(MAXQP + 2, 0.0), rsq(MAXQP + 2, 0.0);
-    for (int l = 0; l < MAXQP + 2; ++l) {
+    std::copy(bpd, bpd + (size_t)QP * QP, reinterpret_cast<float *>(table(c->L.bpf)));
+    double *sq = table(c->L.sq), *rsq = table(c->L.rsq), *rec = table(c->L.rec);
+    for (int l = 0; l < QP + 2; ++l) {
         sq[l] = std::sqrt((double)l);
         rsq[l] = l ? 1.0 / std::sqrt((double)l) : 0.0;
     }
-    hipError_t e = hipMemcpyAsync(c->dev<double>(c->L.p), c->p.data(), sizeof(double) * Q, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.btd), c->Btd.data(), sizeof(double) * c->Btd.size(), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.bpd), bpd.data(), sizeof(double) * bpd.size(), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<float>(c->L.bpf), bpf.data(), sizeof(float) * bpf.size(), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.sq), sq.data(), sizeof(double) * (QP + 2), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.rsq), rsq.data(), sizeof(double) * (QP + 2), hipMemcpyHostToDevice, c->stream);
-    std::vector<double> rec(2 * QP, 0.0);
     for (int l = 0; l < QP; ++l) {
         rec[l] = l ? 1.0 / std::sqrt((double)l) : 0.0;
         rec[QP + l] = std::sqrt((double)l / (double)(l + 1));
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.rec), rec.data(), sizeof(double) * rec.size(), hipMemcpyHostToDevice, c->stream);
     if (p->chi_mode == ELB_CHI_RETFM) {
         c->fm_J = fm_weights(fm_ratio(p), c->fm_w);
-        if (e == hipSuccess) e = hipMemcpyAsync(c->dev<double>(c->L.chiw), c->fm_w.data(), sizeof(double) * c->fm_w.size(), hipMemcpyHostToDevice, c->stream);
+        std::copy(c->fm_w.begin(), c->fm_w.end(), table(c->L.chiw));
     }
+    hipError_t e = hipMemcpyAsync(c->ws, image.data(), c->L.tables, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->dev<int>(c->L.flag), 0, sizeof(int) * 4, c->stream);
     if (e == hipSuccess && p->closure)
         e = hipMemsetAsync(c->dev<unsigned long long>(c->L.outside), 0, sizeof(unsigned long long), c->stream);
@@ -1779,9 +1773,9 @@ int lift_host(int q_from, int q_to, double *Lam)
     return ELB_OK;
 }
 
-// Right-hand side L[psi] of level 0 into level 2 (interior rows, same row layout) of an FP64
-// context: one stage with a_n = 0, a_s = 1, a_L = 1 and dt = 1 writes psi + L to level 1.
-int rhs_into_level2(elb_ctx *c)
+// psi + L[psi] of level 0, without the learned correction, into level 1 (interior rows) of an
+// FP64 context: one stage with a_n = 0, a_s = 1, a_L = 1 and dt = 1.
+int rhs_stage(elb_ctx *c)
 {
     const double dt = c->dt;
     const bool on = c->closure_on;
@@ -1792,12 +1786,18 @@ int rhs_into_level2(elb_ctx *c)
     c->dt = dt;
     c->closure_on = on;
     c->launches = launches;
-    const size_t n = (size_t)c->P.nx * 2 * c->Q;
-    size_t off = (size_t)NG * 2 * c->Q;
-    hipLaunchKernelGGL(k_diff_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
-                       c->dev<double>(c->L.psi[1]) + off, c->dev<double>(c->L.psi[0]) + off,
-                       c->dev<double>(c->L.psi[2]) + off, 2 * c->Q, c->P.nx);
     return hip_check(c, hipGetLastError(), "rhs launch");
+}
+
+// f(std::integral_constant<int, q>) for the student node counts
+template <typename F>
+void with_student_q(int q, F f)
+{
+    switch (q) {
+        case 8: f(std::integral_constant<int, 8>{}); break;
+        case 12: f(std::integral_constant<int, 12>{}); break;
+        default: f(std::integral_constant<int, 16>{}); break;  // closure contexts have q <= 16
+    }
 }
 
 // Allocation-free loss: the per-block partial sums of k_mlp_loss live in a file-scope device
@@ -2007,16 +2007,15 @@ int elb_closure_lift(elb_ctx *student, elb_ctx *teacher)
     if (rc) return fail(t, rc, "lift");
     hipStream_t st = s->stream;
     double *dL = s->dev<double>(s->L.proj);  // QT x QS <= 208 x 16 fits the projection buffer
-    rc = hip_check(t, hipMemcpyAsync(dL, Lam.data(), sizeof(double) * Lam.size(), hipMemcpyHostToDevice, st), "lift upload");
-    if (rc) return rc;
+    rc = upload(s, s->L.proj, Lam.data(), sizeof(double) * Lam.size());
+    if (rc) return fail(t, rc, "lift: %s", s->err.c_str());
     drop_ctx_graph(t);
-    const size_t offT = (size_t)NG * 2 * QT, offS = (size_t)NG * 2 * QS;
-    const unsigned grid = (unsigned)(((size_t)nx * QT + 255) / 256);
-    const double *sp = s->dev<double>(s->L.psi[0]) + offS;
-    double *tp = t->dev<double>(t->L.psi[0]) + offT;
-    hipLaunchKernelGGL(k_project_rows, dim3(grid), dim3(256), 0, st, (const double *)dL, sp, 2 * QS, QS, tp, 2 * QT, QT, nx);
-    hipLaunchKernelGGL(k_project_rows, dim3(grid), dim3(256), 0, st, (const double *)dL, sp + QS, 2 * QS, QS, tp + QT, 2 * QT,
-                       QT, nx);
+    const double *sp = s->dev<double>(s->L.psi[0]) + (size_t)NG * 2 * QS;
+    double *tp = t->dev<double>(t->L.psi[0]) + (size_t)NG * 2 * QT;
+    with_student_q(QS, [&](auto q) {
+        hipLaunchKernelGGL(k_lift_rows<decltype(q)::value>, dim3((nx + LIFT_ROWS - 1) / LIFT_ROWS, 2), dim3((QT + 63) / 64 * 64), 0,
+                           st, (const double *)dL, sp, QT, tp, nx);
+    });
     rc = hip_check(t, hipGetLastError(), "lift launch");
     if (rc) return rc;
     rc = hip_check(t, hipStreamSynchronize(st), "lift");
@@ -2031,21 +2030,20 @@ int elb_rhs(elb_ctx *c, double *phi_rhs, double *theta_rhs)
     if (!c) return ELB_EINVAL;
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
     if (c->P.precision != ELB_FP64) return fail(c, ELB_EINVAL, "elb_rhs needs an FP64 context");
-    int rc = rhs_into_level2(c);
+    int rc = rhs_stage(c);
     if (rc) return rc;
-    int nx = c->P.nx, Q = c->Q;
-    std::vector<double> host((size_t)nx * 2 * Q);
-    rc = hip_check(c, hipMemcpyAsync(host.data(), c->dev<double>(c->L.psi[2]) + (size_t)NG * 2 * Q,
-                                     sizeof(double) * host.size(), hipMemcpyDeviceToHost, c->stream), "rhs copy");
-    if (rc) return rc;
-    rc = check_flag(c);
-    if (rc) return rc;
-    for (int i = 0; i < nx; ++i)
-        for (int k = 0; k < Q; ++k) {
-            if (phi_rhs) phi_rhs[(size_t)i * Q + k] = host[(size_t)i * 2 * Q + k];
-            if (theta_rhs) theta_rhs[(size_t)i * Q + k] = host[(size_t)i * 2 * Q + Q + k];
-        }
-    return ELB_OK;
+    const int nx = c->P.nx, Q = c->Q;
+    const size_t n = (size_t)nx * Q, in = sizeof(double) * (size_t)NG * 2 * Q;
+    // the two planes fill the interior of level 2
+    double *planes = c->dev<double>(c->L.psi[2] + in);
+    hipLaunchKernelGGL(k_rhs_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
+                       (const double *)c->dev<double>(c->L.psi[1] + in), (const double *)c->dev<double>(c->L.psi[0] + in), nx, Q,
+                       planes, planes + n);
+    rc = hip_check(c, hipGetLastError(), "rhs launch");
+    if (!rc) rc = check_flag(c);
+    if (!rc && phi_rhs) rc = download(c, phi_rhs, c->L.psi[2] + in, sizeof(double) * n);
+    if (!rc && theta_rhs) rc = download(c, theta_rhs, c->L.psi[2] + in + sizeof(double) * n, sizeof(double) * n);
+    return rc;
 }
 
 int elb_closure_sample(elb_ctx *teacher, elb_ctx *student, float *x, float *y)
@@ -2059,47 +2057,34 @@ int elb_closure_sample(elb_ctx *teacher, elb_ctx *student, float *x, float *y)
         return fail(s, ELB_EINVAL, "teacher and student differ in grid or boundaries, or q_student > q_teacher");
     if (t->stream != s->stream) return fail(s, ELB_EINVAL, "teacher and student must share a stream");
     const int nx = s->P.nx, QT = t->Q, QS = s->Q;
-    std::vector<double> P((size_t)QS * QT);
+    std::vector<double> P((size_t)QS * QT), Pt((size_t)QT * MLP_OUT, 0.0);
     int rc = projection_host(QT, QS, P.data());
     if (rc) return fail(s, rc, "projection");
+    for (int j = 0; j < QS; ++j)
+        for (int k = 0; k < QT; ++k) Pt[(size_t)k * MLP_OUT + j] = P[(size_t)j * QT + k];
     hipStream_t st = s->stream;
     double *dP = s->dev<double>(s->L.proj);
-    rc = hip_check(s, hipMemcpyAsync(dP, P.data(), sizeof(double) * P.size(), hipMemcpyHostToDevice, st), "projection upload");
+    rc = upload(s, s->L.proj, Pt.data(), sizeof(double) * Pt.size());
     if (rc) return rc;
-    rc = rhs_into_level2(t);                                   // L_T into teacher level 2
+    rc = rhs_stage(t);                                         // psi_T + L_T into teacher level 1
     if (rc) return fail(s, rc, "teacher rhs: %s", t->err.c_str());
     const size_t offT = (size_t)NG * 2 * QT, offS = (size_t)NG * 2 * QS;
-    const unsigned grid = (unsigned)(((size_t)nx * QS + 255) / 256);
-    const double *tp = t->dev<double>(t->L.psi[0]) + offT;
-    double *sp = s->dev<double>(s->L.psi[0]) + offS;
-    hipLaunchKernelGGL(k_project_rows, dim3(grid), dim3(256), 0, st, dP, tp, 2 * QT, QT, sp, 2 * QS, QS, nx);
-    hipLaunchKernelGGL(k_project_rows, dim3(grid), dim3(256), 0, st, dP, tp + QT, 2 * QT, QT, sp + QS, 2 * QS, QS, nx);
-    hipLaunchKernelGGL(k_project_rows, dim3(grid), dim3(256), 0, st, dP, t->dev<double>(t->L.psi[2]) + offT, 2 * QT,
-                       QT, s->dev<double>(s->L.psi[2]) + offS, 2 * QS, QS, nx);
+    const double *tp0 = t->dev<double>(t->L.psi[0]) + offT, *tp1 = t->dev<double>(t->L.psi[1]) + offT;
+    double *sp = s->dev<double>(s->L.psi[0]) + offS, *Lt = s->dev<double>(s->L.psi[2]) + offS;
+    with_student_q(QS, [&](auto q) {
+        hipLaunchKernelGGL(k_project_rows<decltype(q)::value>, dim3((nx + PROJ_THREADS - 1) / PROJ_THREADS, 3),
+                           dim3(PROJ_THREADS), 0, st, (const double *)dP, tp0, tp1, QT, sp, Lt, nx);
+    });
     rc = hip_check(s, hipGetLastError(), "projection launch");
+    if (!rc) rc = rhs_stage(s);                                // and of the projected state
     if (rc) return rc;
-    // student right-hand side of the projected state: level 1 = psi + L, then L in place
-    const double dt = s->dt;
-    const bool on = s->closure_on;
-    s->dt = 1.0;
-    s->closure_on = false;
-    launch_stage(s, 0, 1, 0.0, 1.0);
-    s->dt = dt;
-    s->closure_on = on;
-    const size_t n = (size_t)nx * 2 * QS;
-    hipLaunchKernelGGL(k_diff_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, s->dev<double>(s->L.psi[1]) + offS,
-                       (const double *)sp, s->dev<double>(s->L.psi[1]) + offS, 2 * QS, nx);
     launch_closure_rows(s, 0);
     hipLaunchKernelGGL(k_closure_sample, dim3((nx + 255) / 256), dim3(256), 0, st, s->dev<double>(s->L.rows5),
-                       closure_const(s), nx, QS, (const double *)(s->dev<double>(s->L.psi[2]) + offS),
-                       (const double *)(s->dev<double>(s->L.psi[1]) + offS), 2 * QS, s->dev<float>(s->L.sx),
-                       s->dev<float>(s->L.sy));
+                       closure_const(s), nx, QS, (const double *)Lt, (const double *)(s->dev<double>(s->L.psi[1]) + offS),
+                       (const double *)sp, 2 * QS, s->dev<float>(s->L.sx), s->dev<float>(s->L.sy));
     rc = hip_check(s, hipGetLastError(), "sample launch");
-    if (rc) return rc;
-    rc = hip_check(s, hipMemcpyAsync(x, s->dev<float>(s->L.sx), sizeof(float) * MLP_IN * (size_t)nx,
-                                     hipMemcpyDeviceToHost, st), "sample copy");
-    if (!rc) rc = hip_check(s, hipMemcpyAsync(y, s->dev<float>(s->L.sy), sizeof(float) * QS * (size_t)nx,
-                                              hipMemcpyDeviceToHost, st), "sample copy");
+    if (!rc) rc = download(s, x, s->L.sx, sizeof(float) * MLP_IN * (size_t)nx);
+    if (!rc) rc = download(s, y, s->L.sy, sizeof(float) * QS * (size_t)nx);
     if (rc) return rc;
     rc = check_flag(t);
     if (rc) return fail(s, rc, "teacher: %s", t->err.c_str());
