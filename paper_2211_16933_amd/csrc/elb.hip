@@ -32,7 +32,7 @@ const int kSupportedQ[] = {8, 12, 16, 20, 24, 32, 40, 48, 64, 96, 200};
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t p, btd, bpd, bpf, sq, rsq, rec, cref, gref, ref, rows, check, flag, seedb, psi[3], U[3], out, cons, amp;
+    size_t p, btd, bpd, bpf, sq, rsq, rec, cref, gref, ref, rows, check, oldref, flag, seedb, psi[3], U[3], out, cons, amp;
     // learned closure (params.closure = 1)
     size_t corr, rows5, mparams, mwb, mnorm, pc, proj, outside, sx, sy;
     // chi_RET-FM (params.chi_mode = ELB_CHI_RETFM): ball-average weights
@@ -81,6 +81,7 @@ Layout make_layout(int nx, int Q, int N, int precision, int closure, int chi_rea
     L.ref = L.gref + sizeof(double) * Q;
     L.rows = L.ref + sizeof(double) * 2 * Q;
     L.check = take(sizeof(StateCheck) * CHECK_BLOCKS);
+    L.oldref = take(sizeof(double) * 2 * Q);
     L.seedb = take(sizeof(unsigned));
     size_t lvl = (size_t)(nx + 2 * NG) * 2 * Q * elem_size(precision);
     for (int s = 0; s < 3; ++s) L.psi[s] = take(lvl);
@@ -586,6 +587,15 @@ int download(elb_ctx *c, void *dst, size_t off, size_t bytes)
     return ELB_OK;
 }
 
+// Offsets of the FP64 planes phi, theta [nx][Q] in the interiors of levels 1 and 2 (FP64 storage:
+// both in level 1's), which the next stage writes before anything reads them.
+void dist_planes(const elb_ctx *c, size_t at[2])
+{
+    const size_t skip = (size_t)NG * 2 * c->Q * elem_size(c->P.precision);
+    at[0] = c->L.psi[1] + skip;
+    at[1] = c->P.precision == ELB_FP64 ? at[0] + sizeof(double) * (size_t)c->P.nx * c->Q : c->L.psi[2] + skip;
+}
+
 int flag_status(elb_ctx *c, int flag)
 {
     if (flag) return fail(c, ELB_ENONFINITE, "a cell reached n <= 0, T <= 0 or non-finite moments");
@@ -827,70 +837,64 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
         int rc = elb_set_state_moments(c, n.data(), u.data(), T.data());
         if (rc) return rc;
     }
-    int nx = c->P.nx, Q = c->Q, R = nx + 2 * NG;
-    for (size_t j = 0; j < (size_t)nx * Q; ++j)
-        if (!std::isfinite(phi[j]) || !std::isfinite(theta[j])) return fail(c, ELB_EINVAL, "non-finite distribution value");
-    std::vector<double> old_ref = c->ref;
-    if (c->P.precision != ELB_FP64) {
-        // reference of the deviation storage: mean primitive state of the given cells
+    const int nx = c->P.nx, Q = c->Q, R = nx + 2 * NG;
+    const bool f64 = c->P.precision == ELB_FP64;
+    const size_t n = (size_t)nx * Q;
+    // the planes into the interiors of levels 1 and 2; nothing else changes before they pass
+    size_t at[2];
+    dist_planes(c, at);
+    int rc = upload(c, at[0], phi, sizeof(double) * n);
+    if (!rc) rc = upload(c, at[1], theta, sizeof(double) * n);
+    if (rc) return rc;
+    double *dphi = c->dev<double>(at[0]), *dtheta = c->dev<double>(at[1]);
+    int *bad = c->dev<int>(c->L.check), nonfinite = 0;
+    rc = hip_check(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream), "check reset");
+    if (rc) return rc;
+    std::vector<double> old_ref;
+    if (f64) {
+        // theta follows phi
+        hipLaunchKernelGGL(k_all_finite, dim3((unsigned)std::min<size_t>(2048, (2 * n + 255) / 256)), dim3(256), 0, c->stream,
+                           (const double *)dphi, 2 * n, bad);
+        rc = hip_check(c, hipGetLastError(), "check kernel launch");
+        if (!rc) rc = download(c, &nonfinite, c->L.check, sizeof(int));
+        if (rc) return rc;
+        if (nonfinite) return fail(c, ELB_EINVAL, "non-finite distribution value");
+    } else {
+        // reference of the deviation storage: mean primitive state of the given cells, whose sum
+        // runs over the cells in order
+        hipLaunchKernelGGL(k_dist_sums, dim3((nx + SUM_CELLS - 1) / SUM_CELLS), dim3(SUM_CELLS), 0, c->stream,
+                           (const double *)dphi, (const double *)dtheta, c->dev<double>(c->L.p), nx, Q, c->dev<double>(c->L.rows), bad);
+        rc = hip_check(c, hipGetLastError(), "sum kernel launch");
+        std::vector<double> f(3 * (size_t)nx);
+        if (!rc) rc = download(c, f.data(), c->L.rows, sizeof(double) * f.size());
+        if (!rc) rc = download(c, &nonfinite, c->L.check, sizeof(int));
+        if (rc) return rc;
+        if (nonfinite) return fail(c, ELB_EINVAL, "non-finite distribution value");
         double sn = 0, su = 0, sT = 0;
-        for (int i = 0; i < nx; ++i) {
-            double n = 0, j = 0, e = 0;
-            for (int k = 0; k < Q; ++k) {
-                double v = phi[(size_t)i * Q + k];
-                n += v;
-                j += c->p[k] * v;
-                e += 0.5 * (c->p[k] * c->p[k] * v + theta[(size_t)i * Q + k]);
-            }
-            double u = j / n;
-            sn += n; su += u; sT += (2.0 * e / n - u * u) / 3.0;
-        }
+        for (int i = 0; i < nx; ++i) { sn += f[i]; su += f[(size_t)nx + i]; sT += f[2 * (size_t)nx + i]; }
         if (!(sn > 0) || !(sT > 0) || !std::isfinite(su)) return fail(c, ELB_EINVAL, "distributions with non-positive mean density or temperature");
-        int rr = set_reference(c, sn / nx, su / nx, sT / nx);
-        if (rr) return rr;
-    }
-    int es = elem_size(c->P.precision);
-    std::vector<char> host((size_t)R * 2 * Q * es);
-    // start from the current level 0 so ghost rows are preserved
-    if (c->has_state) {
-        int rc = hip_check(c, hipMemcpyAsync(host.data(), c->dev<char>(c->L.psi[0]), host.size(), hipMemcpyDeviceToHost, c->stream), "dist copy");
-        if (!rc) rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
+        old_ref = c->ref;
+        rc = set_reference(c, sn / nx, su / nx, sT / nx);
+        if (!rc) rc = upload(c, c->L.oldref, old_ref.data(), sizeof(double) * old_ref.size());
         if (rc) return rc;
     }
     // ghost rows (kept from the current state) move to the new reference
-    if (es == 4 && c->has_state && old_ref.size() == (size_t)2 * Q) {
-        for (int r = 0; r < R; ++r) {
-            if (r >= NG && r < nx + NG) continue;
-            for (int m = 0; m < 2 * Q; ++m) {
-                float *v = (float *)host.data() + (size_t)r * 2 * Q + m;
-                *v = (float)((double)*v + old_ref[m] - c->ref[m]);
-            }
-        }
+    const unsigned blocks = (unsigned)(((size_t)R * Q + 255) / 256);
+    if (f64)
+        hipLaunchKernelGGL(k_dist_pack<double>, dim3(blocks), dim3(256), 0, c->stream, (const double *)dphi, (const double *)dtheta,
+                           c->dev<double>(c->L.ref), (const double *)nullptr, nx, Q, c->dev<double>(c->L.psi[0]),
+                           c->dev<double>(c->L.psi[1]), c->dev<double>(c->L.psi[2]));
+    else
+        hipLaunchKernelGGL(k_dist_pack<float>, dim3(blocks), dim3(256), 0, c->stream, (const double *)dphi, (const double *)dtheta,
+                           c->dev<double>(c->L.ref), c->has_state ? c->dev<double>(c->L.oldref) : (const double *)nullptr, nx, Q,
+                           c->dev<float>(c->L.psi[0]), c->dev<float>(c->L.psi[1]), c->dev<float>(c->L.psi[2]));
+    if (c->P.precision == ELB_FP32_MIXED) {
+        // conserved densities of the stored (FP32) distributions, summed in FP64
+        const LevelU lu = {{c->dev<double>(c->L.U[0]), c->dev<double>(c->L.U[1]), c->dev<double>(c->L.U[2])}};
+        hipLaunchKernelGGL(k_conserved_from_psi<float>, dim3((R + 63) / 64), dim3(64), 0, c->stream,
+                           c->dev<float>(c->L.psi[0]), c->dev<double>(c->L.ref), lu, c->dev<double>(c->L.p), R, Q);
     }
-    for (int i = 0; i < nx; ++i)
-        for (int k = 0; k < Q; ++k) {
-            size_t o = (size_t)(i + NG) * 2 * Q + k;
-            if (es == 8) {
-                ((double *)host.data())[o] = phi[(size_t)i * Q + k];
-                ((double *)host.data())[o + Q] = theta[(size_t)i * Q + k];
-            } else {
-                ((float *)host.data())[o] = (float)(phi[(size_t)i * Q + k] - c->ref[k]);
-                ((float *)host.data())[o + Q] = (float)(theta[(size_t)i * Q + k] - c->ref[Q + k]);
-            }
-        }
-    for (int s = 0; s < 3; ++s) {
-        int rc = hip_check(c, hipMemcpyAsync(c->dev<char>(c->L.psi[s]), host.data(), host.size(), hipMemcpyHostToDevice, c->stream), "dist upload");
-        if (rc) return rc;
-        if (c->P.precision == ELB_FP32_MIXED) {
-            // conserved densities of the stored (FP32) distributions, summed in FP64
-            hipLaunchKernelGGL(k_conserved_from_psi<float>, dim3((R + 255) / 256), dim3(256), 0, c->stream,
-                               c->dev<float>(c->L.psi[s]), c->dev<double>(c->L.ref),
-                               c->dev<double>(c->L.U[s]), c->dev<double>(c->L.p), R, Q);
-            rc = hip_check(c, hipGetLastError(), "conserved kernel launch");
-            if (rc) return rc;
-        }
-    }
-    int rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
+    rc = hip_check(c, hipGetLastError(), "distribution launch");
     if (rc) return rc;
     c->has_state = true;
     c->steps = 0;
@@ -1044,20 +1048,21 @@ int elb_get_dist(elb_ctx *c, double *phi, double *theta)
 {
     if (!c) return ELB_EINVAL;
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
-    int nx = c->P.nx, Q = c->Q, R = nx + 2 * NG, es = elem_size(c->P.precision);
-    std::vector<char> host((size_t)R * 2 * Q * es);
-    int rc = hip_check(c, hipMemcpyAsync(host.data(), c->dev<char>(c->L.psi[0]), host.size(), hipMemcpyDeviceToHost, c->stream), "dist copy");
-    if (!rc) rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
-    if (rc) return rc;
-    for (int i = 0; i < nx; ++i)
-        for (int k = 0; k < Q; ++k) {
-            size_t o = (size_t)(i + NG) * 2 * Q + k;
-            double vp = es == 8 ? ((double *)host.data())[o] : (double)((float *)host.data())[o] + c->ref[k];
-            double vt = es == 8 ? ((double *)host.data())[o + Q] : (double)((float *)host.data())[o + Q] + c->ref[Q + k];
-            if (phi) phi[(size_t)i * Q + k] = vp;
-            if (theta) theta[(size_t)i * Q + k] = vt;
-        }
-    return check_flag(c);
+    const int nx = c->P.nx, Q = c->Q;
+    const size_t n = (size_t)nx * Q;
+    size_t at[2];
+    dist_planes(c, at);
+    const dim3 grid((unsigned)((n + 255) / 256));
+    if (c->P.precision == ELB_FP64)
+        hipLaunchKernelGGL(k_dist_planes<double>, grid, dim3(256), 0, c->stream, c->dev<double>(c->L.psi[0]),
+                           c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]));
+    else
+        hipLaunchKernelGGL(k_dist_planes<float>, grid, dim3(256), 0, c->stream, c->dev<float>(c->L.psi[0]),
+                           c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]));
+    int rc = hip_check(c, hipGetLastError(), "dist kernel launch");
+    if (!rc && phi) rc = download(c, phi, at[0], sizeof(double) * n);
+    if (!rc && theta) rc = download(c, theta, at[1], sizeof(double) * n);
+    return rc ? rc : check_flag(c);
 }
 
 int elb_get_conserved(elb_ctx *c, double out[3])

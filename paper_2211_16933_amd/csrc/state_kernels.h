@@ -239,9 +239,14 @@ __global__ __launch_bounds__(INIT_THREADS) void k_init_tiles(InitArgs a, int row
     }
 }
 
-// Conserved densities of every row from the stored distributions plus reference (FP64 sums).
+// Conserved densities of every row of level 0 from the stored distributions plus reference
+// (FP64 sums); those of the ghost rows, which all levels share, go to every level.
+struct LevelU {
+    double *U[3];
+};
+
 template <typename R>
-__global__ void k_conserved_from_psi(const R *psi, const double *ref, double *U, const double *p,
+__global__ void k_conserved_from_psi(const R *psi, const double *ref, LevelU lu, const double *p,
                                      int rows, int Q)
 {
     int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -254,9 +259,112 @@ __global__ void k_conserved_from_psi(const R *psi, const double *ref, double *U,
         j += p[k] * v;
         e += 0.5 * (p[k] * p[k] * v + (double)ph[Q + k] + ref[Q + k]);
     }
-    U[3 * (size_t)r] = n;
-    U[3 * (size_t)r + 1] = j;
-    U[3 * (size_t)r + 2] = e;
+    auto put = [&](double *U) {
+        U[3 * (size_t)r] = n;
+        U[3 * (size_t)r + 1] = j;
+        U[3 * (size_t)r + 2] = e;
+    };
+    put(lu.U[0]);
+    if (r < NG || r >= rows - NG) {
+        put(lu.U[1]);
+        put(lu.U[2]);
+    }
+}
+
+// --------------------------------------------------------------------------------------
+// Whole distributions between the caller's planes phi, theta [nx][Q] (FP64) and level 0.  The
+// planes lie in the interiors of levels 1 and 2, which hold nothing between steps.  Bound by
+// the copies to and from the host; 10007 cells, Q = 40, FP32: storing 3.2 + 3.2 MB back took
+// 470 to 1370 us with the conversion on the host (page faults of its buffer), restoring 1045.
+// --------------------------------------------------------------------------------------
+template <typename R>
+__global__ void k_dist_planes(const R *psi, const double *ref, int nx, int Q, double *phi, double *theta)
+{
+    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (size_t)nx * Q) return;
+    const size_t i = t / Q, o = (i + NG) * 2 * Q + (t - i * Q);
+    const int k = (int)(t - i * Q);
+    phi[t] = sizeof(R) == 8 ? (double)psi[o] : (double)psi[o] + ref[k];
+    theta[t] = sizeof(R) == 8 ? (double)psi[o + Q] : (double)psi[o + Q] + ref[Q + k];
+}
+
+// *bad = 1 when one of n values is not finite.
+__global__ void k_all_finite(const double *v, size_t n, int *bad)
+{
+    bool b = false;
+    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x)
+        b |= !(fabs(v[t]) < HUGE_VAL);
+    if (b) atomicOr(bad, 1);
+}
+
+// Density, velocity and temperature of every cell of the planes, one thread per cell, and the
+// check for finite values.  The sums run over the nodes in order with every operation rounded
+// (no fused multiply-add): the mean state they give is the reference of the FP32 storage, whose
+// bits every later step follows.  Tiles of SUM_K nodes pass through LDS for coalesced reads.
+constexpr int SUM_CELLS = 64, SUM_K = 8;
+
+__global__ __launch_bounds__(SUM_CELLS) void k_dist_sums(const double *phi, const double *theta, const double *p, int nx,
+                                                         int Q, double *fields, int *bad)
+{
+#pragma clang fp contract(off)
+    __shared__ double f[2][SUM_CELLS][SUM_K + 1];
+    const int i0 = blockIdx.x * SUM_CELLS, t = threadIdx.x, cells = min(SUM_CELLS, nx - i0);
+    double n = 0, j = 0, e = 0;
+    bool b = false;
+    for (int k0 = 0; k0 < Q; k0 += SUM_K) {  // Q is a multiple of 4: the last tile may be half
+        const int kn = min(SUM_K, Q - k0);
+        for (int m = t; m < SUM_CELLS * SUM_K; m += SUM_CELLS) {
+            const int c = m / SUM_K, k = m % SUM_K;
+            if (c < cells && k < kn) {
+                const size_t o = (size_t)(i0 + c) * Q + k0 + k;
+                f[0][c][k] = phi[o];
+                f[1][c][k] = theta[o];
+            }
+        }
+        __syncthreads();
+        if (t < cells)
+            for (int k = 0; k < kn; ++k) {
+                const double v = f[0][t][k], w = f[1][t][k], pk = p[k0 + k];
+                b |= !(fabs(v) < HUGE_VAL) || !(fabs(w) < HUGE_VAL);
+                n += v;
+                j += pk * v;
+                e += 0.5 * (pk * pk * v + w);
+            }
+        __syncthreads();
+    }
+    if (b) atomicOr(bad, 1);
+    if (t < cells) {
+        const double u = j / n;
+        fields[i0 + t] = n;
+        fields[(size_t)nx + i0 + t] = u;
+        fields[2 * (size_t)nx + i0 + t] = (2.0 * e / n - u * u) / 3.0;
+    }
+}
+
+// Level 0 from the planes; with old_ref != NULL (FP32) also the ghost rows of every level, moved
+// from the old reference to the new one.
+template <typename R>
+__global__ void k_dist_pack(const double *phi, const double *theta, const double *ref, const double *old_ref, int nx, int Q,
+                            R *psi0, R *psi1, R *psi2)
+{
+    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < (size_t)nx * Q) {
+        const size_t i = t / Q, o = (i + NG) * 2 * Q + (t - i * Q);
+        const int k = (int)(t - i * Q);
+        psi0[o] = sizeof(R) == 8 ? (R)phi[t] : (R)(phi[t] - ref[k]);
+        psi0[o + Q] = sizeof(R) == 8 ? (R)theta[t] : (R)(theta[t] - ref[Q + k]);
+    } else if (old_ref && t < (size_t)(nx + 2 * NG) * Q) {
+        const size_t g = t - (size_t)nx * Q, i = g / Q;  // ghost row 0..5
+        const int k = (int)(g - i * Q);
+        const size_t o = (i < NG ? i : i + nx) * 2 * Q + k;
+        for (int h = 0; h < 2; ++h) {
+            const int m = h * Q + k;
+            const R v = (R)((double)psi0[o + h * Q] + old_ref[m] - ref[m]);
+            psi0[o + h * Q] = v;
+            psi1[o + h * Q] = v;
+            psi2[o + h * Q] = v;
+        }
+    }
 }
 
 // Per interior cell: n, u, T, q_x, P_xx (Sec. II.D) in FP64, two passes over the nodes, and

@@ -45,3 +45,54 @@ def test_state_round_trip_and_refusals(nx, q, precision):
         assert f"cell {cell}:" in str(e.value) and word in str(e.value)
     assert all(np.array_equal(p, r) for p, r in zip(s.moments(), (n, u, T, qx, pxx)))
     s.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("nx,q", [(8, 8), (63, 12), (65, 20), (1000, 12), (4099, 96)])
+def test_distribution_round_trip_and_refusals(nx, q, precision):
+    """Whole distributions out and in: FP64 bit for bit; FP32 storage holds the deviation from the
+    mean state's equilibrium, so a value comes back to half an ulp of its deviation.  The
+    equilibrium is evaluated here again; its rounding (Q terms that cancel at the outer nodes)
+    is part of what the deviation may be."""
+    import paper_2211_16933_amd as elb
+    say(f"case distributions nx={nx} q={q} precision={precision}")
+    w = workloads.shock_tube(nx=nx, q=q)
+    s = elb.Solver(elb.params_from_workload(w, precision=precision))
+    s.set_state_moments(w["n"], w["u"], w["T"])
+    s.step(3)
+    phi, theta = s.dist()
+    p, wt = elb.quadrature(q)
+    n = phi.sum(1)
+    u = phi @ p / n
+    T = (phi @ (p * p) + theta.sum(1) - n * u * u) / (3.0 * n)
+    nr, ur, Tr = n.mean(), u.mean(), T.mean()
+    h, c = [np.ones(q), p], [1.0, ur]
+    for l in range(1, q - 1):
+        h.append((p * h[l] - np.sqrt(l) * h[l - 1]) / np.sqrt(l + 1))
+        c.append((ur * c[l] + (Tr - 1.0) * np.sqrt(l) * c[l - 1]) / np.sqrt(l + 1))
+    terms = nr * wt[:, None] * np.array(h).T * np.array(c)   # [node][order]
+    refs = [terms.sum(1), 2.0 * Tr * terms.sum(1)]
+    noise = 8 * q * 2.3e-16 * np.abs(terms).sum(1)
+    fresh = elb.Solver(elb.params_from_workload(w, precision=precision))
+    for t in (s, fresh):               # onto a state, and as the first state of a context
+        t.set_state_dist(phi, theta)
+        a, b = t.dist()
+        for got, want, ref in ((a, phi, refs[0]), (b, theta, refs[1])):
+            if precision == 0:
+                assert np.array_equal(got, want)
+            else:
+                dev = np.abs(want - ref) + (1.0 + 2.0 * Tr) * noise
+                assert np.all(np.abs(got - want) <= 2.0 ** -24 * dev + 2.0 ** -52 * np.abs(want) + 1e-44)
+    before = s.dist()
+    for bad in (np.nan, np.inf):
+        for which in (0, 1):
+            arrays = [phi.copy(), theta.copy()]
+            arrays[which][nx - 1, q - 1] = bad
+            with pytest.raises(elb.ElbError):
+                s.set_state_dist(*arrays)
+    assert all(np.array_equal(x, y) for x, y in zip(s.dist(), before))
+    # FP64: both continue alike (FP32 ghost rows were rounded about different first references)
+    if precision == 0:
+        s.step(5)
+        fresh.step(5)
+        assert all(np.array_equal(x, y) for x, y in zip(s.dist(), fresh.dist()))
