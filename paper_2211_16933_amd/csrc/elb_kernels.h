@@ -588,7 +588,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     __shared__ double gref_s[DEV ? Q : 1];   // n_r g_k(u_r, T_r), read by the march
     __shared__ __attribute__((aligned(16))) double red[ROWS * 6 > 128 ? ROWS * 6 : 128];
     __shared__ double r_n[ROWS], r_u[ROWS], r_T[ROWS], r_q[ROWS], r_lnn[ROWS], r_lnT[ROWS];
-    __shared__ __attribute__((aligned(16))) R cellv[W * 16];
+    // Constants of a cell.  FP64 where a wave holds both distributions: 8 common ones, then 8 of
+    // phi and 8 of theta, of which a lane reads its own by address: a select of two FP64 values
+    // is two instructions, and the march of Q = 96 spent 9 of about 100 per cell on choosing
+    // (65536 cells: 112 -> 108 us).  FP32 chooses with selects, which cost as much as the reads
+    // (Q = 40: 10.4 us both), and the learned closure keeps its four blocks per CU that way.
+    constexpr bool MIX = S * (Q / 2) % 64 != 0;
+    constexpr bool OWN = MIX && sizeof(R) == 8 && !CL;
+    constexpr int CV = OWN ? 24 : 16;
+    __shared__ __attribute__((aligned(16))) R cellv[W * CV];
     __shared__ double jm[BOOK ? 2 * W : 1];
     __shared__ double gsum[BOOK ? 3 * (W + 1) : 1];
     __shared__ double ucell[BOOK ? 6 * W : 1];  // bookkeeping: U^(s), then U^n of the cells
@@ -623,12 +631,23 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
 
+    // chi_RET-FM, dynamic LDS: the weights w[2J+1], n over the cells i0-3-J .. i0+wcount+2+J,
+    // chi and ln chi of the staged rows
+    double *fm_wts = nullptr, *fm_n = nullptr, *fm_chi = nullptr, *fm_lnchi = nullptr;
+    if constexpr (RET) {
+        extern __shared__ double fm_s[];
+        fm_wts = fm_s;
+        fm_n = fm_wts + (2 * a.fm_J + 1);
+        fm_chi = fm_n + (2 * a.fm_J + ROWS);
+        fm_lnchi = fm_chi + ROWS;
+    }
+
     // item of this thread: sign half, distribution (phi or theta), strip and node.  When the
     // S Q/2 items of one sign and one distribution fill whole waves (THW), each wave holds
     // items of one distribution only, and the march is compiled for it; otherwise the
     // distribution is chosen per lane.
     constexpr int HQ = S * (Q / 2);
-    constexpr bool THW = HQ % 64 == 0;
+    constexpr bool THW = !MIX;
     const bool neg = tid < G::HW;
     const int it = neg ? tid : tid - G::HW;   // it >= H (ds >= S): no item
     int ds, jn;
@@ -690,6 +709,51 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         const double crefv = DEV ? a.cref[min(tid, QP - 1)] : 0.0;
         const double grefv = DEV ? a.gref[min(tid, Q - 1)] : 0.0;
         const double wv = FIX ? a.w[min(tid, Q - 1)] : 0.0;
+        // chi_RET-FM: the density of the J cells beyond each side of the staged rows, RL lanes per
+        // cell and the additions in the order of phase A, so that a cell's density does not
+        // depend on the tile that reads it (with bookkeeping the tracked n); issued here, behind
+        // the tile's loads, which they would otherwise wait for one after the other
+        if constexpr (RET) {
+            const int J = a.fm_J;
+            for (int x = tid; x <= 2 * J; x += NT) fm_wts[x] = a.fm_w[x];
+            auto beyond = [&](int e) {  // storage row of the e-th of the 2J cells beyond
+                const int c = e < J ? i0 - NG - J + e : i0 + wcount + NG + (e - J);
+                return a.periodic ? row_of(c, nx, 1) : min(max(c, -NG), nx + NG - 1) + NG;
+            };
+            auto slot = [&](int e) { return e < J ? e : rows + e; };
+            if constexpr (BOOK) {
+                for (int e = tid; e < 2 * J; e += NT) fm_n[slot(e)] = a.U_s[3 * (size_t)beyond(e)];
+            } else {
+                for (int base = 0; base < 2 * J * RL; base += NT) {
+                    const int t = base + tid, e = t / RL, m = t % RL;
+                    double v = 0.0;
+                    if (e < 2 * J) {
+                        const R *ph = a.psi_s + (size_t)beyond(e) * C2 + m;
+                        // all values of a lane are in flight together
+                        if constexpr ((Q / 2) % RL == 0) {
+                            R f[Q / (2 * RL)], g[Q / (2 * RL)];
+#pragma unroll
+                            for (int x = 0; x < Q / (2 * RL); ++x) {
+                                f[x] = ph[RL * x];
+                                g[x] = ph[Q - 1 - 2 * m - RL * x];
+                            }
+#pragma unroll
+                            for (int x = 0; x < Q / (2 * RL); ++x) v += (double)f[x] + (double)g[x];
+                        } else {
+                            R f[Q / RL];
+#pragma unroll
+                            for (int x = 0; x < Q / RL; ++x) f[x] = ph[RL * x];
+#pragma unroll
+                            for (int x = 0; x < Q / RL; ++x) v += (double)f[x];
+                        }
+                    }
+                    if constexpr (RL == 8) v += dpp_f64<DPP_MIR8>(v);
+                    v += dpp_f64<DPP_X2>(v);
+                    v += dpp_f64<DPP_X1>(v);
+                    if (e < 2 * J && m == 0) fm_n[slot(e)] = DEV ? v + a.ref_sum[0] : v;
+                }
+            }
+        }
         double *const sinkd = reinterpret_cast<double *>(sink) + lane;
         // when the block is a whole number of rows wide, every load of a thread falls in the
         // same column of the tile, NT / VPR rows apart
@@ -883,6 +947,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         r_q[j] = q;
         r_lnn[j] = log(n);
         r_lnT[j] = log(T);
+        if constexpr (RET) fm_n[a.fm_J + j] = n;
     }
     __syncthreads();
 
@@ -905,60 +970,20 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         }
     }
 
-    // ---- phase R (chi_RET-FM only): the density of the J cells beyond each side of the
-    // staged rows (RL lanes per cell and the additions in the order of phase A, so that a
-    // cell's density does not depend on the tile that reads it; with bookkeeping the tracked
-    // n), then per staged row nbar = sum_{|m|<=J} w_m n_{c+m}, chi = chi_SET(b nbar / 4) and ln chi.
-    // Dynamic LDS: w[2J+1], n over the cells i0-3-J .. i0+wcount+2+J, chi[ROWS], ln chi[ROWS].
-    double *rchi = nullptr, *rlnchi = nullptr;
+    // ---- phase R (chi_RET-FM only): per staged row nbar = sum_{|m|<=J} w_m n_{c+m} (the
+    // densities beyond the staged rows came with phase 0), chi = chi_SET(b nbar / 4) and ln chi
     if constexpr (RET) {
-        extern __shared__ double fm_s[];
-        const int J = a.fm_J;
-        double *wts = fm_s;
-        double *next = wts + (2 * J + 1);
-        rchi = next + (2 * J + ROWS);
-        rlnchi = rchi + ROWS;
-        for (int idx = tid; idx <= 2 * J; idx += NT) wts[idx] = a.fm_w[idx];
-        for (int j = tid; j < rows; j += NT) next[J + j] = r_n[j];
-        auto beyond = [&](int e) {  // storage row of the e-th of the 2J cells beyond
-            const int c = e < J ? i0 - NG - J + e : i0 + wcount + NG + (e - J);
-            return a.periodic ? row_of(c, nx, 1) : min(max(c, -NG), nx + NG - 1) + NG;
-        };
-        auto slot = [&](int e) { return e < J ? e : rows + e; };
-        if constexpr (BOOK) {
-            for (int e = tid; e < 2 * J; e += NT) next[slot(e)] = a.U_s[3 * (size_t)beyond(e)];
-        } else {
-            for (int base = 0; base < 2 * J * RL; base += NT) {
-                const int t = base + tid, e = t / RL, m = t % RL;
-                double v = 0.0;
-                if (e < 2 * J) {
-                    const R *ph = a.psi_s + (size_t)beyond(e) * C2;
-                    if constexpr ((Q / 2) % RL == 0) {
-#pragma unroll 4
-                        for (int kk = m; kk < Q / 2; kk += RL) v += (double)ph[kk] + (double)ph[Q - 1 - kk];
-                    } else {
-#pragma unroll 4
-                        for (int kk = m; kk < Q; kk += RL) v += (double)ph[kk];
-                    }
-                }
-                if constexpr (RL == 8) v += dpp_f64<DPP_MIR8>(v);
-                v += dpp_f64<DPP_X2>(v);
-                v += dpp_f64<DPP_X1>(v);
-                if (e < 2 * J && m == 0) next[slot(e)] = DEV ? v + a.ref_sum[0] : v;
-            }
-        }
-        __syncthreads();
         for (int j = tid; j < rows; j += NT) {
             double nb = 0.0;
-            for (int m = 0; m <= 2 * J; ++m) nb = fma(wts[m], next[j + m], nb);
+            for (int m = 0; m <= 2 * a.fm_J; ++m) nb = fma(fm_wts[m], fm_n[j + m], nb);
             double eta = 0.25 * a.b * nb;
             if (!(nb > 0.0) || !(eta < 1.0)) {
                 atomicOr(a.flag, 1);
                 eta = 0.0;  // keep the block finite; the flag reports the failure
             }
             const double cc = chi_set(eta);
-            rchi[j] = cc;
-            rlnchi[j] = log(cc);
+            fm_chi[j] = cc;
+            fm_lnchi[j] = log(cc);
         }
         __syncthreads();
     }
@@ -979,8 +1004,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         const double dlnT = FD6(r_lnT);
         double chi, dlnchi;
         if constexpr (RET) {
-            chi = rchi[j];
-            dlnchi = FD6(rlnchi);
+            chi = fm_chi[j];
+            dlnchi = FD6(fm_lnchi);
         } else {
             // chi = (2 - eta) / (2 (1 - eta)^3), d ln chi / d ln n = eta (5 - 2 eta) /
             // ((1 - eta)(2 - eta))  (Sec. II.A, chain rule from ln n)
@@ -1003,15 +1028,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         const double itau = n * chi * sqrt(T) * imu * (r2 * dpr * nT);  // 1/tau = n T / mu
         const double iT = r2 * ab * n, in = r2 * ab * T;
         if constexpr (CL) csc_s[i] = n * itau;  // scale of the learned closure's output
-        // per-cell constants of the march, in four 16-byte groups: three read by every item,
-        // the last by the theta items (items that choose phi or theta per lane form the theta
-        // terms from the phi ones).  With x2 = xi^2 / T, the J1 bracket is
+        // per-cell constants of the march.  With x2 = xi^2 / T, the J1 bracket is
         // xi (A + C (x2 + e2)) + B (x2 - e1) and the Shakhov factor qc xi (x2 - e0), with
         // (e0, e1, e2) = (3, 1, 1/3) for phi and (1, 1/3, 7/3) for theta, A = d ln chi + 2 d ln n,
         // B = 0.6 du, C = 0.3 d ln T (derivatives in x), qc = (1 - Pr) q / (5 n T^2).
         const double A = dlnchi + 2.0 * dlnn, Bu = 0.6 * du, C = 0.3 * dlnT;
         const double qc = (1.0 - pr) * (0.2 * in) * iT * iT * q;
-        R *cv = cellv + i * 16;
+        R *cv = cellv + i * CV;
         cv[0] = (R)u;
         cv[1] = (R)iT;
         cv[2] = (R)qc;
@@ -1024,14 +1047,27 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
             reinterpret_cast<unsigned *>(cv)[7] = mix32((unsigned)(i0 + i) * 0x9E3779B1u ^ sd * 0x85EBCA77u);
         else
             cv[7] = R(0);
-        cv[8] = (R)(A + C * (1.0 / 3.0));               // phi: A + C e2
-        cv[9] = (R)(-3.0 * qc);                         //      -qc e0
-        cv[10] = (R)(2.0 * T);                          // theta: 2T
-        cv[11] = (R)(DEV ? 2.0 * (T - a.T_ref) : 0.0);  //        2 (T - T_r)
-        cv[12] = (R)(A + C * (7.0 / 3.0));              //        A + C e2
-        cv[13] = (R)(-Bu * (1.0 / 3.0));                //        -B e1
-        cv[14] = R(0);
-        cv[15] = R(0);
+        const R Ap = (R)(A + C * (1.0 / 3.0));          // phi: A + C e2
+        const R T2 = (R)(2.0 * T), dT2 = (R)(DEV ? 2.0 * (T - a.T_ref) : 0.0);  // theta: 2T, 2 (T - T_r)
+        if constexpr (OWN) {
+            // A + C e2, -B e1, -qc e0, and what multiplies n g in the target
+            const R Cr = (R)C, Br = (R)Bu, qr = (R)qc;
+            cv[8] = Ap;
+            cv[9] = -Br;
+            cv[10] = qr * R(-3);
+            cv[11] = R(1);
+            cv[16] = fma(Cr, R(2), Ap);
+            cv[17] = Br * (R(-1) / R(3));
+            cv[18] = -qr;
+            cv[19] = T2;
+        } else {
+            cv[8] = Ap;
+            cv[9] = (R)(-3.0 * qc);                     // phi: -qc e0
+            cv[10] = T2;                                // theta
+            cv[11] = dT2;
+            cv[12] = (R)(A + C * (7.0 / 3.0));          // theta: A + C e2
+            cv[13] = (R)(-Bu * (1.0 / 3.0));            // theta: -B e1
+        }
         if constexpr (BOOK) {
             // exact moments of J1 (eq. j1_expanded): momentum -y n T (dlnchi + 2 dlnn + dlnT),
             // energy u * momentum - y n T du; its mass moment vanishes
@@ -1237,7 +1273,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         const int mlim = wcount - ib;               // cells of this strip inside the tile
         R *const outp = a.psi_out + (size_t)(i0 + ib + NG) * C2 + dc;
         const R *const inp = a.psi_n + (size_t)(i0 + ib + NG) * C2 + dc;
-        const R *const cvb = cellv + ib * 16;       // per-cell constants of the strip
+        const R *const cvb = cellv + ib * CV;       // per-cell constants of the strip
         const R *const gbb = gbuf + ib * GS;        // equilibrium rows of the strip
         R *const fxb = cbuf + ib * FS + dc;         // bookkeeping: flux rows of the strip
         // the learned closure's correction at this item's cells (phi items only): fused,
@@ -1255,9 +1291,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         auto march = [&](auto negc, auto thc) {
             constexpr bool NEGC = decltype(negc)::value;
             constexpr int THC = decltype(thc)::value;
+            // phi: psi_S = n g (1 + sh), theta: psi_S = 2 T n g (1 + sh), sh = qc xi (x2 - e0)
             const bool th = THC == 2 ? isth : THC == 1;
-            // phi: psi_S = n g (1 + sh), theta: psi_S = 2 T n g (1 + sh), sh = qc xi (x2 - e0);
-            // per-lane choice (THC = 2): the e-terms from the phi constants, A + C e2 =
+            const R *const cvm = cvb + (isth ? 16 : 8);  // OWN: the lane's own constants
+            // per-lane choice by selects: the e-terms from the phi constants, A + C e2 =
             // (A + C/3) + C (e2 - 1/3), -B e1 = B (-e1), -qc e0 = qc (-e0)
             const R de2 = th ? R(2) : R(0);
             const R ne1 = th ? R(-1) / R(3) : R(-1);
@@ -1273,13 +1310,12 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
             // choice: 0-11), so that no read lands in the registers of an unused value, which
             // the next read could take over.
             constexpr bool EARLY = sizeof(R) == 4 && !FIX;
-            constexpr int NG4 = THC == 1 ? 4 : 3;
             struct CellIn { R cv[16]; R e, o; };
             auto fetch = [&](const int m) {
                 CellIn ci;
                 if constexpr (sizeof(R) == 4) {
-                    const floatx4 *cq = reinterpret_cast<const floatx4 *>(cvb + m * 16);
-                    const floatx2 *ch = reinterpret_cast<const floatx2 *>(cvb + m * 16);
+                    const floatx4 *cq = reinterpret_cast<const floatx4 *>(cvb + m * CV);
+                    const floatx2 *ch = reinterpret_cast<const floatx2 *>(cvb + m * CV);
 #pragma unroll
                     for (int q4 = 0; q4 < 2; ++q4) {
                         const floatx4 x = cq[q4];
@@ -1298,7 +1334,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
                     }
                 } else {
 #pragma unroll
-                    for (int t = 0; t < 4 * NG4; ++t) ci.cv[t] = cvb[m * 16 + t];
+                    for (int t = 0; t < 7; ++t) ci.cv[t] = cvb[m * CV + t];
+                    if constexpr (OWN) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) ci.cv[8 + t] = cvm[m * CV + t];
+                    } else {
+                        constexpr int t0 = THC == 1 ? 10 : 8, t1 = THC == 0 ? 10 : THC == 1 ? 14 : 12;
+#pragma unroll
+                        for (int t = t0; t < t1; ++t) ci.cv[t] = cvb[m * CV + t];
+                    }
                 }
                 if constexpr (SPLIT) {
                     ci.e = gbb[m * GS + kp];
@@ -1319,7 +1363,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
                 } else if constexpr (THC == 1) {
                     Ap = cv[12]; Bp = cv[13]; Qp = -qc;
                 } else {
-                    Ap = fma(C, de2, cv[8]); Bp = Bu * ne1; Qp = qc * ne0;
+                    if constexpr (OWN) { Ap = cv[8]; Bp = cv[9]; Qp = cv[10]; }
+                    else { Ap = fma(C, de2, cv[8]); Bp = Bu * ne1; Qp = qc * ne0; }
                 }
                 // n g_k, or n g_k - n_r g_k^r
                 const R dg = SPLIT ? (NEGC ? ci.e - ci.o : ci.e + ci.o) : ci.e;
@@ -1330,15 +1375,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
                 // theta takes 2T dg + 2 (T - T_r) n_r g^r, which keeps the deviation's precision)
                 R mng, psiS;
                 if constexpr (THC == 2) {
-                    const R mth = th ? cv[10] : R(1);   // 1 (phi) or 2T (theta)
-                    const R dth = th ? cv[11] : R(0);   // 0 (phi) or 2 (T - T_r) (theta)
-                    mng = mth * (dg + gref);
-                    psiS = fma(mng, sh, fma(mth, dg, dth * gref));
+                    const R mth = OWN ? cv[11] : th ? cv[10] : R(1);  // 1 (phi) or 2T (theta)
+                    const R dth = DEV && th ? cv[11] : R(0);          // 0 (phi) or 2 (T - T_r) (theta)
+                    mng = mth * (DEV ? dg + gref : dg);
+                    psiS = fma(mng, sh, DEV ? fma(mth, dg, dth * gref) : mth * dg);
                 } else if constexpr (THC == 1) {
-                    mng = cv[10] * (dg + gref);
-                    psiS = fma(mng, sh, fma(cv[10], dg, cv[11] * gref));
+                    mng = cv[10] * (DEV ? dg + gref : dg);
+                    psiS = DEV ? fma(mng, sh, fma(cv[10], dg, cv[11] * gref)) : fma(mng, sh, cv[10] * dg);
                 } else {
-                    mng = dg + gref;
+                    mng = DEV ? dg + gref : dg;
                     psiS = fma(mng, sh, dg);
                 }
                 const R br = fma(xi, fma(C, x2, Ap), fma(Bu, x2, Bp));
