@@ -651,6 +651,29 @@ int64_t elb_workspace_bytes(const elb_params *p)
 
 namespace {
 
+// The stage kernel's copy of Bt, packed per MFMA lane (phase C of the stage kernel).  Where the
+// projection splits by the parity of l over the positive nodes (in halves of KD):
+//   Bp[par][tn][lane][ks] = Bt[2 ((lane / 16) KS + ks) + par][Q/2 + 16 tn + lane % 16],
+// otherwise Bp[tn][lane][ks] = Bt[(lane / 16) KS + ks][16 tn + lane % 16] (KD = QP); KS = KD / 4.
+// Both fill at most QP x QP values (zero outside the table).
+template <typename R>
+void pack_projection(const std::vector<double> &Bt, int Q, int elem, R *out)
+{
+    const int QP = padded_q(Q), QH = Q / 2;
+    const bool split = split_projection(Q, elem);
+    const int KD = split ? padded_q(QH) : QP, KS = KD / 4, TN = KD / 16, NP = split ? 2 : 1;
+    for (int par = 0; par < NP; ++par)
+        for (int tn = 0; tn < TN; ++tn)
+            for (int ln = 0; ln < 64; ++ln)
+                for (int ks = 0; ks < KS; ++ks) {
+                    const int kk = ln >> 4, cl = tn * 16 + (ln & 15);
+                    const int l = split ? 2 * (kk * KS + ks) + par : kk * KS + ks;
+                    const int k = split ? QH + cl : cl;
+                    out[(((size_t)par * TN + tn) * 64 + ln) * KS + ks] =
+                        (R)(l < QP && k < QP ? Bt[(size_t)l * QP + k] : 0.0);
+                }
+}
+
 // elb_create; `stage` is the pinned buffer of the batch that the context belongs to, or NULL.
 int create_ctx(const elb_params *p, void *dev_workspace, int64_t workspace_bytes, void *hip_stream, HostStage *stage,
                elb_ctx **out)
@@ -683,29 +706,13 @@ int create_ctx(const elb_params *p, void *dev_workspace, int64_t workspace_bytes
         hermite_orthonormal(N, c->p[k], h.data());
         for (int l = 0; l <= N; ++l) c->Btd[(size_t)l * QP + k] = c->w[k] * h[l];
     }
-    // the stage kernel's copy of Bt, packed per MFMA lane (phase C of the stage kernel).
-    // When Q/2 is a multiple of 16 it is split by the parity of l over the positive nodes:
-    //   Bp[par][tn][lane][ks] = Bt[2 ((lane / 16) KS + ks) + par][Q/2 + 16 tn + lane % 16],
-    //   KS = Q/8; otherwise Bp[tn][lane][ks] = Bt[(lane / 16) KS + ks][16 tn + lane % 16],
-    //   KS = QP/4.  Both fill QP x QP values.
-    const bool split = (Q / 2) % 16 == 0;
-    const int KD = split ? Q / 2 : QP, KS = KD / 4, TN = KD / 16, NP = split ? 2 : 1;
     // every table in an image of its part of the workspace, uploaded at once
     std::vector<double> image(c->L.tables / sizeof(double), 0.0);
     auto table = [&](size_t off) { return image.data() + off / sizeof(double); };
     std::copy(c->p.begin(), c->p.end(), table(c->L.p));
     std::copy(c->Btd.begin(), c->Btd.end(), table(c->L.btd));
-    double *bpd = table(c->L.bpd);
-    for (int par = 0; par < NP; ++par)
-        for (int tn = 0; tn < TN; ++tn)
-            for (int ln = 0; ln < 64; ++ln)
-                for (int ks = 0; ks < KS; ++ks) {
-                    const int kk = ln >> 4, cl = tn * 16 + (ln & 15);
-                    const int l = split ? 2 * (kk * KS + ks) + par : kk * KS + ks;
-                    const int k = split ? Q / 2 + cl : cl;
-                    bpd[(((size_t)par * TN + tn) * 64 + ln) * KS + ks] = c->Btd[(size_t)l * QP + k];
-                }
-    std::copy(bpd, bpd + (size_t)QP * QP, reinterpret_cast<float *>(table(c->L.bpf)));
+    pack_projection(c->Btd, Q, sizeof(double), table(c->L.bpd));
+    pack_projection(c->Btd, Q, sizeof(float), reinterpret_cast<float *>(table(c->L.bpf)));
     double *sq = table(c->L.sq), *rsq = table(c->L.rsq), *rec = table(c->L.rec);
     for (int l = 0; l < QP + 2; ++l) {
         sq[l] = std::sqrt((double)l);

@@ -106,6 +106,15 @@ ELB_SHAPE(double, 96, 2, 8)
 ELB_SHAPE(double, 200, 2, 8)
 #undef ELB_SHAPE
 
+// Whether the projection onto Q nodes splits into even and odd orders (also the layout of the
+// table Bt): whole 16-wide halves, or in FP64 padded ones of at most 3/5 of the full product
+// (and Q > 64: smaller products are not what a block waits for).
+constexpr bool split_projection(int Q, int elem)
+{
+    const int h = Q / 2, hp = (h + 15) / 16 * 16, qp = (Q + 15) / 16 * 16;
+    return h % 16 == 0 || (elem == 8 && Q > 64 && 2 * hp * hp * 5 <= 3 * qp * qp);
+}
+
 template <typename R, int Q, int S_, int L_>
 struct Geometry {
     static constexpr int S = S_, L = L_;
@@ -147,12 +156,15 @@ struct Geometry {
     // The nodes are symmetric (p_{Q-1-k} = -p_k, equal weights) and He_l has the parity of
     // l, so when Q/2 fills whole 16-wide MFMA tiles the projection splits into even and odd
     // orders over the QH = Q/2 positive nodes (half the work); then QP = 2 QH.
-    static constexpr int QH = Q / 2;
-    static constexpr bool SPLIT = QH % 16 == 0;
+    // FP64 pads the halves where that costs well under the full product (Q = 200: 2 x 112^2
+    // against 208^2, and half as long a chain per tile); FP32 keeps the order of its sums.
+    static constexpr int QH = Q / 2, QHP = (QH + 15) / 16 * 16;
+    static constexpr bool SPLIT = split_projection(Q, sizeof(R));
+    static constexpr int GW = SPLIT ? 2 * QHP : QP;  // columns of the two buffers below
     // LDS row stride of the c buffer (coefficients; [even | odd] when split) and the g
     // buffer (g; [E | O] half sums when split): a multiple of 16 bytes (16-byte operand
     // reads), off a multiple of 32 banks
-    static constexpr int GS = QP + 16 / (int)sizeof(R);
+    static constexpr int GS = GW + 16 / (int)sizeof(R);
     // Every wave holds items of one velocity sign, so the upwind direction of the march is
     // uniform per wave (Q = 200: 400 items per sign in 7 waves each, the last one a quarter
     // full).
@@ -548,7 +560,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
 {
     using G = Geometry<R, Q, S_, L_>;
     constexpr int W = G::W, C2 = G::C2, NT = G::NT, ROWS = G::ROWS, QP = G::QP, GS = G::GS;
-    constexpr int QH = G::QH, WM = G::WM;
+    constexpr int QH = G::QH, QHP = G::QHP, WM = G::WM;
     constexpr bool SPLIT = G::SPLIT;
     constexpr int RG = G::RG;
     constexpr int S = G::S, L = G::L, H = G::H;
@@ -886,7 +898,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     // ---- phase A2 (rows) and zero padding of the coefficient buffer, needed only when the
     // expansion stops short of the padded node count (rows of cells beyond a partial tile
     // give equilibria of cells that are never stored)
-    if (a.N + 1 < QP)
+    if (a.N + 1 < G::GW)
         for (int idx = tid; idx < W * GS; idx += NT) cbuf[idx] = R(0);
     for (int j = tid; j < rows; j += NT) {
         double S0 = red[j * 6 + 0], S1 = red[j * 6 + 1], S2 = red[j * 6 + 2];
@@ -1133,7 +1145,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     // segment's transfer matrix prod [[A_l, B_l], [1, 0]], a scan over the lanes before it
     // gives the segment's starting pair (c_{l0}, c_{l0-1}), and the lane then runs its
     // segment.  With deviation storage the reference coefficients n_r c_l(u_r, T_r) are
-    // subtracted.  Split projection: even orders go to ci[l / 2], odd ones to ci[QH + l / 2].
+    // subtracted.  Split projection: even orders go to ci[l / 2], odd ones to ci[QHP + l / 2].
     {
         const int t = tid - (NT - RG * W);
         if (t >= 0 && t / RG < wcount) {
@@ -1144,7 +1156,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
             const int l0 = 1 + (g * steps) / RG, l1 = 1 + ((g + 1) * steps) / RG;
             R *ci = cbuf + i * GS;
             auto put = [&](int l, double c) {
-                const int o = SPLIT ? (l & 1) * QH + (l >> 1) : l;
+                const int o = SPLIT ? (l & 1) * QHP + (l >> 1) : l;
                 ci[o] = (R)(n * c - (DEV ? cref_s[DEV ? l : 0] : 0.0));
             };
             double s0 = u, s1 = 1.0;  // (c_{l0}, c_{l0 - 1})
@@ -1200,7 +1212,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     //   full:  Bp[tn][lane][ks] = Bt[kk KS + ks][16 tn + lane % 16]
     {
         typedef typename Acc4<R>::type A4;
-        constexpr int KD = SPLIT ? QH : QP;          // contraction length of one tile
+        constexpr int KD = SPLIT ? QHP : QP;         // contraction length of one tile
         constexpr int TM = WM / 16, TN = KD / 16, KS = KD / 4, NP = SPLIT ? 2 : 1;
         constexpr int VB = 16 / (int)sizeof(R);      // values per 16-byte load
         static_assert(KS % VB == 0, "k-steps in whole 16-byte loads");
@@ -1209,7 +1221,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
             const int par = t % NP, tt = t / NP;
             const int tm = tt / TN, tn = tt - tm * TN;
             const int row = tm * 16 + (lane & 15), col = tn * 16 + (lane & 15);
-            const float4 *ap = reinterpret_cast<const float4 *>(cbuf + row * GS + par * QH + kk * KS);
+            const float4 *ap = reinterpret_cast<const float4 *>(cbuf + row * GS + par * QHP + kk * KS);
             const float4 *bp = reinterpret_cast<const float4 *>(
                 a.Bt + (((size_t)par * TN + tn) * 64 + lane) * KS);
             A4 acc;
@@ -1228,7 +1240,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int orow = sizeof(R) == 4 ? 4 * kk + r : kk + 4 * r;
-                gbuf[(tm * 16 + orow) * GS + par * QH + col] = acc[r];
+                gbuf[(tm * 16 + orow) * GS + par * QHP + col] = acc[r];
             }
         }
     }
@@ -1346,7 +1358,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
                 }
                 if constexpr (SPLIT) {
                     ci.e = gbb[m * GS + kp];
-                    ci.o = gbb[m * GS + QH + kp];
+                    ci.o = gbb[m * GS + QHP + kp];
                 } else {
                     ci.e = gbb[m * GS + k];
                     ci.o = R(0);
