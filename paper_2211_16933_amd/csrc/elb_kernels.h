@@ -508,14 +508,25 @@ struct WenoMarch {
             // 1e50: a weight 1e-100 below the largest is zero at FP64 precision, and the
             // products stay below 1e200.  If some indicator vanishes, the weights are
             // delta_q on the zero set and 0 elsewhere (Table III limits).
+            // Waves without a vanishing indicator skip the selects (a branch of the wave: 8 of
+            // some 70 instructions per interface).
             const R mn = fmin(s1, fmin(s2, s3));
             const bool z = mn == R(0);
-            const R im = recip(z ? R(1) : mn);
-            const R g1 = fmin(s1 * im, R(1e50)), g2 = fmin(s2 * im, R(1e50)), g3 = fmin(s3 * im, R(1e50));
-            const R q1 = g1 * g1, q2 = g2 * g2, q3 = g3 * g3;
-            t1 = z ? (s1 == R(0) ? R(0.1) : R(0)) : R(0.1) * (q2 * q3);
-            t2 = z ? (s2 == R(0) ? R(0.6) : R(0)) : R(0.6) * (q1 * q3);
-            t3 = z ? (s3 == R(0) ? R(0.3) : R(0)) : R(0.3) * (q1 * q2);
+            auto products = [&](R im) {
+                const R g1 = fmin(s1 * im, R(1e50)), g2 = fmin(s2 * im, R(1e50)), g3 = fmin(s3 * im, R(1e50));
+                const R q1 = g1 * g1, q2 = g2 * g2, q3 = g3 * g3;
+                t1 = R(0.1) * (q2 * q3);
+                t2 = R(0.6) * (q1 * q3);
+                t3 = R(0.3) * (q1 * q2);
+            };
+            if (__builtin_amdgcn_ballot_w64(z) == 0) {
+                products(recip(mn));
+            } else {
+                products(recip(z ? R(1) : mn));
+                t1 = z ? (s1 == R(0) ? R(0.1) : R(0)) : t1;
+                t2 = z ? (s2 == R(0) ? R(0.6) : R(0)) : t2;
+                t3 = z ? (s3 == R(0) ? R(0.3) : R(0)) : t3;
+            }
         }
     }
 };
