@@ -220,6 +220,27 @@ __device__ inline int row_of(int cell, int nx, int periodic)
     return cell + NG;
 }
 
+// A raw buffer over `bytes` bytes at p: loads at offsets beyond them give zero, stores are dropped.
+__device__ inline __amdgpu_buffer_rsrc_t tile_buffer(void *p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00027000);
+}
+template <typename R>
+__device__ inline R buffer_load(__amdgpu_buffer_rsrc_t b, unsigned at)
+{
+    if constexpr (sizeof(R) == 4) return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(b, at, 0, 0));
+    else return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(b, at, 0, 0));
+}
+__device__ inline void buffer_store(float v, __amdgpu_buffer_rsrc_t b, unsigned at)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), b, at, 0, 0);
+}
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+__device__ inline void buffer_store(double v, __amdgpu_buffer_rsrc_t b, unsigned at)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v), b, at, 0, 0);
+}
+
 __device__ inline floatx4 mfma16x16x4(float a, float b, floatx4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -1272,15 +1293,23 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         // stores may alias these addresses (the last stage writes over psi^n), so loads
         // issued inside the march could not be moved ahead of the stores before them.  (FP64
         // keeps the loads in the march: the registers would spill.)
-        // One uniform branch around branch-free loads (cells past a partial tile read the
-        // tile's last cell and are not stored), so that each cell waits for its own load only.
+        // One uniform branch around branch-free loads, so that each cell waits for its own load
+        // only.
         constexpr bool PRE = sizeof(R) == 4;
         R pn[PRE ? L : 1];
+        const bool has_n = a.a_n != 0.0;
+        // the tile's rows of psi^n and of the output as buffers that end with its last cell:
+        // loads past the end (cells beyond a partial tile; all of psi^n in stage 1) give zero
+        // and stores there are dropped, so neither needs a clamp, a test or a branch per cell
+        const unsigned tile_bytes = (unsigned)(wcount * C2 * (int)sizeof(R));
+        const auto buf_n = tile_buffer(const_cast<R *>(a.psi_n) + (size_t)(i0 + NG) * C2, has_n ? tile_bytes : 0u);
+        const auto buf_out = tile_buffer(a.psi_out + (size_t)(i0 + NG) * C2, tile_bytes);
+        const unsigned at0 = (unsigned)((ib * C2 + dc) * (int)sizeof(R));
+        constexpr unsigned ROWB = C2 * sizeof(R);
         if constexpr (PRE) {
-            const R *const nrow = a.psi_n + (size_t)(i0 + NG) * C2 + dc;
-            if (a.a_n != 0.0) {
+            if (has_n) {
 #pragma unroll
-                for (int m = 0; m < L; ++m) pn[m] = nrow[(size_t)min(ib + m, wcount - 1) * C2];
+                for (int m = 0; m < L; ++m) pn[m] = buffer_load<R>(buf_n, at0 + m * ROWB);
             } else {
 #pragma unroll
                 for (int m = 0; m < L; ++m) pn[m] = R(0);
@@ -1292,10 +1321,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         const R pidx = (R)a.w_flux * pk;            // RK weight x p_k / (6 dx)
         const R pk6 = BOOK ? pk6_s[BOOK ? k : 0] : R(0);  // flux = interpolant x p_k / 6
         const R a_n = (R)a.a_n;
-        const bool has_n = a.a_n != 0.0;
         const int mlim = wcount - ib;               // cells of this strip inside the tile
-        R *const outp = a.psi_out + (size_t)(i0 + ib + NG) * C2 + dc;
-        const R *const inp = a.psi_n + (size_t)(i0 + ib + NG) * C2 + dc;
         const R *const cvb = cellv + ib * CV;       // per-cell constants of the strip
         const R *const gbb = gbuf + ib * GS;        // equilibrium rows of the strip
         R *const fxb = cbuf + ib * FS + dc;         // bookkeeping: flux rows of the strip
@@ -1426,14 +1452,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
                         __float_as_uint(f3 + D) & 0x7f800000u, 31u << 23);   // ulp / 256
                     const float byte = (float)((__float_as_uint(cv[7]) ^ hc) & 255u);
                     const R out = f3 + fma(__uint_as_float(eb), byte - 127.5f, D);
-                    if (m < mlim) outp[(size_t)m * C2] = out;
+                    buffer_store(out, buf_out, at0 + m * ROWB);
                 } else {
+                    // stage 1 loads psi^n = 0 (a_n = 0 adds a zero)
                     R out = f3 - pidx * dI - (f3 - psiS) * itw + myw * br * mng;
-                    if (m < mlim) {
-                        if (THC != 1 && !th && corr) out += (R)cdt * corr[(size_t)m * Q];
-                        if (has_n) out += a_n * (inp[(size_t)m * C2] - f3);
-                        outp[(size_t)m * C2] = out;
-                    }
+                    if (THC != 1 && !th && corr && m < mlim) out += (R)cdt * corr[(size_t)m * Q];
+                    out += a_n * (buffer_load<R>(buf_n, at0 + m * ROWB) - f3);
+                    buffer_store(out, buf_out, at0 + m * ROWB);
                 }
             };
             WenoMarch<R> wm;
