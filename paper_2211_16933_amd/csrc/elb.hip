@@ -1304,47 +1304,46 @@ void drop_graph(elb_batch *b)
     b->graph_steps = 0;
 }
 
-// One stage of every group.  With fork (graph capture), groups 1.. run on side streams that
-// wait for the stage's start on st and are joined back into st at its end, so the captured
-// graph holds them as parallel branches.
-void enqueue_stage(elb_batch *b, hipStream_t st, int s_in, int s_out, bool fork)
+// Stage `s` (0, 1, 2) of one group on stream st.
+void enqueue_stage(elb_batch *b, const BatchGroup &g, hipStream_t st, int s, uint32_t seed)
 {
-    const size_t G = b->groups.size();
-    fork = fork && G > 1 && b->side.size() + 1 >= G;
-    if (fork) (void)hipEventRecord(b->ev_fork, st);
-    for (size_t gi = 0; gi < G; ++gi) {
-        auto &g = b->groups[gi];
-        hipStream_t gs = st;
-        if (fork && gi > 0) {
-            gs = b->side[gi - 1];
-            (void)hipStreamWaitEvent(gs, b->ev_fork, 0);
-        }
-        const int v = g.chosen;
-        BatchStage bs{};
-        bs.inst = b->d_inst;
-        bs.items = g.d_items[v];
-        bs.nitems = g.nitems[v];
-        bs.s_in = s_in;
-        bs.s_out = s_out;
-        bs.a_n = RK_AN[s_in];
-        bs.seed = b->capturing ? b->cap_seed : b->launches;
-        bs.seed_base = b->capturing ? b->seed_dev : nullptr;
-        g.variants[v]->launch(bs, g.grid[v], group_lds(g, v), gs);
-        if (fork && gi > 0) (void)hipEventRecord(b->ev_join[gi - 1], gs);
-    }
-    if (fork)
-        for (size_t gi = 1; gi < G; ++gi) (void)hipStreamWaitEvent(st, b->ev_join[gi - 1], 0);
-    if (b->capturing) ++b->cap_seed;
-    else ++b->launches;
+    const int v = g.chosen;
+    BatchStage bs{};
+    bs.inst = b->d_inst;
+    bs.items = g.d_items[v];
+    bs.nitems = g.nitems[v];
+    bs.s_in = s;
+    bs.s_out = (s + 1) % 3;
+    bs.a_n = RK_AN[s];
+    bs.seed = seed;
+    bs.seed_base = b->capturing ? b->seed_dev : nullptr;
+    g.variants[v]->launch(bs, g.grid[v], group_lds(g, v), st);
 }
 
+// nsteps steps of every group.  With fork (graph capture), groups 1.. run on side streams that
+// wait for the start on st and are joined back into st at the end, so the captured graph holds
+// them as parallel branches.  The groups share nothing that is written, so a branch runs through
+// all its steps: joined after every stage, each stage waited for its slowest group's last
+// blocks (128 problems of 4 node counts, 150 stages and the readout: 14.5 ms, 13.0 without).
 void enqueue_steps(elb_batch *b, hipStream_t st, int64_t nsteps, bool fork)
 {
-    for (int64_t s = 0; s < nsteps; ++s) {
-        enqueue_stage(b, st, 0, 1, fork);
-        enqueue_stage(b, st, 1, 2, fork);
-        enqueue_stage(b, st, 2, 0, fork);
+    const size_t G = b->groups.size();
+    const uint32_t seed0 = b->capturing ? b->cap_seed : b->launches;
+    if (fork && G > 1 && b->side.size() + 1 >= G) {
+        (void)hipEventRecord(b->ev_fork, st);
+        for (size_t gi = 0; gi < G; ++gi) {
+            hipStream_t gs = gi ? b->side[gi - 1] : st;
+            if (gi) (void)hipStreamWaitEvent(gs, b->ev_fork, 0);
+            for (int64_t j = 0; j < 3 * nsteps; ++j)
+                enqueue_stage(b, b->groups[gi], gs, (int)(j % 3), seed0 + (uint32_t)j);
+            if (gi) (void)hipEventRecord(b->ev_join[gi - 1], gs);
+        }
+        for (size_t gi = 1; gi < G; ++gi) (void)hipStreamWaitEvent(st, b->ev_join[gi - 1], 0);
+    } else {
+        for (int64_t j = 0; j < 3 * nsteps; ++j)
+            for (const auto &g : b->groups) enqueue_stage(b, g, st, (int)(j % 3), seed0 + (uint32_t)j);
     }
+    (b->capturing ? b->cap_seed : b->launches) = seed0 + (uint32_t)(3 * nsteps);
 }
 
 // The graph is captured on the batch's private stream (the caller's stream may be the
