@@ -550,22 +550,22 @@ int init_levels(elb_ctx *c)
     return hip_check(c, hipGetLastError(), "init kernel launch");
 }
 
-int run_moments(elb_ctx *c, bool conserved = false)
+// `o`: n, u, T, q, Pxx [nx] each, in device or pinned memory, then the failure flag.
+int run_moments(elb_ctx *c, double *o, bool conserved = false)
 {
-    int nx = c->P.nx, Q = c->Q;
-    double *o = c->dev<double>(c->L.out);
+    const int nx = c->P.nx, Q = c->Q;
     // MOM_LANES threads per cell
     const int threads = 256;
     const unsigned blocks = (unsigned)(((size_t)nx * MOM_LANES + threads - 1) / threads);
     const double *U = c->P.precision == ELB_FP32_MIXED ? c->dev<double>(c->L.U[0]) : nullptr;
+    double *cons = conserved ? c->dev<double>(c->L.cons) : nullptr;
+    const int *flag = c->dev<int>(c->L.flag);
     if (c->P.precision == ELB_FP64)
         hipLaunchKernelGGL(k_moments<double>, dim3(blocks), dim3(threads), 0, c->stream,
-                           c->dev<double>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, o + nx,
-                           o + 2 * nx, o + 3 * nx, o + 4 * nx, conserved ? c->dev<double>(c->L.cons) : nullptr);
+                           c->dev<double>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, flag, cons);
     else
         hipLaunchKernelGGL(k_moments<float>, dim3(blocks), dim3(threads), 0, c->stream,
-                           c->dev<float>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, o + nx,
-                           o + 2 * nx, o + 3 * nx, o + 4 * nx, conserved ? c->dev<double>(c->L.cons) : nullptr);
+                           c->dev<float>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, flag, cons);
     return hip_check(c, hipGetLastError(), "moments kernel launch");
 }
 
@@ -990,14 +990,19 @@ int elb_get_moments(elb_ctx *c, double *n, double *u, double *T, double *qx, dou
 {
     if (!c) return ELB_EINVAL;
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
-    int rc = run_moments(c);
-    if (rc) return rc;
     const size_t nx = c->P.nx;
     double *dst[5] = {n, u, T, qx, pxx};
-    // fields and flag in one copy when the pinned buffer holds them, else field by field
+    // Few cells: the kernel writes the fields and the flag into the pinned buffer itself, which
+    // saves the copy (about 5 us); more: one copy when the buffer holds them, else field by field
     const size_t bytes = sizeof(double) * (5 * nx + 2);
-    if (char *st = c->stage->take(bytes, c->stream)) {
-        rc = hip_check(c, hipMemcpyAsync(st, c->dev<char>(c->L.out), bytes, hipMemcpyDeviceToHost, c->stream), "moments copy");
+    char *st = c->stage->take(bytes, c->stream);
+    const bool direct = st && nx <= MOM_DIRECT;
+    double *o = direct ? reinterpret_cast<double *>(st) : c->dev<double>(c->L.out);
+    int rc = run_moments(c, o);
+    if (rc) return rc;
+    if (st) {
+        if (!direct)
+            rc = hip_check(c, hipMemcpyAsync(st, o, bytes, hipMemcpyDeviceToHost, c->stream), "moments copy");
         if (!rc) rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
         if (rc) return rc;
         c->stage->used = 0;
@@ -1018,7 +1023,9 @@ int elb_get_amplitudes(elb_ctx *c, double k, double out[2])
     if (!out || !std::isfinite(k)) return fail(c, ELB_EINVAL, "NULL output or non-finite k");
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
     const int nx = c->P.nx, Q = c->Q;
-    double *amp = c->dev<double>(c->L.amp);
+    // the kernel writes the three numbers into the pinned buffer itself
+    char *st = c->stage->take(3 * sizeof(double), c->stream);
+    double *amp = st ? reinterpret_cast<double *>(st) : c->dev<double>(c->L.amp);
     const int *flag = c->dev<int>(c->L.flag);
     const double *U = c->P.precision == ELB_FP32_MIXED ? c->dev<double>(c->L.U[0]) : nullptr;
     const double *dens = c->dev<double>(c->L.out);
@@ -1027,7 +1034,7 @@ int elb_get_amplitudes(elb_ctx *c, double k, double out[2])
     // takes about 0.8 us per 64 cells and 16 nodes, the extra launch 6 us.
     const bool direct = U || (size_t)nx * ((Q + MOM_LANES - 1) / MOM_LANES) <= AMP_DIRECT;
     if (!direct) {
-        int rc = run_moments(c);
+        int rc = run_moments(c, c->dev<double>(c->L.out));
         if (rc) return rc;
     }
     if (U || !direct)
@@ -1044,7 +1051,13 @@ int elb_get_amplitudes(elb_ctx *c, double k, double out[2])
     int rc = hip_check(c, hipGetLastError(), "amplitude kernel launch");
     if (rc) return rc;
     double v[3];
-    rc = download(c, v, c->L.amp, sizeof v);
+    if (st) {
+        rc = hip_check(c, hipStreamSynchronize(c->stream), "stream sync");
+        std::memcpy(v, st, sizeof v);
+        c->stage->used = 0;
+    } else {
+        rc = download(c, v, c->L.amp, sizeof v);
+    }
     if (rc) return rc;
     out[0] = v[0];
     out[1] = v[1];
@@ -1076,7 +1089,7 @@ int elb_get_conserved(elb_ctx *c, double out[3])
 {
     if (!c || !out) return ELB_EINVAL;
     if (!c->has_state) return fail(c, ELB_ESTATE, "no state set");
-    int rc = run_moments(c, true);
+    int rc = run_moments(c, c->dev<double>(c->L.out), true);
     if (rc) return rc;
     int nx = c->P.nx;
     std::vector<double> cons(3 * (size_t)nx);

@@ -376,6 +376,7 @@ __global__ void k_dist_pack(const double *phi, const double *theta, const double
 // takes the nodes m, m + 16, ... of phi and theta, and each pass ends with 4 exchange steps
 // inside the 16-lane group.  The second pass re-reads the row from cache.
 constexpr int MOM_LANES = 16;
+constexpr size_t MOM_DIRECT = 2048;  // cells whose moments go straight to pinned memory
 
 __device__ inline double sum16(double v)
 {
@@ -386,9 +387,12 @@ __device__ inline double sum16(double v)
 
 template <typename R>
 __global__ void k_moments(const R *psi, const double *ref, const double *U, const double *p,
-                          int nx, int Q, double *out_n, double *out_u, double *out_T,
-                          double *out_q, double *out_pxx, double *out_cons)
+                          int nx, int Q, double *out, const int *flag, double *out_cons)
 {
+    // out: n, u, T, q, Pxx [nx] each, and the failure flag behind them
+    double *const out_n = out, *const out_u = out + nx, *const out_T = out + 2 * (size_t)nx,
+           *const out_q = out + 3 * (size_t)nx, *const out_pxx = out + 4 * (size_t)nx;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<int *>(out + 5 * (size_t)nx) = *flag;
     const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t i = gid / MOM_LANES;           // one cell per 16-lane group
     const int part = (int)(gid % MOM_LANES);
