@@ -50,7 +50,7 @@ void launch_stage(const void *args, int blocks, size_t shm, hipStream_t st)
 // bits.  X3: also compiled with the learned closure inside (whole 16-cell tiles, Q <= 16).
 #if ELB_STAGE_MODE == 0
 #define ELB_SMALL_TILES(X2, X3) \
-    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024) X3(8, 8, 4, ANY) \
+    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024) X2(8, 8, 4, ANY) \
     X2(12, 8, 1, 256) X3(12, 8, 2, 512) X3(12, 8, 4, 1300) \
     X2(16, 8, 1, 256) X3(16, 8, 2, 512) X3(16, 8, 4, 1024) \
     X2(20, 8, 1, 256) X2(20, 8, 2, 512) \
@@ -63,7 +63,7 @@ void launch_stage(const void *args, int blocks, size_t shm, hipStream_t st)
     X2(200, 2, 2, 128) X2(200, 2, 4, 256)
 #else
 #define ELB_SMALL_TILES(X2, X3) \
-    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024) X3(8, 8, 4, ANY) \
+    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024) X2(8, 8, 4, ANY) \
     X2(12, 8, 1, 256) X3(12, 8, 2, 512) X3(12, 8, 4, 1300) \
     X3(16, 8, 2, 512) X3(16, 8, 4, 1024) \
     X2(20, 8, 1, 256) X2(20, 8, 2, 256) X2(20, 8, 4, 1024) \
@@ -94,6 +94,13 @@ typedef float Real;
 
 const StageKernel kStage[] = {
     ELB_SMALL_TILES(ELB_S2, ELB_S3)
+    // Q = 8 with the learned closure, 65536 cells: FP64 4-cell strips 29.0 us, 8-cell 36.7; mixed
+    // 27.7 and 23.0 (32768 cells: 15.7 and 19.2)
+#if ELB_STAGE_MODE == 0
+    ELB_ST(8, 8, 4, ANY, false, true)
+#else
+    ELB_ST(8, 8, 4, 1300, false, true) ELB_ST(8, 8, 8, INT_MAX, false, true)
+#endif
     ELB_L3(12) ELB_L3(16) ELB_L2(20) ELB_L2(24) ELB_L2(32)
     ELB_L2(40) ELB_L2(48) ELB_L2(64) ELB_L2(96) ELB_L2(200)
 };

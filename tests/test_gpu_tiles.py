@@ -62,3 +62,35 @@ def test_batch_tiles_of_small_problems():
         s.set_state_moments(w["n"], w["u"], w["T"])
         s.step(60)
         assert all(np.array_equal(x, y) for x, y in zip(s.dist(), b.dist(i)))
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32_MIXED])
+@pytest.mark.parametrize("q,nx", [(8, 33), (8, 20001), (8, 45001), (12, 8300), (12, 60001), (16, 8300)])
+def test_learned_closure_on_every_tile(q, nx, precision):
+    """The learned closure inside the stage at cell counts that select each of its tiles, against
+    its two separate kernels: the same network arithmetic, with inputs from row moments summed
+    in another order, so a bfloat16 rounding may flip here and there (5e-3 of the correction's
+    effect, as for a single tile)."""
+    import paper_2211_16933_amd as elb
+    from paper_2211_16933_amd import learned
+    w = workloads.shock_tube(nx=nx, q=q)
+    x = workloads.cell_centres(nx, 1.0)
+    s = 0.5 * (1.0 + np.tanh((x - 0.5) / 0.05))
+    w["n"], w["u"], w["T"] = [a + (b - a) * s for a, b in zip(w["left"], w["right"])]
+    norm = learned.make_norm([1.25, 0, 1.1] + [0.0] * 7 + [0.4, -1.3], [0.3, 0.3, 0.3] + [0.5] * 7 + [1.0, 1.0],
+                             np.zeros(q), np.full(q, nx / 2000.0), -np.full(12, 1e3), np.full(12, 1e3))
+    # (the output scale makes up for the time step, which falls with the cell size, so that the
+    # effect of 3 steps stands far above the FP32 rounding at every size)
+    say(f"case closure tiles q={q} nx={nx} precision={precision}")
+    runs = {}
+    for enabled in (0, 1, 2):
+        c = elb.Solver(elb.params_from_workload(w, precision=precision, closure=1))
+        c.set_state_moments(w["n"], w["u"], w["T"])
+        if enabled:
+            c.set_closure(learned.init_params(q, 5), norm, enabled)
+        c.step(3)
+        runs[enabled] = c.dist()[0]
+        c.close()
+    effect = np.linalg.norm(runs[2] - runs[0])
+    assert effect >= 1e-5 * np.linalg.norm(runs[0])
+    assert np.linalg.norm(runs[1] - runs[2]) <= 5e-3 * effect
