@@ -36,7 +36,7 @@ struct StageArgs {
     const double *p;      // nodes p_k
     const double *w;      // quadrature weights w_k (bookkeeping: moment fix-up)
     const R *Bt;          // Bt[l][k] = w_k He_l(p_k)/sqrt(l!) (zero outside l<=N, k<Q), packed
-                          // per MFMA lane, split by parity when Q/2 % 16 == 0 (phase C)
+                          // per MFMA lane, split by parity where split_projection says so (phase C)
     const double *cref;   // deviation storage: n_r c_l(u_r, T_r), l < Qp
     const double *gref;   // deviation storage: n_r g_k(u_r, T_r), k < Q
     const double *rec;    // [2][Qp]: 1/sqrt(l) and sqrt(l/(l+1)) (recurrence constants)
@@ -100,8 +100,8 @@ ELB_SHAPE(double, 32, 4, 8)
 ELB_SHAPE(double, 40, 8, 8)
 ELB_SHAPE(double, 48, 4, 8)
 ELB_SHAPE(double, 64, 2, 8)
-// Q = 96: 2 x 8 (6 waves, up to 96 registers, three blocks per CU); 4 x 8 held to 80
-// registers spilled in the march
+// Q = 96: 2 x 8 (6 waves, 92 registers: a block's waves go 2, 2, 1, 1 to the four SIMDs, so
+// two blocks share a CU); 4 x 8 held to 80 registers spilled in the march
 ELB_SHAPE(double, 96, 2, 8)
 ELB_SHAPE(double, 200, 2, 8)
 #undef ELB_SHAPE
@@ -127,7 +127,7 @@ struct Geometry {
     static constexpr int HW = (H + 63) / 64 * 64;
     static constexpr int NT = 2 * HW;
     // occupancy the register allocation is held to (waves per SIMD): two blocks of 10 or 12
-    // waves (3 per SIMD each), three of 8 or three of 6 per CU; 1 = no constraint.  Tiles
+    // waves (3 per SIMD each), three of 8 or two of 6 per CU; 1 = no constraint.  Tiles
     // smaller than the large-problem one run about one block per CU, where registers cost
     // nothing (FP64 Q = 64, 128 cells, 4 x 4 held to six waves per SIMD: spills, 9.6 us).
     static constexpr int WD = Shape<R, Q>::S * Shape<R, Q>::L;  // cells of the large-problem tile
@@ -635,7 +635,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
     // Constants of a cell.  FP64 where a wave holds both distributions: 8 common ones, then 8 of
     // phi and 8 of theta, of which a lane reads its own by address: a select of two FP64 values
     // is two instructions, and the march of Q = 96 spent 9 of about 100 per cell on choosing
-    // (65536 cells: 112 -> 108 us).  FP32 chooses with selects, which cost as much as the reads
+    // (65536 cells: 112 -> 108 us when it was changed).  FP32 chooses with selects, which cost as much as the reads
     // (Q = 40: 10.4 us both), and the learned closure keeps its four blocks per CU that way.
     constexpr bool MIX = S * (Q / 2) % 64 != 0;
     constexpr bool OWN = MIX && sizeof(R) == 8 && !CL;
@@ -1322,6 +1322,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
         const R pk6 = BOOK ? pk6_s[BOOK ? k : 0] : R(0);  // flux = interpolant x p_k / 6
         const R a_n = (R)a.a_n;
         const int mlim = wcount - ib;               // cells of this strip inside the tile
+        R *const outp = a.psi_out + (size_t)(i0 + ib + NG) * C2 + dc;  // (plain FP32)
         const R *const cvb = cellv + ib * CV;       // per-cell constants of the strip
         const R *const gbb = gbuf + ib * GS;        // equilibrium rows of the strip
         R *const fxb = cbuf + ib * FS + dc;         // bookkeeping: flux rows of the strip
@@ -1452,7 +1453,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
                         __float_as_uint(f3 + D) & 0x7f800000u, 31u << 23);   // ulp / 256
                     const float byte = (float)((__float_as_uint(cv[7]) ^ hc) & 255u);
                     const R out = f3 + fma(__uint_as_float(eb), byte - 127.5f, D);
-                    buffer_store(out, buf_out, at0 + m * ROWB);
+                    // Plain FP32 keeps a branch per cell around its store: free to move the
+                    // cells into each other, the compiler makes its march slower (65536 cells:
+                    // Q = 96 55.7 us, with the branch 49.5; Q = 64 36.7 and 31.5, Q = 32 21.9
+                    // and 18.2).  With the bookkeeping in the march the buffer is the faster
+                    // one (Q = 96: 54.1, with the branch 55.6).
+                    if constexpr (MODE == MODE_FP32) {
+                        if (m < mlim) outp[(size_t)m * C2] = out;
+                    } else {
+                        buffer_store(out, buf_out, at0 + m * ROWB);
+                    }
                 } else {
                     // stage 1 loads psi^n = 0 (a_n = 0 adds a zero)
                     R out = f3 - pidx * dI - (f3 - psiS) * itw + myw * br * mng;
