@@ -1453,11 +1453,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs<R> &a, const int blk)
                         __float_as_uint(f3 + D) & 0x7f800000u, 31u << 23);   // ulp / 256
                     const float byte = (float)((__float_as_uint(cv[7]) ^ hc) & 255u);
                     const R out = f3 + fma(__uint_as_float(eb), byte - 127.5f, D);
-                    // Plain FP32 keeps a branch per cell around its store: free to move the
-                    // cells into each other, the compiler makes its march slower (65536 cells:
-                    // Q = 96 55.7 us, with the branch 49.5; Q = 64 36.7 and 31.5, Q = 32 21.9
-                    // and 18.2).  With the bookkeeping in the march the buffer is the faster
-                    // one (Q = 96: 54.1, with the branch 55.6).
+                    // Plain FP32 keeps a branch per cell around its store.  Without it the
+                    // compiler overlaps more of one cell with the next than the registers
+                    // hold: at Q = 32, 48 and 96 8 to 12 of them spill, Q = 64 takes 87 and a
+                    // block less per CU (65536 cells: Q = 96 55.7 us, with the branch 49.5;
+                    // Q = 64 36.7 and 31.5, Q = 32 21.9 and 18.2).  With the bookkeeping the
+                    // march fits (78), and the buffer is the faster one (Q = 96: 54.1, with
+                    // the branch 55.6).
                     if constexpr (MODE == MODE_FP32) {
                         if (m < mlim) outp[(size_t)m * C2] = out;
                     } else {
