@@ -11,6 +11,7 @@
 
 #include "elb_kernels.h"
 #include "mlp_device.h"
+#include "state_kernels.h"
 
 namespace elb {
 
@@ -665,13 +666,14 @@ __global__ __launch_bounds__(256) void k_lift_rows(const double *__restrict__ La
 
 // The right-hand side psi1 - psi0 of the interior rows as two planes, phi [nx][Q] and theta
 // [nx][Q] (FP64).
-__global__ void k_rhs_planes(const double *psi1, const double *psi0, int nx, int Q, double *phi, double *theta)
+__global__ __launch_bounds__(PLANE_THREADS) void k_rhs_planes(const double *psi1, const double *psi0, int nx, int Q, double *phi,
+                                                              double *theta)
 {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)nx * Q) return;
-    const size_t i = t / Q, o = i * 2 * Q + (t - i * Q);
-    phi[t] = psi1[o] - psi0[o];
-    theta[t] = psi1[o + Q] - psi0[o + Q];
+    for (size_t t = plane_first(); t < (size_t)nx * Q; t += plane_stride()) {
+        const size_t i = t / Q, o = i * 2 * Q + (t - i * Q);
+        phi[t] = psi1[o] - psi0[o];
+        theta[t] = psi1[o + Q] - psi0[o + Q];
+    }
 }
 
 }  // namespace elb

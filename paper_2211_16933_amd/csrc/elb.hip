@@ -886,13 +886,13 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
         if (rc) return rc;
     }
     // ghost rows (kept from the current state) move to the new reference
-    const unsigned blocks = (unsigned)(((size_t)R * Q + 255) / 256);
+    const dim3 grid = plane_grid((size_t)R * Q);
     if (f64)
-        hipLaunchKernelGGL(k_dist_pack<double>, dim3(blocks), dim3(256), 0, c->stream, (const double *)dphi, (const double *)dtheta,
+        hipLaunchKernelGGL(k_dist_pack<double>, grid, dim3(PLANE_THREADS), 0, c->stream, (const double *)dphi, (const double *)dtheta,
                            c->dev<double>(c->L.ref), (const double *)nullptr, nx, Q, c->dev<double>(c->L.psi[0]),
                            c->dev<double>(c->L.psi[1]), c->dev<double>(c->L.psi[2]));
     else
-        hipLaunchKernelGGL(k_dist_pack<float>, dim3(blocks), dim3(256), 0, c->stream, (const double *)dphi, (const double *)dtheta,
+        hipLaunchKernelGGL(k_dist_pack<float>, grid, dim3(PLANE_THREADS), 0, c->stream, (const double *)dphi, (const double *)dtheta,
                            c->dev<double>(c->L.ref), c->has_state ? c->dev<double>(c->L.oldref) : (const double *)nullptr, nx, Q,
                            c->dev<float>(c->L.psi[0]), c->dev<float>(c->L.psi[1]), c->dev<float>(c->L.psi[2]));
     if (c->P.precision == ELB_FP32_MIXED) {
@@ -1072,12 +1072,12 @@ int elb_get_dist(elb_ctx *c, double *phi, double *theta)
     const size_t n = (size_t)nx * Q;
     size_t at[2];
     dist_planes(c, at);
-    const dim3 grid((unsigned)((n + 255) / 256));
+    const dim3 grid = plane_grid(n);
     if (c->P.precision == ELB_FP64)
-        hipLaunchKernelGGL(k_dist_planes<double>, grid, dim3(256), 0, c->stream, c->dev<double>(c->L.psi[0]),
+        hipLaunchKernelGGL(k_dist_planes<double>, grid, dim3(PLANE_THREADS), 0, c->stream, c->dev<double>(c->L.psi[0]),
                            c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]));
     else
-        hipLaunchKernelGGL(k_dist_planes<float>, grid, dim3(256), 0, c->stream, c->dev<float>(c->L.psi[0]),
+        hipLaunchKernelGGL(k_dist_planes<float>, grid, dim3(PLANE_THREADS), 0, c->stream, c->dev<float>(c->L.psi[0]),
                            c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]));
     int rc = hip_check(c, hipGetLastError(), "dist kernel launch");
     if (!rc && phi) rc = download(c, phi, at[0], sizeof(double) * n);
@@ -2060,7 +2060,7 @@ int elb_rhs(elb_ctx *c, double *phi_rhs, double *theta_rhs)
     const size_t n = (size_t)nx * Q, in = sizeof(double) * (size_t)NG * 2 * Q;
     // the two planes fill the interior of level 2
     double *planes = c->dev<double>(c->L.psi[2] + in);
-    hipLaunchKernelGGL(k_rhs_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
+    hipLaunchKernelGGL(k_rhs_planes, plane_grid(n), dim3(PLANE_THREADS), 0, c->stream,
                        (const double *)c->dev<double>(c->L.psi[1] + in), (const double *)c->dev<double>(c->L.psi[0] + in), nx, Q,
                        planes, planes + n);
     rc = hip_check(c, hipGetLastError(), "rhs launch");

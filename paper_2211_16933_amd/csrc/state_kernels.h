@@ -276,16 +276,33 @@ __global__ void k_conserved_from_psi(const R *psi, const double *ref, LevelU lu,
 // planes lie in the interiors of levels 1 and 2, which hold nothing between steps.  Bound by
 // the copies to and from the host; 10007 cells, Q = 40, FP32: storing 3.2 + 3.2 MB back took
 // 470 to 1370 us with the conversion on the host (page faults of its buffer), restoring 1045.
+//
+// A launch must stay below 2^32 threads, and a plane of 2^32 values or more fits this card: one
+// that large was launched with the remainder of its threads, and all other values were left as
+// they were, without an error.  So the kernels over whole planes stride over them; 8192 blocks
+// (eight rounds of four blocks per CU) keep the copy bandwidth-bound.
 // --------------------------------------------------------------------------------------
-template <typename R>
-__global__ void k_dist_planes(const R *psi, const double *ref, int nx, int Q, double *phi, double *theta)
+constexpr int PLANE_THREADS = 256, PLANE_BLOCKS = 8192;
+
+inline dim3 plane_grid(size_t values)
 {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)nx * Q) return;
-    const size_t i = t / Q, o = (i + NG) * 2 * Q + (t - i * Q);
-    const int k = (int)(t - i * Q);
-    phi[t] = sizeof(R) == 8 ? (double)psi[o] : (double)psi[o] + ref[k];
-    theta[t] = sizeof(R) == 8 ? (double)psi[o + Q] : (double)psi[o + Q] + ref[Q + k];
+    const size_t blocks = (values + PLANE_THREADS - 1) / PLANE_THREADS;
+    return dim3((unsigned)(blocks < (size_t)PLANE_BLOCKS ? blocks : (size_t)PLANE_BLOCKS));
+}
+
+__device__ inline size_t plane_first() { return (size_t)blockIdx.x * PLANE_THREADS + threadIdx.x; }
+__device__ inline size_t plane_stride() { return (size_t)gridDim.x * PLANE_THREADS; }
+
+template <typename R>
+__global__ __launch_bounds__(PLANE_THREADS) void k_dist_planes(const R *psi, const double *ref, int nx, int Q, double *phi,
+                                                               double *theta)
+{
+    for (size_t t = plane_first(); t < (size_t)nx * Q; t += plane_stride()) {
+        const size_t i = t / Q, o = (i + NG) * 2 * Q + (t - i * Q);
+        const int k = (int)(t - i * Q);
+        phi[t] = sizeof(R) == 8 ? (double)psi[o] : (double)psi[o] + ref[k];
+        theta[t] = sizeof(R) == 8 ? (double)psi[o + Q] : (double)psi[o + Q] + ref[Q + k];
+    }
 }
 
 // *bad = 1 when one of n values is not finite.
@@ -344,25 +361,27 @@ __global__ __launch_bounds__(SUM_CELLS) void k_dist_sums(const double *phi, cons
 // Level 0 from the planes; with old_ref != NULL (FP32) also the ghost rows of every level, moved
 // from the old reference to the new one.
 template <typename R>
-__global__ void k_dist_pack(const double *phi, const double *theta, const double *ref, const double *old_ref, int nx, int Q,
-                            R *psi0, R *psi1, R *psi2)
+__global__ __launch_bounds__(PLANE_THREADS) void k_dist_pack(const double *phi, const double *theta, const double *ref,
+                                                             const double *old_ref, int nx, int Q, R *psi0, R *psi1, R *psi2)
 {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < (size_t)nx * Q) {
-        const size_t i = t / Q, o = (i + NG) * 2 * Q + (t - i * Q);
-        const int k = (int)(t - i * Q);
-        psi0[o] = sizeof(R) == 8 ? (R)phi[t] : (R)(phi[t] - ref[k]);
-        psi0[o + Q] = sizeof(R) == 8 ? (R)theta[t] : (R)(theta[t] - ref[Q + k]);
-    } else if (old_ref && t < (size_t)(nx + 2 * NG) * Q) {
-        const size_t g = t - (size_t)nx * Q, i = g / Q;  // ghost row 0..5
-        const int k = (int)(g - i * Q);
-        const size_t o = (i < NG ? i : i + nx) * 2 * Q + k;
-        for (int h = 0; h < 2; ++h) {
-            const int m = h * Q + k;
-            const R v = (R)((double)psi0[o + h * Q] + old_ref[m] - ref[m]);
-            psi0[o + h * Q] = v;
-            psi1[o + h * Q] = v;
-            psi2[o + h * Q] = v;
+    const size_t interior = (size_t)nx * Q, all = old_ref ? interior + (size_t)2 * NG * Q : interior;
+    for (size_t t = plane_first(); t < all; t += plane_stride()) {
+        if (t < interior) {
+            const size_t i = t / Q, o = (i + NG) * 2 * Q + (t - i * Q);
+            const int k = (int)(t - i * Q);
+            psi0[o] = sizeof(R) == 8 ? (R)phi[t] : (R)(phi[t] - ref[k]);
+            psi0[o + Q] = sizeof(R) == 8 ? (R)theta[t] : (R)(theta[t] - ref[Q + k]);
+        } else {
+            const size_t g = t - interior, i = g / Q;  // ghost row 0..5
+            const int k = (int)(g - i * Q);
+            const size_t o = (i < NG ? i : i + nx) * 2 * Q + k;
+            for (int h = 0; h < 2; ++h) {
+                const int m = h * Q + k;
+                const R v = (R)((double)psi0[o + h * Q] + old_ref[m] - ref[m]);
+                psi0[o + h * Q] = v;
+                psi1[o + h * Q] = v;
+                psi2[o + h * Q] = v;
+            }
         }
     }
 }
