@@ -837,13 +837,6 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
 {
     if (!c) return ELB_EINVAL;
     if (!phi || !theta) return fail(c, ELB_EINVAL, "NULL input array");
-    if (!c->has_state && c->P.bc == ELB_BC_EQUILIBRIUM) {
-        // ghost rows need the equilibrium of the end states: set them from a uniform state
-        // first (interior rows are overwritten below)
-        std::vector<double> n(c->P.nx, c->P.ghost_left[0]), u(c->P.nx, c->P.ghost_left[1]), T(c->P.nx, c->P.ghost_left[2]);
-        int rc = elb_set_state_moments(c, n.data(), u.data(), T.data());
-        if (rc) return rc;
-    }
     const int nx = c->P.nx, Q = c->Q, R = nx + 2 * NG;
     const bool f64 = c->P.precision == ELB_FP64;
     const size_t n = (size_t)nx * Q;
@@ -857,7 +850,7 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
     int *bad = c->dev<int>(c->L.check), nonfinite = 0;
     rc = hip_check(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream), "check reset");
     if (rc) return rc;
-    std::vector<double> old_ref;
+    double mean[3] = {};
     if (f64) {
         // theta follows phi
         hipLaunchKernelGGL(k_all_finite, dim3((unsigned)std::min<size_t>(2048, (2 * n + 255) / 256)), dim3(256), 0, c->stream,
@@ -880,8 +873,19 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
         double sn = 0, su = 0, sT = 0;
         for (int i = 0; i < nx; ++i) { sn += f[i]; su += f[(size_t)nx + i]; sT += f[2 * (size_t)nx + i]; }
         if (!(sn > 0) || !(sT > 0) || !std::isfinite(su)) return fail(c, ELB_EINVAL, "distributions with non-positive mean density or temperature");
-        old_ref = c->ref;
-        rc = set_reference(c, sn / nx, su / nx, sT / nx);
+        mean[0] = sn / nx; mean[1] = su / nx; mean[2] = sT / nx;
+    }
+    // the values are taken from here on
+    if (!c->has_state && c->P.bc == ELB_BC_EQUILIBRIUM) {
+        // ghost rows need the equilibrium of the end states: set them from a uniform state
+        // first (which leaves the interiors of levels 1 and 2, and with them the planes, alone)
+        std::vector<double> gn(nx, c->P.ghost_left[0]), gu(nx, c->P.ghost_left[1]), gT(nx, c->P.ghost_left[2]);
+        rc = elb_set_state_moments(c, gn.data(), gu.data(), gT.data());
+        if (rc) return rc;
+    }
+    if (!f64) {
+        const std::vector<double> old_ref = c->ref;
+        rc = set_reference(c, mean[0], mean[1], mean[2]);
         if (!rc) rc = upload(c, c->L.oldref, old_ref.data(), sizeof(double) * old_ref.size());
         if (rc) return rc;
     }

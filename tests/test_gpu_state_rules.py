@@ -1,0 +1,51 @@
+"""What setting a state promises beyond its values (needs an MI355X): a refused restore leaves a
+fresh context without a state."""
+import numpy as np
+import pytest
+
+from helpers import say
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+FP64, FP32, FP32_MIXED = 0, 1, 2
+
+
+def _tube(nx=65, q=12, precision=FP64, **kw):
+    import paper_2211_16933_amd as elb
+    w = workloads.shock_tube(nx=nx, q=q)
+    return w, elb.Solver(elb.params_from_workload(w, precision=precision), **kw)
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32, FP32_MIXED])
+def test_refused_first_restore_leaves_no_state(precision):
+    """A fresh context with end states: refused distributions must not leave the uniform state
+    behind that its ghost rows are built from."""
+    import paper_2211_16933_amd as elb
+    say(f"case refused first restore precision={precision}")
+    w, s = _tube(precision=precision)
+    s.set_state_moments(w["n"], w["u"], w["T"])
+    s.step(3)
+    phi, theta = s.dist()
+    bad = []
+    for which in (0, 1):
+        arrays = [phi.copy(), theta.copy()]
+        arrays[which][7, 3] = np.nan
+        bad.append(arrays)
+    if precision != FP64:                       # (FP64 storage has no mean state to refuse)
+        bad.append([-phi, theta])
+    for arrays in bad:
+        _, f = _tube(precision=precision)
+        with pytest.raises(elb.ElbError) as e:
+            f.set_state_dist(*arrays)
+        assert e.value.code == elb.ELB_EINVAL
+        for call in (lambda: f.step(1), f.moments, f.dist, f.conserved, lambda: f.amplitudes(1.0)):
+            with pytest.raises(elb.ElbError) as e:
+                call()
+            assert e.value.code == elb.ELB_ESTATE
+        f.set_state_dist(phi, theta)            # and a good restore is taken afterwards
+        _, g = _tube(precision=precision)
+        g.set_state_dist(phi, theta)
+        f.step(5)
+        g.step(5)
+        assert all(np.array_equal(x, y) for x, y in zip(f.dist(), g.dist()))
