@@ -139,7 +139,8 @@ int elb_set_state_moments(elb_ctx *c, const double *n, const double *u, const do
  * quadrature-weighted).  Used for checkpoint restore: in ELB_FP64 a restored run continues
  * bit for bit.  In the FP32 modes the values are rounded to the FP32 storage, and in
  * ELB_FP32_MIXED the tracked conserved densities restart from the sums of the given
- * distributions, so a restart continues the run to FP32 rounding only. */
+ * distributions, so a restart continues the run to FP32 rounding only.  As with
+ * elb_set_state_moments, an earlier failure (ELB_ENONFINITE) is forgotten. */
 int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta);
 
 /* Enqueue nsteps RK3 steps (3 stage launches each) on the context stream.  Asynchronous.

@@ -894,11 +894,12 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
     if (f64)
         hipLaunchKernelGGL(k_dist_pack<double>, grid, dim3(PLANE_THREADS), 0, c->stream, (const double *)dphi, (const double *)dtheta,
                            c->dev<double>(c->L.ref), (const double *)nullptr, nx, Q, c->dev<double>(c->L.psi[0]),
-                           c->dev<double>(c->L.psi[1]), c->dev<double>(c->L.psi[2]));
+                           c->dev<double>(c->L.psi[1]), c->dev<double>(c->L.psi[2]), c->dev<int>(c->L.flag));
     else
         hipLaunchKernelGGL(k_dist_pack<float>, grid, dim3(PLANE_THREADS), 0, c->stream, (const double *)dphi, (const double *)dtheta,
                            c->dev<double>(c->L.ref), c->has_state ? c->dev<double>(c->L.oldref) : (const double *)nullptr, nx, Q,
-                           c->dev<float>(c->L.psi[0]), c->dev<float>(c->L.psi[1]), c->dev<float>(c->L.psi[2]));
+                           c->dev<float>(c->L.psi[0]), c->dev<float>(c->L.psi[1]), c->dev<float>(c->L.psi[2]),
+                           c->dev<int>(c->L.flag));
     if (c->P.precision == ELB_FP32_MIXED) {
         // conserved densities of the stored (FP32) distributions, summed in FP64
         const LevelU lu = {{c->dev<double>(c->L.U[0]), c->dev<double>(c->L.U[1]), c->dev<double>(c->L.U[2])}};

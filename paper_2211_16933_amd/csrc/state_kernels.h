@@ -359,11 +359,14 @@ __global__ __launch_bounds__(SUM_CELLS) void k_dist_sums(const double *phi, cons
 }
 
 // Level 0 from the planes; with old_ref != NULL (FP32) also the ghost rows of every level, moved
-// from the old reference to the new one.
+// from the old reference to the new one.  Clears the failure flag, which belongs to the state that
+// these values replace.
 template <typename R>
 __global__ __launch_bounds__(PLANE_THREADS) void k_dist_pack(const double *phi, const double *theta, const double *ref,
-                                                             const double *old_ref, int nx, int Q, R *psi0, R *psi1, R *psi2)
+                                                             const double *old_ref, int nx, int Q, R *psi0, R *psi1, R *psi2,
+                                                             int *flag)
 {
+    if (plane_first() < 4) flag[plane_first()] = 0;
     const size_t interior = (size_t)nx * Q, all = old_ref ? interior + (size_t)2 * NG * Q : interior;
     for (size_t t = plane_first(); t < all; t += plane_stride()) {
         if (t < interior) {
