@@ -22,6 +22,7 @@
  *    for its copies).  The workspace must outlive the context.
  *  - Work is enqueued on the HIP stream given to elb_create (NULL = default stream).
  *    elb_step is asynchronous; calls that return host data synchronise that stream.
+ *    Setting a state is refused (ELB_EHIP) while that stream is being captured.
  *  - A context is used from one host thread at a time.  Distinct contexts are
  *    independent.
  */

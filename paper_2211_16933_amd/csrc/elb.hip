@@ -502,6 +502,17 @@ int upload(elb_ctx *c, size_t off, const void *src, size_t bytes)
     return ELB_OK;
 }
 
+// Refuses a call whose stream is being captured.  A small state goes up through the pinned buffer
+// without a wait, which a capture would take in: the call would report a state that is not set,
+// and a replay would upload whatever the buffer holds by then.
+int not_captured(elb_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const int rc = hip_check(c, hipStreamIsCapturing(c->stream, &st), "stream query");
+    if (rc) return rc;
+    return st == hipStreamCaptureStatusNone ? ELB_OK : fail(c, ELB_EHIP, "a state cannot be set while the stream is captured");
+}
+
 // make_reference and its upload.
 int set_reference(elb_ctx *c, double n_r, double u_r, double T_r)
 {
@@ -756,6 +767,7 @@ int elb_set_state_moments(elb_ctx *c, const double *n, const double *u, const do
 {
     if (!c) return ELB_EINVAL;
     if (!n || !u || !T) return fail(c, ELB_EINVAL, "NULL input array");
+    if (int rc = not_captured(c)) return rc;
     const int nx = c->P.nx;
     const size_t nb = sizeof(double) * nx, tables = sizeof(double) * (padded_q(c->Q) + 3 * (size_t)c->Q);
     // the reference tables and the fields in one upload; fields too large for the pinned
@@ -837,6 +849,7 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
 {
     if (!c) return ELB_EINVAL;
     if (!phi || !theta) return fail(c, ELB_EINVAL, "NULL input array");
+    if (int rc = not_captured(c)) return rc;
     const int nx = c->P.nx, Q = c->Q, R = nx + 2 * NG;
     const bool f64 = c->P.precision == ELB_FP64;
     const size_t n = (size_t)nx * Q;

@@ -1,5 +1,6 @@
 """What setting a state promises beyond its values (needs an MI355X): a refused restore leaves a
-fresh context without a state, and a good one ends a failure."""
+fresh context without a state, a good one ends a failure, and no state is set while the stream is
+captured into a graph."""
 import numpy as np
 import pytest
 
@@ -78,4 +79,41 @@ def test_restore_ends_a_failure(precision, nx):
     f.set_state_dist(phi, theta)
     f.step(2)
     if precision == FP64:          # (FP32 ghost rows were rounded about other references)
+        assert all(np.array_equal(x, y) for x, y in zip(s.dist(), f.dist()))
+
+
+@pytest.mark.parametrize("nx", [65, 2100])
+def test_no_state_is_set_under_capture(nx):
+    """The caller captures a step of the context's stream: setting a state is refused, the capture
+    goes on, and its replays advance the state that was set before."""
+    import torch
+    import paper_2211_16933_amd as elb
+    say(f"case set under capture nx={nx}")
+    stream = torch.cuda.Stream()
+    w, s = _tube(nx=nx, stream=stream)
+    s.set_state_moments(w["n"], w["u"], w["T"])
+    s.step(3)
+    phi, theta = s.dist()
+    b = elb.BatchSolver([elb.params_from_workload(w, precision=FP64)], stream=stream)
+    b.set_state_moments(0, w["n"], w["u"], w["T"])
+    before = b.dist(0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+        s.step(1)
+        for call in (lambda: s.set_state_moments(1.1 * w["n"], w["u"], w["T"]), lambda: s.set_state_dist(phi, theta),
+                     lambda: b.set_state_moments(0, 1.1 * w["n"], w["u"], w["T"])):
+            with pytest.raises(elb.ElbError) as e:
+                call()
+            assert e.value.code == elb.ELB_EHIP
+        s.step(1)
+    assert all(np.array_equal(x, y) for x, y in zip(b.dist(0), before))
+    _, f = _tube(nx=nx)
+    f.set_state_moments(w["n"], w["u"], w["T"])
+    f.step(3)
+    for _ in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        s.step(1)
+        f.step(3)
         assert all(np.array_equal(x, y) for x, y in zip(s.dist(), f.dist()))
