@@ -18,8 +18,9 @@
  *  - Host arrays are caller-owned and copied before the call returns.
  *  - Device memory is caller-owned: the caller allocates elb_workspace_bytes() bytes of
  *    device memory (256-byte aligned) and passes it to elb_create; the library keeps no
- *    other device allocation (a context or batch also holds up to 256 KB of pinned host memory
- *    for its copies).  The workspace must outlive the context.
+ *    other device allocation.  The workspace must outlive the context.  (A context or batch also
+ *    holds up to 256 KB of pinned host memory for its copies, which passes to later ones: at
+ *    most 16 MB in the process.)
  *  - Work is enqueued on the HIP stream given to elb_create (NULL = default stream).
  *    elb_step is asynchronous; calls that return host data synchronise that stream.
  *    Setting a state is refused (ELB_EHIP) while that stream is being captured.

@@ -123,40 +123,100 @@ bool q_supported(int q)
 
 // Pinned host memory that the small uploads and downloads of a context (or of a batch, whose
 // contexts share one stream) go through: taken piece by piece, given back as a whole once the
-// stream has been waited for.  Allocated when the context or batch is created (first use costs
-// 0.1 to 0.3 ms), at most STAGE_MAX bytes.  Measured, us per copy with its wait: 16 KB to the
+// stream has been waited for.  Reserved when the context or batch is created (the first use of a
+// new one costs 0.1 to 0.3 ms), at most STAGE_MAX bytes.  Measured, us per copy with its wait: 16 KB to the
 // host 26 pageable, 12 pinned; 256 KB 116 and 20 (with the copy out of the pinned buffer); from
 // 512 KB (COPY_DIRECT) the runtime pins the caller's pages itself and takes 29, as the pinned
 // buffer does.
 constexpr size_t STAGE_MIN = size_t(1) << 14, STAGE_MAX = size_t(1) << 18, COPY_DIRECT = size_t(1) << 19;
 
-struct HostStage {
+// Pinned buffers pass from closed contexts to new ones: freeing one would wait for every stream of
+// the device, and contexts are independent.  At most PINNED_MAX bytes are ever taken (64 of the
+// largest buffers in use at once); contexts beyond them copy from pageable memory.  The buffers
+// that wait for reuse stay until the process ends.
+constexpr size_t PINNED_MAX = size_t(1) << 24;
+
+struct PinnedBuffer {
     char *p = nullptr;
-    size_t cap = 0, used = 0;
-    ~HostStage() { if (p) (void)hipHostFree(p); }
+    size_t cap = 0;
+    int device = -1;
+};
+
+class PinnedPool {
+public:
+    // a buffer of at least `cap` bytes for the current device (p == NULL: none)
+    PinnedBuffer take(size_t cap)
+    {
+        PinnedBuffer b;
+        if (hipGetDevice(&b.device) != hipSuccess) {
+            (void)hipGetLastError();
+            return b;
+        }
+        std::lock_guard<std::mutex> lk(mu_);
+        int best = -1;
+        for (int i = 0; i < nfree_; ++i)
+            if (free_[i].device == b.device && free_[i].cap >= cap && (best < 0 || free_[i].cap < free_[best].cap)) best = i;
+        if (best >= 0) {
+            b = free_[best];
+            free_[best] = free_[--nfree_];
+            return b;
+        }
+        if (taken_ + cap > PINNED_MAX) return b;
+        if (hipHostMalloc(reinterpret_cast<void **>(&b.p), cap, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            b.p = nullptr;
+            return b;
+        }
+        b.cap = cap;
+        taken_ += cap;
+        std::memset(b.p, 0, cap);  // first touch
+        return b;
+    }
+    // no enqueued copy or kernel may still use it
+    void give(const PinnedBuffer &b)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        free_[nfree_++] = b;
+    }
+
+private:
+    std::mutex mu_;
+    PinnedBuffer free_[PINNED_MAX / STAGE_MIN];  // a place for every buffer there can be
+    int nfree_ = 0;
+    size_t taken_ = 0;
+};
+
+// never destroyed: contexts may be closed while the process ends
+PinnedPool &pinned_pool()
+{
+    static PinnedPool *pool = new PinnedPool();
+    return *pool;
+}
+
+struct HostStage {
+    PinnedBuffer buf;
+    size_t used = 0;
+    // the stream of its copies has been waited for (buf.p = NULL: without success, so that the
+    // buffer must not be used again)
+    ~HostStage() { if (buf.p) pinned_pool().give(buf); }
+    size_t cap() const { return buf.cap; }
     // a buffer of `n` bytes within the limits above (none: everything is copied directly)
     void reserve(size_t n)
     {
-        cap = STAGE_MIN;
-        while (cap < n && cap < STAGE_MAX) cap *= 2;
-        if (hipHostMalloc(reinterpret_cast<void **>(&p), cap, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-            cap = 0;
-            return;
-        }
-        std::memset(p, 0, cap);  // first touch
+        size_t want = STAGE_MIN;
+        while (want < n && want < STAGE_MAX) want *= 2;
+        buf = pinned_pool().take(want);
     }
     // n bytes that no enqueued copy uses; NULL: more than the buffer holds
     char *take(size_t n, hipStream_t st)
     {
         n = align256(n);
-        if (n > cap) return nullptr;
-        if (used + n > cap) {
+        if (n > cap()) return nullptr;
+        if (used + n > cap()) {
             if (hipStreamSynchronize(st) != hipSuccess) return nullptr;
             used = 0;
         }
-        char *at = p + used;
+        char *at = buf.p + used;
         used += n;
         return at;
     }
@@ -490,8 +550,8 @@ void make_reference(elb_ctx *c, double n_r, double u_r, double T_r, double *tabl
 int upload(elb_ctx *c, size_t off, const void *src, size_t bytes)
 {
     for (size_t at = 0; at < bytes;) {
-        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap;
-        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap / 2);
+        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap();
+        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap() / 2);
         char *st = direct ? nullptr : c->stage->take(n, c->stream);
         if (st) std::memcpy(st, (const char *)src + at, n);
         hipError_t e = hipMemcpyAsync(c->dev<char>(off + at), st ? st : (const char *)src + at, n, hipMemcpyHostToDevice, c->stream);
@@ -585,8 +645,8 @@ int run_moments(elb_ctx *c, double *o, bool conserved = false)
 int download(elb_ctx *c, void *dst, size_t off, size_t bytes)
 {
     for (size_t at = 0; at < bytes;) {
-        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap;
-        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap);
+        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap();
+        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap());
         char *st = direct ? nullptr : c->stage->take(n, c->stream);
         hipError_t e = hipMemcpyAsync(st ? st : (char *)dst + at, c->dev<char>(off + at), n, hipMemcpyDeviceToHost, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -749,7 +809,12 @@ int create_ctx(const elb_params *p, void *dev_workspace, int64_t workspace_bytes
     }
     if (stage) c->stage = stage;
     else c->own_stage.reserve(stage_bytes(p));
-    if (set_reference(c, 1.0, 0.0, 1.0) != ELB_OK) { g_create_error = c->err; delete c; return ELB_EHIP; }
+    if (set_reference(c, 1.0, 0.0, 1.0) != ELB_OK) {
+        g_create_error = c->err;
+        if (hipStreamSynchronize(c->stream) != hipSuccess) c->own_stage.buf.p = nullptr;
+        delete c;
+        return ELB_EHIP;
+    }
     *out = c;
     return ELB_OK;
 }
@@ -1140,6 +1205,7 @@ int elb_destroy(elb_ctx *c)
 {
     if (!c) return ELB_EINVAL;
     hipError_t e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) c->own_stage.buf.p = nullptr;
     delete c;
     return e == hipSuccess ? ELB_OK : ELB_EHIP;
 }
@@ -1711,7 +1777,7 @@ const char *elb_batch_last_error(const elb_batch *b)
 int elb_batch_destroy(elb_batch *b)
 {
     if (!b) return ELB_EINVAL;
-    (void)hipStreamSynchronize(b->stream);
+    if (hipStreamSynchronize(b->stream) != hipSuccess) b->stage.buf.p = nullptr;
     drop_graph(b);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
     for (auto sd : b->side) (void)hipStreamDestroy(sd);
