@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <sstream>
@@ -75,8 +76,9 @@ Layout make_layout(int nx, int Q, int N, int precision, int closure, int chi_rea
     L.rec = take(sizeof(double) * 2 * QP);
     L.chiw = chi_reach >= 0 ? take(sizeof(double) * (2 * (size_t)chi_reach + 1)) : o;
     L.tables = o;  // up to here uploaded at creation
-    // uploaded together when a state is set: reference tables, then the fields n, u, T
-    L.cref = take(sizeof(double) * (QP + 3 * (size_t)Q + 3 * (size_t)nx));
+    // uploaded together when a state is set: reference tables, then the fields n, u, T (and a
+    // place for the check of distributions)
+    L.cref = take(sizeof(double) * (QP + 3 * (size_t)Q + 3 * (size_t)nx + 1));
     L.gref = L.cref + sizeof(double) * QP;
     L.ref = L.gref + sizeof(double) * Q;
     L.rows = L.ref + sizeof(double) * 2 * Q;
@@ -124,11 +126,12 @@ bool q_supported(int q)
 // Pinned host memory that the small uploads and downloads of a context (or of a batch, whose
 // contexts share one stream) go through: taken piece by piece, given back as a whole once the
 // stream has been waited for.  Reserved when the context or batch is created (the first use of a
-// new one costs 0.1 to 0.3 ms), at most STAGE_MAX bytes.  Measured, us per copy with its wait: 16 KB to the
-// host 26 pageable, 12 pinned; 256 KB 116 and 20 (with the copy out of the pinned buffer); from
-// 512 KB (COPY_DIRECT) the runtime pins the caller's pages itself and takes 29, as the pinned
-// buffer does.
-constexpr size_t STAGE_MIN = size_t(1) << 14, STAGE_MAX = size_t(1) << 18, COPY_DIRECT = size_t(1) << 19;
+// new one costs 0.1 to 0.3 ms), at most STAGE_MAX bytes.  What the buffer does not hold as a whole is
+// copied directly.  Measured, us per copy with its wait, to the host, directly / through the
+// buffer: 16 KB 22 / 15, 64 KB 12 / 13, 256 KB 20 / 20; in two pieces 384 KB 26 / 35, 512 KB 32 / 40.
+// The caller's array makes no difference when its pages are mapped, copied before or not; pages
+// touched for the first time add 0.15 to 0.25 us per KB on either way.
+constexpr size_t STAGE_MIN = size_t(1) << 14, STAGE_MAX = size_t(1) << 18;
 
 // Pinned buffers pass from closed contexts to new ones: freeing one would wait for every stream of
 // the device, and contexts are independent.  At most PINNED_MAX bytes are ever taken (64 of the
@@ -193,18 +196,23 @@ PinnedPool &pinned_pool()
     return *pool;
 }
 
+// The first bytes hold the failure flag that a kernel leaves for the host, the rest is taken piece
+// by piece.
+constexpr size_t STAGE_HEAD = 256;
+
 struct HostStage {
     PinnedBuffer buf;
     size_t used = 0;
     // the stream of its copies has been waited for (buf.p = NULL: without success, so that the
     // buffer must not be used again)
     ~HostStage() { if (buf.p) pinned_pool().give(buf); }
-    size_t cap() const { return buf.cap; }
+    size_t cap() const { return buf.p ? buf.cap - STAGE_HEAD : 0; }
+    int *flag() const { return reinterpret_cast<int *>(buf.p); }
     // a buffer of `n` bytes within the limits above (none: everything is copied directly)
     void reserve(size_t n)
     {
         size_t want = STAGE_MIN;
-        while (want < n && want < STAGE_MAX) want *= 2;
+        while (want < n + STAGE_HEAD && want < STAGE_MAX) want *= 2;
         buf = pinned_pool().take(want);
     }
     // n bytes that no enqueued copy uses; NULL: more than the buffer holds
@@ -216,7 +224,7 @@ struct HostStage {
             if (hipStreamSynchronize(st) != hipSuccess) return nullptr;
             used = 0;
         }
-        char *at = buf.p + used;
+        char *at = buf.p + STAGE_HEAD + used;
         used += n;
         return at;
     }
@@ -545,21 +553,16 @@ void make_reference(elb_ctx *c, double n_r, double u_r, double T_r, double *tabl
     }
 }
 
-// Copies `bytes` from the host to the workspace in stream order: through the pinned buffer, or
-// directly (and then waiting) when they are many.  The source may change after the return.
-int upload(elb_ctx *c, size_t off, const void *src, size_t bytes)
+// Copies `bytes` from the host to the workspace in stream order: through the pinned buffer when it
+// holds them, else from the caller's memory.  The source may change after the return; with
+// wait = false only after the stream has been waited for.
+int upload(elb_ctx *c, size_t off, const void *src, size_t bytes, bool wait = true)
 {
-    for (size_t at = 0; at < bytes;) {
-        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap();
-        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap() / 2);
-        char *st = direct ? nullptr : c->stage->take(n, c->stream);
-        if (st) std::memcpy(st, (const char *)src + at, n);
-        hipError_t e = hipMemcpyAsync(c->dev<char>(off + at), st ? st : (const char *)src + at, n, hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess && !st) e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) return hip_check(c, e, "copy to the device");
-        at += n;
-    }
-    return ELB_OK;
+    char *st = c->stage->take(bytes, c->stream);
+    if (st) std::memcpy(st, src, bytes);
+    hipError_t e = hipMemcpyAsync(c->dev<char>(off), st ? st : src, bytes, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess && !st && wait) e = hipStreamSynchronize(c->stream);
+    return hip_check(c, e, "copy to the device");
 }
 
 // Refuses a call whose stream is being captured.  A small state goes up through the pinned buffer
@@ -640,21 +643,38 @@ int run_moments(elb_ctx *c, double *o, bool conserved = false)
     return hip_check(c, hipGetLastError(), "moments kernel launch");
 }
 
-// Copies `bytes` from the workspace to the host, waiting for the stream: through the pinned
-// buffer, or directly when they are many.
-int download(elb_ctx *c, void *dst, size_t off, size_t bytes)
+// Copies pieces of the workspace to the host (dst = NULL: not wanted) with one wait for the stream:
+// through the pinned buffer as far as it holds them, the others directly.
+struct Piece {
+    void *dst;
+    size_t off, bytes;
+};
+
+int download(elb_ctx *c, std::initializer_list<Piece> pieces)
 {
-    for (size_t at = 0; at < bytes;) {
-        const bool direct = bytes >= COPY_DIRECT || !c->stage->cap();
-        const size_t n = direct ? bytes : std::min(bytes - at, c->stage->cap());
-        char *st = direct ? nullptr : c->stage->take(n, c->stream);
-        hipError_t e = hipMemcpyAsync(st ? st : (char *)dst + at, c->dev<char>(off + at), n, hipMemcpyDeviceToHost, c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) return hip_check(c, e, "copy to the host");
-        if (st) std::memcpy((char *)dst + at, st, n);
-        c->stage->used = 0;  // the stream has been waited for
-        at += n;
+    char *st[6] = {};
+    size_t all = 0;
+    for (const Piece &p : pieces) all += align256(p.dst ? p.bytes : 0);
+    hipError_t e = hipSuccess;
+    if (c->stage->used && c->stage->used + all > c->stage->cap()) {
+        e = hipStreamSynchronize(c->stream);
+        c->stage->used = 0;
     }
+    int i = 0;
+    for (const Piece &p : pieces) {
+        char *&at = st[i++];
+        if (!p.dst || e != hipSuccess) continue;
+        if (c->stage->used + align256(p.bytes) <= c->stage->cap()) at = c->stage->take(p.bytes, c->stream);
+        e = hipMemcpyAsync(at ? at : p.dst, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return hip_check(c, e, "copy to the host");
+    i = 0;
+    for (const Piece &p : pieces) {
+        if (st[i]) std::memcpy(p.dst, st[i], p.bytes);
+        ++i;
+    }
+    c->stage->used = 0;  // the stream has been waited for
     return ELB_OK;
 }
 
@@ -676,7 +696,7 @@ int flag_status(elb_ctx *c, int flag)
 int check_flag(elb_ctx *c)
 {
     int flag = 0;
-    int rc = download(c, &flag, c->L.flag, sizeof flag);
+    int rc = download(c, {{&flag, c->L.flag, sizeof flag}});
     return rc ? rc : flag_status(c, flag);
 }
 
@@ -861,8 +881,10 @@ int elb_set_state_moments(elb_ctx *c, const double *n, const double *u, const do
     StateCheck sum{};
     double sn = 0, su = 0, sT = 0;
     auto mean_state = [&]() {
-        if (c->P.precision != ELB_FP64)  // FP64 storage has no reference state
-            for (int i = 0; i < nx; ++i) { sn += n[i]; su += u[i]; sT += T[i]; }
+        if (c->P.precision == ELB_FP64) return;  // FP64 storage has no reference state
+        double a = 0, b = 0, d = 0;              // (in registers)
+        for (int i = 0; i < nx; ++i) { a += n[i]; b += u[i]; d += T[i]; }
+        sn = a; su = b; sT = d;
     };
     const bool on_gpu = nx > CHECK_HOST_CELLS;
     if (on_gpu) {
@@ -875,7 +897,7 @@ int elb_set_state_moments(elb_ctx *c, const double *n, const double *u, const do
         if (rc) return rc;
         mean_state();
         StateCheck part[CHECK_BLOCKS];
-        rc = download(c, part, c->L.check, sizeof(StateCheck) * blocks);
+        rc = download(c, {{part, c->L.check, sizeof(StateCheck) * blocks}});
         if (rc) return rc;
         sum = part[0];
         for (int i = 1; i < blocks; ++i) sum.add(part[i]);
@@ -921,20 +943,24 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
     // the planes into the interiors of levels 1 and 2; nothing else changes before they pass
     size_t at[2];
     dist_planes(c, at);
-    int rc = upload(c, at[0], phi, sizeof(double) * n);
-    if (!rc) rc = upload(c, at[1], theta, sizeof(double) * n);
-    if (rc) return rc;
+    int rc = upload(c, at[0], phi, sizeof(double) * n, false);
+    if (!rc) rc = upload(c, at[1], theta, sizeof(double) * n, false);
     double *dphi = c->dev<double>(at[0]), *dtheta = c->dev<double>(at[1]);
-    int *bad = c->dev<int>(c->L.check), nonfinite = 0;
-    rc = hip_check(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream), "check reset");
-    if (rc) return rc;
+    // behind the cells' sums, so that one copy brings both
+    const size_t bad_at = c->L.rows + sizeof(double) * 3 * nx;
+    int *bad = c->dev<int>(bad_at), nonfinite = 0;
+    if (!rc) rc = hip_check(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream), "check reset");
+    if (rc) {
+        (void)hipStreamSynchronize(c->stream);  // the planes may still be read
+        return rc;
+    }
     double mean[3] = {};
     if (f64) {
         // theta follows phi
         hipLaunchKernelGGL(k_all_finite, dim3((unsigned)std::min<size_t>(2048, (2 * n + 255) / 256)), dim3(256), 0, c->stream,
                            (const double *)dphi, 2 * n, bad);
-        rc = hip_check(c, hipGetLastError(), "check kernel launch");
-        if (!rc) rc = download(c, &nonfinite, c->L.check, sizeof(int));
+        rc = download(c, {{&nonfinite, bad_at, sizeof nonfinite}});
+        if (!rc) rc = hip_check(c, hipGetLastError(), "check kernel launch");
         if (rc) return rc;
         if (nonfinite) return fail(c, ELB_EINVAL, "non-finite distribution value");
     } else {
@@ -942,11 +968,11 @@ int elb_set_state_dist(elb_ctx *c, const double *phi, const double *theta)
         // runs over the cells in order
         hipLaunchKernelGGL(k_dist_sums, dim3((nx + SUM_CELLS - 1) / SUM_CELLS), dim3(SUM_CELLS), 0, c->stream,
                            (const double *)dphi, (const double *)dtheta, c->dev<double>(c->L.p), nx, Q, c->dev<double>(c->L.rows), bad);
-        rc = hip_check(c, hipGetLastError(), "sum kernel launch");
-        std::vector<double> f(3 * (size_t)nx);
-        if (!rc) rc = download(c, f.data(), c->L.rows, sizeof(double) * f.size());
-        if (!rc) rc = download(c, &nonfinite, c->L.check, sizeof(int));
+        std::vector<double> f(3 * (size_t)nx + 1);
+        rc = download(c, {{f.data(), c->L.rows, sizeof(double) * f.size()}});
+        if (!rc) rc = hip_check(c, hipGetLastError(), "sum kernel launch");
         if (rc) return rc;
+        std::memcpy(&nonfinite, &f[3 * (size_t)nx], sizeof nonfinite);
         if (nonfinite) return fail(c, ELB_EINVAL, "non-finite distribution value");
         double sn = 0, su = 0, sT = 0;
         for (int i = 0; i < nx; ++i) { sn += f[i]; su += f[(size_t)nx + i]; sT += f[2 * (size_t)nx + i]; }
@@ -1095,9 +1121,11 @@ int elb_get_moments(elb_ctx *c, double *n, double *u, double *T, double *qx, dou
         std::memcpy(&flag, st + sizeof(double) * 5 * nx, sizeof flag);
         return flag_status(c, flag);
     }
-    for (int f = 0; f < 5 && !rc; ++f)
-        if (dst[f]) rc = download(c, dst[f], c->L.out + sizeof(double) * f * nx, sizeof(double) * nx);
-    return rc ? rc : check_flag(c);
+    int flag = 0;
+    const size_t at = c->L.out, nb = sizeof(double) * nx;
+    rc = download(c, {{dst[0], at, nb}, {dst[1], at + nb, nb}, {dst[2], at + 2 * nb, nb}, {dst[3], at + 3 * nb, nb},
+                      {dst[4], at + 4 * nb, nb}, {&flag, c->L.flag, sizeof flag}});
+    return rc ? rc : flag_status(c, flag);
 }
 
 int elb_get_amplitudes(elb_ctx *c, double k, double out[2])
@@ -1139,7 +1167,7 @@ int elb_get_amplitudes(elb_ctx *c, double k, double out[2])
         std::memcpy(v, st, sizeof v);
         c->stage->used = 0;
     } else {
-        rc = download(c, v, c->L.amp, sizeof v);
+        rc = download(c, {{v, c->L.amp, sizeof v}});
     }
     if (rc) return rc;
     out[0] = v[0];
@@ -1158,14 +1186,16 @@ int elb_get_dist(elb_ctx *c, double *phi, double *theta)
     const dim3 grid = plane_grid(n);
     if (c->P.precision == ELB_FP64)
         hipLaunchKernelGGL(k_dist_planes<double>, grid, dim3(PLANE_THREADS), 0, c->stream, c->dev<double>(c->L.psi[0]),
-                           c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]));
+                           c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]), c->dev<int>(c->L.flag),
+                           c->stage->flag());
     else
         hipLaunchKernelGGL(k_dist_planes<float>, grid, dim3(PLANE_THREADS), 0, c->stream, c->dev<float>(c->L.psi[0]),
-                           c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]));
+                           c->dev<double>(c->L.ref), nx, Q, c->dev<double>(at[0]), c->dev<double>(at[1]), c->dev<int>(c->L.flag),
+                           c->stage->flag());
     int rc = hip_check(c, hipGetLastError(), "dist kernel launch");
-    if (!rc && phi) rc = download(c, phi, at[0], sizeof(double) * n);
-    if (!rc && theta) rc = download(c, theta, at[1], sizeof(double) * n);
-    return rc ? rc : check_flag(c);
+    if (!rc) rc = download(c, {{phi, at[0], sizeof(double) * n}, {theta, at[1], sizeof(double) * n}});
+    if (rc) return rc;
+    return c->stage->flag() ? flag_status(c, *c->stage->flag()) : check_flag(c);
 }
 
 int elb_get_conserved(elb_ctx *c, double out[3])
@@ -2149,9 +2179,9 @@ int elb_rhs(elb_ctx *c, double *phi_rhs, double *theta_rhs)
                        planes, planes + n);
     rc = hip_check(c, hipGetLastError(), "rhs launch");
     if (!rc) rc = check_flag(c);
-    if (!rc && phi_rhs) rc = download(c, phi_rhs, c->L.psi[2] + in, sizeof(double) * n);
-    if (!rc && theta_rhs) rc = download(c, theta_rhs, c->L.psi[2] + in + sizeof(double) * n, sizeof(double) * n);
-    return rc;
+    if (rc) return rc;
+    const size_t at = c->L.psi[2] + in, nb = sizeof(double) * n;
+    return download(c, {{phi_rhs, at, nb}, {theta_rhs, at + nb, nb}});
 }
 
 int elb_closure_sample(elb_ctx *teacher, elb_ctx *student, float *x, float *y)
@@ -2191,8 +2221,7 @@ int elb_closure_sample(elb_ctx *teacher, elb_ctx *student, float *x, float *y)
                        closure_const(s), nx, QS, (const double *)Lt, (const double *)(s->dev<double>(s->L.psi[1]) + offS),
                        (const double *)sp, 2 * QS, s->dev<float>(s->L.sx), s->dev<float>(s->L.sy));
     rc = hip_check(s, hipGetLastError(), "sample launch");
-    if (!rc) rc = download(s, x, s->L.sx, sizeof(float) * MLP_IN * (size_t)nx);
-    if (!rc) rc = download(s, y, s->L.sy, sizeof(float) * QS * (size_t)nx);
+    if (!rc) rc = download(s, {{x, s->L.sx, sizeof(float) * MLP_IN * (size_t)nx}, {y, s->L.sy, sizeof(float) * QS * (size_t)nx}});
     if (rc) return rc;
     rc = check_flag(t);
     if (rc) return fail(s, rc, "teacher: %s", t->err.c_str());

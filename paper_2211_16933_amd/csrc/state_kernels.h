@@ -295,8 +295,9 @@ __device__ inline size_t plane_stride() { return (size_t)gridDim.x * PLANE_THREA
 
 template <typename R>
 __global__ __launch_bounds__(PLANE_THREADS) void k_dist_planes(const R *psi, const double *ref, int nx, int Q, double *phi,
-                                                               double *theta)
+                                                               double *theta, const int *flag, int *flag_out)
 {
+    if (flag_out && plane_first() == 0) *flag_out = *flag;  // pinned memory: no copy of its own
     for (size_t t = plane_first(); t < (size_t)nx * Q; t += plane_stride()) {
         const size_t i = t / Q, o = (i + NG) * 2 * Q + (t - i * Q);
         const int k = (int)(t - i * Q);

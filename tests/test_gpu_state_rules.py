@@ -1,6 +1,6 @@
 """What setting a state promises beyond its values (needs an MI355X): a refused restore leaves a
 fresh context without a state, a good one ends a failure, and no state is set while the stream is
-captured into a graph."""
+captured into a graph; and the copies at the sizes where their way changes."""
 import numpy as np
 import pytest
 
@@ -117,3 +117,34 @@ def test_no_state_is_set_under_capture(nx):
         s.step(1)
         f.step(3)
         assert all(np.array_equal(x, y) for x, y in zip(s.dist(), f.dist()))
+
+
+@pytest.mark.parametrize("nx,q", [(402, 40), (403, 8), (404, 8), (504, 40), (6546, 8), (6547, 8), (6547, 40), (33000, 8)])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_copies_at_the_edges_of_the_pinned_buffer(nx, q, precision):
+    """Readouts and restores whose pieces fill the buffer (16 KB to 256 KB less its 256-byte head) to
+    the last value, one cell more or less, and whose pieces go part through it, part directly."""
+    import paper_2211_16933_amd as elb
+    say(f"case copies nx={nx} q={q} precision={precision}")
+    w, s = _tube(nx=nx, q=q, precision=precision)
+    s.set_state_moments(w["n"], w["u"], w["T"])
+    s.step(2)
+    phi, theta = s.dist()
+    p, _ = elb.quadrature(q)
+    n, u, T, qx, pxx = s.moments()
+    # sums of q terms in another order: q rounding errors of the largest partial sums, which the
+    # outer nodes' cubes scale (below 10 p_max^3 here)
+    tol = 16 * q * 2.3e-16 * (1.0 + 10.0 * p[-1] ** 3)
+    xi = p - u[:, None]
+    e = 0.5 * xi * xi * phi + 0.5 * theta
+    for got, want in ((n, phi.sum(1)), (u, phi @ p / n), (T, e.sum(1) / (1.5 * n)), (qx, (xi * e).sum(1)),
+                      (pxx, (xi * xi * phi).sum(1))):
+        assert np.max(np.abs(got - want)) <= tol
+    back = phi[::-1].copy(), theta[::-1].copy()
+    s.set_state_dist(*back)
+    got = s.dist()
+    if precision == FP64:
+        assert all(np.array_equal(a, b) for a, b in zip(got, back))
+    else:           # deviations below 0.5 in FP32
+        assert all(np.max(np.abs(a - b)) <= 0.5 * 2.0 ** -24 + 1e-15 for a, b in zip(got, back))
+    assert np.max(np.abs(s.moments()[0] - n[::-1])) <= tol + (0.0 if precision == FP64 else q * 0.5 * 2.0 ** -24)
