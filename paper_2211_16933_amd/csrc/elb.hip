@@ -628,18 +628,20 @@ int init_levels(elb_ctx *c)
 int run_moments(elb_ctx *c, double *o, bool conserved = false)
 {
     const int nx = c->P.nx, Q = c->Q;
-    // MOM_LANES threads per cell
     const int threads = 256;
-    const unsigned blocks = (unsigned)(((size_t)nx * MOM_LANES + threads - 1) / threads);
     const double *U = c->P.precision == ELB_FP32_MIXED ? c->dev<double>(c->L.U[0]) : nullptr;
     double *cons = conserved ? c->dev<double>(c->L.cons) : nullptr;
     const int *flag = c->dev<int>(c->L.flag);
-    if (c->P.precision == ELB_FP64)
-        hipLaunchKernelGGL(k_moments<double>, dim3(blocks), dim3(threads), 0, c->stream,
-                           c->dev<double>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, flag, cons);
-    else
-        hipLaunchKernelGGL(k_moments<float>, dim3(blocks), dim3(threads), 0, c->stream,
-                           c->dev<float>(c->L.psi[0]), c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, o, flag, cons);
+    for (int first = 0; first < nx; first += MOM_CELLS) {  // nx <= 2^30
+        // MOM_LANES threads per cell
+        const unsigned blocks = (unsigned)(((size_t)std::min(nx - first, MOM_CELLS) * MOM_LANES + threads - 1) / threads);
+        if (c->P.precision == ELB_FP64)
+            hipLaunchKernelGGL(k_moments<double>, dim3(blocks), dim3(threads), 0, c->stream, c->dev<double>(c->L.psi[0]),
+                               c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, first, o, flag, cons);
+        else
+            hipLaunchKernelGGL(k_moments<float>, dim3(blocks), dim3(threads), 0, c->stream, c->dev<float>(c->L.psi[0]),
+                               c->dev<double>(c->L.ref), U, c->dev<double>(c->L.p), nx, Q, first, o, flag, cons);
+    }
     return hip_check(c, hipGetLastError(), "moments kernel launch");
 }
 

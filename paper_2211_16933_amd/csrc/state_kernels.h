@@ -397,8 +397,10 @@ __global__ __launch_bounds__(PLANE_THREADS) void k_dist_pack(const double *phi, 
 //
 // 16 lanes per cell (MOM_LANES), so a wave reads four rows as 64-byte segments: lane m
 // takes the nodes m, m + 16, ... of phi and theta, and each pass ends with 4 exchange steps
-// inside the 16-lane group.  The second pass re-reads the row from cache.
-constexpr int MOM_LANES = 16;
+// inside the 16-lane group.  The second pass re-reads the row from cache.  A launch takes the cells
+// from `first` on, at most MOM_CELLS of them: one of 2^32 threads or more would run only the
+// remainder.
+constexpr int MOM_LANES = 16, MOM_CELLS = 1 << 24;
 constexpr size_t MOM_DIRECT = 2048;  // cells whose moments go straight to pinned memory
 
 __device__ inline double sum16(double v)
@@ -410,14 +412,14 @@ __device__ inline double sum16(double v)
 
 template <typename R>
 __global__ void k_moments(const R *psi, const double *ref, const double *U, const double *p,
-                          int nx, int Q, double *out, const int *flag, double *out_cons)
+                          int nx, int Q, int first, double *out, const int *flag, double *out_cons)
 {
     // out: n, u, T, q, Pxx [nx] each, and the failure flag behind them
     double *const out_n = out, *const out_u = out + nx, *const out_T = out + 2 * (size_t)nx,
            *const out_q = out + 3 * (size_t)nx, *const out_pxx = out + 4 * (size_t)nx;
     if (blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<int *>(out + 5 * (size_t)nx) = *flag;
     const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t i = gid / MOM_LANES;           // one cell per 16-lane group
+    const size_t i = first + gid / MOM_LANES;   // one cell per 16-lane group
     const int part = (int)(gid % MOM_LANES);
     // every lane of a group shares i, so a group is live or idle as a whole; idle groups
     // still run the exchanges (on zeros) and store nothing

@@ -1,5 +1,5 @@
-"""Distributions read and restored over whole planes (needs an MI355X): every value, also where a
-plane holds more values than a launch may hold threads."""
+"""Distributions read and restored over whole planes, and the moments of every cell (needs an
+MI355X): every value, also where there are more than a launch may hold threads for."""
 import ctypes
 
 import numpy as np
@@ -69,3 +69,26 @@ def test_planes_beyond_one_sweep_of_a_launch(precision):
     back = [np.tile(b[::-1], (copies, 1)) for b in state]      # another state, restored
     many.set_state_dist(*back)
     assert all(np.max(np.abs(a - b)) <= tol for a, b in zip(many.dist(), back))
+
+
+def test_moments_of_2_28_cells():
+    """2^28 + 77 cells, 16 threads each: the uniform state at rest in every cell."""
+    import psutil
+    import torch
+    import paper_2211_16933_amd as elb
+    nx = (1 << 28) + 77
+    P = elb.params_from_workload(_wave(nx, 8), precision=elb.FP32)
+    torch.cuda.empty_cache()
+    if psutil.virtual_memory().available < 16 * 8 * nx or torch.cuda.mem_get_info()[0] < 1.1 * elb.workspace_bytes(P):
+        pytest.skip("not enough host or GPU memory for 2^28 cells")
+    say(f"case moments of {nx} cells")
+    s = elb.Solver(P)
+    one = np.ones(nx)
+    s.set_state_moments(one, np.zeros(nx), one)
+    got = s.moments()
+    s.close()
+    # the state equals its own reference: sums of 8 values, each rounded to 1e-16
+    for f, want in zip(got, (1.0, 0.0, 1.0, 0.0, 1.0)):
+        assert f.size == nx and max(abs(f.min() - want), abs(f.max() - want)) <= 1e-14
+    del s, got, one
+    torch.cuda.empty_cache()
