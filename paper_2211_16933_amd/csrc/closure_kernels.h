@@ -118,10 +118,16 @@ __device__ inline void mlp_forward_rows(MlpSmem &s, int wave, int lane, float *z
 // are bound by latency, and each is cut into as many short blocks as the shapes give: 16 rows
 // per block forward and backward, the 64 columns of a layer spread over four waves, every
 // weight a wave needs loaded from L2 at the start (no staging in LDS); weight gradients by
-// (128-row chunk, layer), from operands that the forward and backward kernels leave in the
-// layout the matrix cores read.  Batch 4096, us per launch before (64 rows per block with
-// staged weights; gradients one block per chunk, transposing through LDS) and now: forward
-// 17.8 / 6.9, backward 17.3 / 7.0, weight gradients 75.6 / 5.7, reduction 8.6 / 3.2.
+// (128-row chunk, layer), from operands that the backward kernel leaves in the layout the matrix
+// cores read.  Batch 4096, us per launch before (64 rows per block with staged weights; gradients
+// one block per chunk, transposing through LDS) and now: forward 17.8 / 5.4, backward 17.3 / 8.6,
+// weight gradients 75.6 / 5.6, reduction 8.6 / 3.2.
+//
+// From about 2e5 rows on, the forward is bound by what it writes, 830 bytes per row (mostly the
+// pre-activations, which stay FP32).  It is also all that an evaluation runs, so the transposed
+// operands, another 450 bytes, are left to the backward kernel, which has the pre-activations in
+// hand: 1048576 rows 325 us (625 with them in the forward, 2-byte stores 256 bytes apart; 365
+// before), 4194304 rows 1241 (2638; 1407).  Backward and gradients there: 1.9 ms (5.7), 7.8 (22.6).
 // --------------------------------------------------------------------------------------
 constexpr int TRAIN_ROWS = 16;  // batch rows per block, forward and backward
 
@@ -134,17 +140,15 @@ __device__ inline size_t chunk_at(int b, int c, int cols)
 
 // Training forward: rows b < batch of x[index[b]] (or x[b]), normalised, through the MLP.
 // y [batch][16] (normalised outputs).  Kept for the backward pass: z [3][batch][64]
-// pre-activations, and transposed by chunk the bf16 layer inputs a0t (32 columns) and at
-// (64 columns, layers 2..4, lstride apart).
+// pre-activations and the bf16 inputs a0 [batch][32].  A block takes `tiles` tiles of 16 rows one
+// after another with its weights in registers (forward_tiles).
 __global__ __launch_bounds__(256) void k_mlp_forward(const unsigned short *wb, const float *params,
                                                      const float *norm, const float *x,
-                                                     const int *index, int batch, float *y,
-                                                     unsigned short *a0t, unsigned short *at, size_t astride,
-                                                     float *z)
+                                                     const int *index, int batch, int tiles, float *y,
+                                                     unsigned short *a0, float *z)
 {
     __shared__ __attribute__((aligned(16))) unsigned short act[2][TRAIN_ROWS * AS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int row0 = blockIdx.x * TRAIN_ROWS;
     const int col = lane & 15, rq = 4 * (lane >> 4), kq = 8 * (lane >> 4);
     const int c = wave * 16 + col;  // this lane's output column of the hidden layers
     const bf16x8 w1 = ld8(wb + OFF_W1 + c * MLP_K1 + kq);
@@ -157,43 +161,45 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const unsigned short *wb, c
     }
     const float bias[3] = {params[OFF_B1 + c], params[OFF_B2 + c], params[OFF_B3 + c]};
     const float bias4 = params[OFF_B4 + col];
-    // inputs: 16 rows of 32 columns, two per thread
-    for (int j = threadIdx.x; j < TRAIN_ROWS * MLP_K1; j += 256) {
-        const int r = j / MLP_K1, k = j % MLP_K1, b = row0 + r;
-        float v = 0.f;
-        if (b < batch && k < MLP_IN) {
-            const int src = index ? index[b] : b;
-            v = (x[(size_t)src * MLP_IN + k] - norm[NRM_IN_MEAN + k]) / norm[NRM_IN_STD + k];
-        }
-        const unsigned short h = f2bf(v);
-        act[0][r * AS + k] = h;
-        a0t[chunk_at(b, k, MLP_K1)] = h;
-    }
-    __syncthreads();
     const size_t zstride = (size_t)batch * MLP_H;
-    floatx4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(act[0] + col * AS + kq), w1, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-#pragma unroll
-    for (int l = 0; l < 3; ++l) {
-        unsigned short *out = act[(l + 1) & 1];
-        ushort4 h4;
-        unsigned short *h = reinterpret_cast<unsigned short *>(&h4);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float zz = acc[r] + bias[l];
-            if (row0 + rq + r < batch) z[l * zstride + (size_t)(row0 + rq + r) * MLP_H + c] = zz;
-            h[r] = f2bf(silu(zz));
-            out[(rq + r) * AS + c] = h[r];
+    const int end = (int)min((long long)batch, ((long long)blockIdx.x + 1) * tiles * TRAIN_ROWS);
+    for (int row0 = blockIdx.x * tiles * TRAIN_ROWS; row0 < end; row0 += TRAIN_ROWS) {
+        // inputs: 16 rows of 32 columns, two neighbours per thread.  act[0] is free: what the tile
+        // before read from it was read before its last barrier
+        {
+            const int r = threadIdx.x >> 4, k = 2 * (threadIdx.x & 15), b = row0 + r;
+            ushort2 h = {0, 0};
+            if (b < batch && k < MLP_IN) {
+                const float *xr = x + (size_t)(index ? index[b] : b) * MLP_IN;
+                h.x = f2bf((xr[k] - norm[NRM_IN_MEAN + k]) / norm[NRM_IN_STD + k]);
+                h.y = f2bf((xr[k + 1] - norm[NRM_IN_MEAN + k + 1]) / norm[NRM_IN_STD + k + 1]);
+            }
+            *reinterpret_cast<ushort2 *>(act[0] + r * AS + k) = h;
+            if (b < batch) *reinterpret_cast<ushort2 *>(a0 + (size_t)b * MLP_K1 + k) = h;
         }
-        *reinterpret_cast<ushort4 *>(at + l * astride + chunk_at(row0 + rq, c, MLP_H)) = h4;
         __syncthreads();
-        if (l == 2 && wave > 0) return;  // 16 outputs: one wave
-        const bf16x8 *w = l == 0 ? w2 : l == 1 ? w3 : w4;
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(out + col * AS + kq), w[0], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(out + col * AS + 32 + kq), w[1], acc, 0, 0, 0);
-    }
+        floatx4 acc =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(act[0] + col * AS + kq), w1, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (row0 + rq + r < batch) y[(size_t)(row0 + rq + r) * MLP_OUT + col] = acc[r] + bias4;
+        for (int l = 0; l < 3; ++l) {
+            unsigned short *out = act[(l + 1) & 1];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float zz = acc[r] + bias[l];
+                if (row0 + rq + r < batch) z[l * zstride + (size_t)(row0 + rq + r) * MLP_H + c] = zz;
+                out[(rq + r) * AS + c] = f2bf(silu(zz));
+            }
+            __syncthreads();
+            if (l == 2 && wave > 0) continue;  // 16 outputs: one wave
+            const bf16x8 *w = l == 0 ? w2 : l == 1 ? w3 : w4;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(out + col * AS + kq), w[0], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(out + col * AS + 32 + kq), w[1], acc, 0, 0, 0);
+        }
+        if (wave == 0)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (row0 + rq + r < batch) y[(size_t)(row0 + rq + r) * MLP_OUT + col] = acc[r] + bias4;
+    }
 }
 
 // Loss mean((y - t_norm)^2) over batch x q_out and its gradient dy (zero on padded outputs);
@@ -244,10 +250,12 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double *part, int n,
 
 // Backward pass, per row: dz4 = dy; da_l = bf16(dz_{l+1}) W_{l+1}; dz_l = da_l SiLU'(z_l).
 // dz [3][batch][64] (layers 1..3, FP32, for the bias gradients), and transposed by chunk in
-// bf16 gt (64 columns, layers 1..3, gstride apart) and g4t (16 columns, dy).
+// bf16 gt (64 columns, layers 1..3, tstride apart) and g4t (16 columns, dy), and the layer inputs
+// at (64 columns, layers 2..4, tstride apart) and a0t (32 columns).
 __global__ __launch_bounds__(256) void k_mlp_backward(const unsigned short *wb, const float *dy,
-                                                      const float *z, int batch, float *dz, unsigned short *gt,
-                                                      size_t gstride, unsigned short *g4t)
+                                                      const float *z, const unsigned short *a0, int batch, float *dz,
+                                                      unsigned short *gt, unsigned short *at, size_t tstride,
+                                                      unsigned short *g4t, unsigned short *a0t)
 {
     __shared__ __attribute__((aligned(16))) unsigned short act[2][TRAIN_ROWS * AS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -274,6 +282,22 @@ __global__ __launch_bounds__(256) void k_mlp_backward(const unsigned short *wb, 
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             zv[l][r] = rq + r < nvalid ? z[l * lstride + (size_t)(row0 + rq + r) * MLP_H + c] : 0.f;
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        ushort4 h4;
+        unsigned short *h = reinterpret_cast<unsigned short *>(&h4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[r] = f2bf(silu(zv[l][r]));
+        *reinterpret_cast<ushort4 *>(at + l * tstride + chunk_at(row0 + rq, c, MLP_H)) = h4;
+    }
+    if (threadIdx.x < MLP_K1 * TRAIN_ROWS / 4) {  // four rows of a column
+        const int k = threadIdx.x % MLP_K1, r0 = threadIdx.x / MLP_K1 * 4;
+        ushort4 h4;
+        unsigned short *h = reinterpret_cast<unsigned short *>(&h4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[r] = r0 + r < nvalid ? a0[(size_t)(row0 + r0 + r) * MLP_K1 + k] : (unsigned short)0;
+        *reinterpret_cast<ushort4 *>(a0t + chunk_at(row0 + r0, k, MLP_K1)) = h4;
+    }
     for (int j = threadIdx.x; j < TRAIN_ROWS * MLP_K1; j += 256) {
         const int r = j / MLP_K1, k = j % MLP_K1;
         const float v = (k < MLP_OUT && r < nvalid) ? dy[(size_t)(row0 + r) * MLP_OUT + k] : 0.f;
@@ -309,7 +333,7 @@ __global__ __launch_bounds__(256) void k_mlp_backward(const unsigned short *wb, 
             h[r] = f2bf(d);
             out[(rq + r) * AS + c] = h[r];
         }
-        *reinterpret_cast<ushort4 *>(gt + l * gstride + chunk_at(row0 + rq, c, MLP_H)) = h4;
+        *reinterpret_cast<ushort4 *>(gt + l * tstride + chunk_at(row0 + rq, c, MLP_H)) = h4;
         __syncthreads();
     }
 }

@@ -1829,10 +1829,20 @@ int elb_batch_destroy(elb_batch *b)
 namespace {
 
 struct MlpWs {
-    size_t a0t, at, g4t, gt, z, dz, part, lpart, total;
+    size_t a0, a0t, at, g4t, gt, z, dz, part, lpart, total;
     size_t lstride;  // elements from layer to layer of at and gt
     int nblk_w, nblk_l;
 };
+
+// Tiles of 16 rows per block of the training forward: as many as leave 1024 blocks (four per CU),
+// up to 8, so that the weights are read from L2 once for all of them.  us with 1 / 2 / 4 / 8 tiles:
+// 16384 rows 8.9 / 8.8 / 10.8 / 17, 32768 14.8 / 12.1 / 13.1 / 18, 65536 23 / 20 / 18 / 23,
+// 131072 40 / 31 / 30 / 28, 4194304 1507 / 1375 / 1289 / 1241 (16: 1242).
+int forward_tiles(int64_t batch)
+{
+    const int64_t t = batch / TRAIN_ROWS / 1024;
+    return t >= 8 ? 8 : t >= 4 ? 4 : t >= 2 ? 2 : 1;
+}
 
 MlpWs mlp_ws(int64_t batch)
 {
@@ -1844,6 +1854,7 @@ MlpWs mlp_ws(int64_t batch)
     // transposed bf16 operands of the weight gradients, in whole chunks
     const size_t rows = (size_t)w.nblk_w * WGRAD_ROWS;
     w.lstride = rows * MLP_H;
+    w.a0 = take(sizeof(unsigned short) * MLP_K1 * (size_t)batch);
     w.a0t = take(sizeof(unsigned short) * MLP_K1 * rows);
     w.at = take(sizeof(unsigned short) * 3 * w.lstride);
     w.g4t = take(sizeof(unsigned short) * MLP_OUT * rows);
@@ -1998,10 +2009,10 @@ int elb_mlp_forward(const float *params, const uint16_t *wb, const float *norm, 
     if (!params || !wb || !norm || !x || !y || !ws || batch < 1 || batch > kMaxBatch) return ELB_EINVAL;
     MlpWs w = mlp_ws(batch);
     char *base = (char *)ws;
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((batch + TRAIN_ROWS - 1) / TRAIN_ROWS)), dim3(256), 0,
+    const int tiles = forward_tiles(batch), rows = tiles * TRAIN_ROWS;
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((batch + rows - 1) / rows)), dim3(256), 0,
                        (hipStream_t)stream, (const unsigned short *)wb, params, norm, x, (const int *)index,
-                       (int)batch, y, (unsigned short *)(base + w.a0t), (unsigned short *)(base + w.at), w.lstride,
-                       (float *)(base + w.z));
+                       (int)batch, tiles, y, (unsigned short *)(base + w.a0), (float *)(base + w.z));
     return hipGetLastError() == hipSuccess ? ELB_OK : ELB_EHIP;
 }
 
@@ -2061,7 +2072,8 @@ int elb_mlp_backward(const uint16_t *wb, const float *dy, int64_t batch, float *
     float *dz = (float *)(base + w.dz);
     unsigned short *gt = (unsigned short *)(base + w.gt), *g4t = (unsigned short *)(base + w.g4t);
     hipLaunchKernelGGL(k_mlp_backward, dim3((unsigned)((batch + TRAIN_ROWS - 1) / TRAIN_ROWS)), dim3(256), 0, st,
-                       (const unsigned short *)wb, dy, z, (int)batch, dz, gt, w.lstride, g4t);
+                       (const unsigned short *)wb, dy, z, (const unsigned short *)(base + w.a0), (int)batch, dz, gt,
+                       (unsigned short *)(base + w.at), w.lstride, g4t, (unsigned short *)(base + w.a0t));
     hipLaunchKernelGGL(k_mlp_wgrad, dim3(w.nblk_w, 4), dim3(WGRAD_THREADS), 0, st, dy, (const float *)dz,
                        (const unsigned short *)gt, w.lstride, (const unsigned short *)g4t,
                        (const unsigned short *)(base + w.a0t), (const unsigned short *)(base + w.at), w.lstride, (int)batch,
