@@ -47,12 +47,16 @@ void launch_stage(const void *args, int blocks, size_t shm, hipStream_t st)
 // mixed 41.1 / 42.5).
 // Every tile keeps the strip count's split of a wave into phi or theta items and the lane
 // count of the coefficient recurrence (Geometry::RG) of the large one, so all give the same
-// bits.  X3: also compiled with the learned closure inside (whole 16-cell tiles, Q <= 16).
+// bits.  X3: also compiled with the learned closure inside (whole 16-cell tiles, Q <= 16), which
+// has a limit of its own: the closure's blocks are fewer per compute unit, and one more round of
+// them costs more than the short strips save (Q = 12, us on 4-cell / 8-cell strips: FP64 1032 blocks
+// 22.0 / 20.8; mixed 1125 17.9 / 20.4, 1282 23.8 / 20.6).
 #if ELB_STAGE_MODE == 0
+#define CL12 1024
 #define ELB_SMALL_TILES(X2, X3) \
-    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024) X2(8, 8, 4, ANY) \
-    X2(12, 8, 1, 256) X3(12, 8, 2, 512) X3(12, 8, 4, 1300) \
-    X2(16, 8, 1, 256) X3(16, 8, 2, 512) X3(16, 8, 4, 1024) \
+    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024, 1024) X2(8, 8, 4, ANY) \
+    X2(12, 8, 1, 256) X3(12, 8, 2, 512, 512) X3(12, 8, 4, 1300, CL12) \
+    X2(16, 8, 1, 256) X3(16, 8, 2, 512, 512) X3(16, 8, 4, 1024, 1024) \
     X2(20, 8, 1, 256) X2(20, 8, 2, 512) \
     X2(24, 8, 1, 256) X2(24, 8, 2, 512) \
     X2(32, 4, 2, 256) X2(32, 4, 4, 512) \
@@ -62,10 +66,11 @@ void launch_stage(const void *args, int blocks, size_t shm, hipStream_t st)
     X2(96, 2, 2, 256) X2(96, 2, 4, 256) \
     X2(200, 2, 2, 128) X2(200, 2, 4, 256)
 #else
+#define CL12 1280
 #define ELB_SMALL_TILES(X2, X3) \
-    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024) X2(8, 8, 4, ANY) \
-    X2(12, 8, 1, 256) X3(12, 8, 2, 512) X3(12, 8, 4, 1300) \
-    X3(16, 8, 2, 512) X3(16, 8, 4, 1024) \
+    X2(8, 8, 1, 1024) X3(8, 8, 2, 1024, 1024) X2(8, 8, 4, ANY) \
+    X2(12, 8, 1, 256) X3(12, 8, 2, 512, 512) X3(12, 8, 4, 1300, CL12) \
+    X3(16, 8, 2, 512, 512) X3(16, 8, 4, 1024, 1024) \
     X2(20, 8, 1, 256) X2(20, 8, 2, 256) X2(20, 8, 4, 1024) \
     X2(24, 16, 1, 256) X2(24, 16, 2, 256) X2(24, 16, 4, 512) \
     X2(32, 8, 1, 256) X2(32, 8, 2, 256) X2(32, 8, 4, 512) \
@@ -87,10 +92,10 @@ typedef float Real;
      &launch_stage<Real, QV, SV, LV, RET, CL>},
 // chi_SET and chi_RET-FM; and for Q <= 16 with the learned closure inside
 #define ELB_S2(QV, SV, LV, CAP) ELB_ST(QV, SV, LV, CAP, false, false) ELB_ST(QV, SV, LV, CAP, true, false)
-#define ELB_S3(QV, SV, LV, CAP) ELB_S2(QV, SV, LV, CAP) ELB_ST(QV, SV, LV, CAP, false, true)
+#define ELB_S3(QV, SV, LV, CAP, CLCAP) ELB_S2(QV, SV, LV, CAP) ELB_ST(QV, SV, LV, CLCAP, false, true)
 // the large-problem tile
 #define ELB_L2(QV) ELB_S2(QV, (Shape<Real, QV>::S), (Shape<Real, QV>::L), INT_MAX)
-#define ELB_L3(QV) ELB_S3(QV, (Shape<Real, QV>::S), (Shape<Real, QV>::L), INT_MAX)
+#define ELB_L3(QV) ELB_S3(QV, (Shape<Real, QV>::S), (Shape<Real, QV>::L), INT_MAX, INT_MAX)
 
 const StageKernel kStage[] = {
     ELB_SMALL_TILES(ELB_S2, ELB_S3)
@@ -118,6 +123,7 @@ void launch_batch(const BatchStage &bs, int grid, size_t shm, hipStream_t st)
 #define ELB_BK(QV, SV, LV) ELB_BKX(QV, SV, LV, INT_MAX, false)
 #define ELB_BKR(QV, SV, LV) ELB_BKX(QV, SV, LV, INT_MAX, true)
 #define ELB_BK2(QV, SV, LV, CAP) ELB_BKX(QV, SV, LV, CAP, false) ELB_BKX(QV, SV, LV, CAP, true)
+#define ELB_BK3(QV, SV, LV, CAP, CLCAP) ELB_BK2(QV, SV, LV, CAP)
 
 // Variant 0 of every Q is the single-problem shape; the FP32 modes also have the 16-cell strips
 // in blocks of up to 384 threads, between which the tuner chooses.  chi_RET-FM: the
@@ -144,7 +150,7 @@ const BatchKernel kBatch[] = {
     ELB_BKR(24, 16, 8) ELB_BKR(32, 8, 8) ELB_BKR(40, 8, 8) ELB_BKR(48, 8, 8)
     ELB_BKR(64, 6, 8) ELB_BKR(96, 4, 8) ELB_BKR(200, 2, 8)
 #endif
-    ELB_SMALL_TILES(ELB_BK2, ELB_BK2)
+    ELB_SMALL_TILES(ELB_BK2, ELB_BK3)
 };
 #endif
 
