@@ -132,6 +132,11 @@ struct Geometry {
     // nothing (FP64 Q = 64, 128 cells, 4 x 4 held to six waves per SIMD: spills, 9.6 us).
     static constexpr int WD = Shape<R, Q>::S * Shape<R, Q>::L;  // cells of the large-problem tile
     static constexpr int WV = W < WD ? 1 : (NT == 768 || NT == 640 || NT == 512) ? 6 : NT == 384 ? 5 : 1;
+    // The batched form of the large FP64 tiles that have no such constraint is held to 128 registers,
+    // within which the single form stays by itself.  Left alone it took 132 at Q = 16, 32 and 64 and
+    // lost the fourth wave per SIMD: 64 problems of 4000 cells 58.5, 121 and 252 us per stage; held
+    // 51.6, 104 and 214.
+    static constexpr int WVB = WV == 1 && W == WD && sizeof(R) == 8 ? 4 : WV;
     // with the learned closure inside (Q <= 16): at least two blocks per CU, and four waves
     // per SIMD for blocks of up to four waves (four or more blocks per CU)
     static constexpr int WVCL0 = NT <= 256 ? 4 : (2 * NT / 64 + 3) / 4;
@@ -1646,7 +1651,7 @@ struct BatchStage {
 
 template <typename R, int Q, int S_, int L_, int MODE, bool RET>
 __global__ __launch_bounds__((Geometry<R, Q, S_, L_>::NT))
-__attribute__((amdgpu_waves_per_eu(Geometry<R, Q, S_, L_>::WV))) void k_stage_batch(BatchStage bs)
+__attribute__((amdgpu_waves_per_eu(Geometry<R, Q, S_, L_>::WVB))) void k_stage_batch(BatchStage bs)
 {
     {
         const int item = blockIdx.x;  // one (instance, tile) item per block
