@@ -30,7 +30,9 @@ TIMED_RUNS = 5  # the reported time is the median of this many timed runs of K s
 # rocprofv3 summary of the stage kernel on the default workload: FETCH_SIZE and WRITE_SIZE
 # per launch, scaled by a plain device copy, stamped with the hash of the kernel source
 TRAFFIC_PROFILE = os.path.join(REPO, "profiles", "k_stage_shock_tube_nx65536_q96_fp32_mixed.md")
-KERNEL_SOURCE = os.path.join(REPO, "paper_2211_16933_amd", "csrc", "elb_kernels.h")
+# the kernel, and the table of the tile that a problem takes
+KERNEL_SOURCES = [os.path.join(REPO, "paper_2211_16933_amd", "csrc", f)
+                  for f in ("elb_kernels.h", "stage_kernels.hip")]
 
 PRECISIONS = {"fp64": 0, "fp32": 1, "fp32_mixed": 2}
 DTYPES = {"fp64": "f64", "fp32": "f32", "fp32_mixed": "f32+f64"}
@@ -58,8 +60,11 @@ def stage_flop_per_pair(q):
 
 def kernel_source_hash():
     import hashlib
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic():
