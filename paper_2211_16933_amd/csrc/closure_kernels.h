@@ -66,11 +66,9 @@ __device__ inline void mlp_stage_weights(MlpSmem &s, const unsigned short *wb, c
 }
 
 // Forward pass of the 16 rows whose bf16 inputs are in s.act[wave][0] (columns 0..31).
-// Pre-activations of the hidden layers go to z (row stride 64, 3 layers of zstride floats)
-// when z != NULL, for rows < nvalid.  Output y[16][16] (FP32) in the D layout of acc4.
-// Every wave of the block must call this (it synchronises the block between layers).
-__device__ inline void mlp_forward_rows(MlpSmem &s, int wave, int lane, float *z, size_t zstride,
-                                        int nvalid, floatx4 &acc4)
+// Output y[16][16] (FP32) in the D layout of acc4.  Every wave of the block must call this (it
+// synchronises the block between layers).
+__device__ inline void mlp_forward_rows(MlpSmem &s, int wave, int lane, floatx4 &acc4)
 {
     unsigned short *a0 = s.act[wave][0], *a1 = s.act[wave][1];
     floatx4 acc[4];
@@ -82,9 +80,7 @@ __device__ inline void mlp_forward_rows(MlpSmem &s, int wave, int lane, float *z
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = rq + r, c = t * 16 + col;
-            float zz = acc[t][r] + s.bias[c];
-            if (z && row < nvalid) z[(size_t)row * MLP_H + c] = zz;
-            a1[row * AS + c] = f2bf(silu(zz));
+            a1[row * AS + c] = f2bf(silu(acc[t][r] + s.bias[c]));
         }
     __syncthreads();
     // layers 2 and 3: K = 64
@@ -99,9 +95,7 @@ __device__ inline void mlp_forward_rows(MlpSmem &s, int wave, int lane, float *z
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = rq + r, c = t * 16 + col;
-                float zz = acc[t][r] + s.bias[(l + 1) * MLP_H + c];
-                if (z && row < nvalid) z[(l + 1) * zstride + (size_t)row * MLP_H + c] = zz;
-                aout[row * AS + c] = f2bf(silu(zz));
+                aout[row * AS + c] = f2bf(silu(acc[t][r] + s.bias[(l + 1) * MLP_H + c]));
             }
         __syncthreads();
     }
@@ -581,7 +575,7 @@ __global__ __launch_bounds__(256) void k_closure_apply(const unsigned short *wb,
     }
     __syncthreads();
     floatx4 o;
-    mlp_forward_rows(s, wave, lane, nullptr, 0, 16, o);
+    mlp_forward_rows(s, wave, lane, o);
     {
         const int col = lane & 15, rq = 4 * (lane >> 4);
 #pragma unroll

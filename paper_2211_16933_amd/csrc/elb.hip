@@ -395,7 +395,7 @@ const StageKernel *pick_stage(const elb_params *p, int ret, int closure)
         if (k->q == p->q && k->ret == ret && k->closure == closure && (p->nx + k->cells() - 1) / k->cells() <= k->cap)
             return k;
     }
-    return nullptr;  // not reached: the large-problem tile takes any number of blocks
+    return nullptr;  // not reached: the last tile of a Q takes any number of blocks
 }
 
 template <typename R>
@@ -1285,8 +1285,8 @@ struct elb_batch {
     std::vector<elb_ctx *> ctx;
     std::vector<BatchGroup> groups;
     hipStream_t cap_stream = nullptr;  // private stream used only to capture the graph
-    // capture only: side streams and events that fork the Q groups of a stage into parallel
-    // branches of the graph and join them before the next stage
+    // capture only: side streams and events that fork the Q groups into parallel branches of the
+    // graph, each through all steps of the chunk, and join them at its end
     std::vector<hipStream_t> side;
     hipEvent_t ev_fork = nullptr;
     std::vector<hipEvent_t> ev_join;

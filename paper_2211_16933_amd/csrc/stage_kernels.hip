@@ -107,7 +107,11 @@ const StageKernel kStage[] = {
     ELB_ST(8, 8, 4, 1300, false, true) ELB_ST(8, 8, 8, INT_MAX, false, true)
 #endif
     ELB_L3(12) ELB_L3(16) ELB_L2(20) ELB_L2(24) ELB_L2(32)
-    ELB_L2(40) ELB_L2(48) ELB_L2(64) ELB_L2(96) ELB_L2(200)
+    ELB_L2(40) ELB_L2(48)
+#if ELB_STAGE_MODE != 1  // plain FP32 takes its 4 x 8 tile at any size
+    ELB_L2(64)
+#endif
+    ELB_L2(96) ELB_L2(200)
 };
 
 #if ELB_STAGE_MODE != 3
