@@ -377,12 +377,20 @@ StageTable stage_table(int precision, int fixup)
     }
 }
 
-// bytes a context uploads to set a state, and downloads as moments
+// bytes a context uploads to set a state, and downloads as moments; with the learned closure also the
+// projection table of a lift or a sample, and a sample that is small (a direct copy of up to 16 KB
+// costs 7 us more than one through the buffer; larger ones the same)
 size_t stage_bytes(const elb_params *p)
 {
     const size_t nx = p->nx;
-    return std::max(align256(sizeof(double) * (padded_q(p->q) + 3 * (size_t)p->q + 3 * nx)),
-                    align256(sizeof(double) * (5 * nx + 2)));
+    size_t n = std::max(align256(sizeof(double) * (padded_q(p->q) + 3 * (size_t)p->q + 3 * nx)),
+                        align256(sizeof(double) * (5 * nx + 2)));
+    if (p->closure) {
+        n = std::max(n, align256(sizeof(double) * MAXQP * MLP_OUT));
+        const size_t sample = align256(sizeof(float) * MLP_IN * nx) + align256(sizeof(float) * p->q * nx);
+        if (sample <= (size_t(1) << 16) - STAGE_HEAD) n = std::max(n, sample);
+    }
+    return n;
 }
 
 // The stage kernel of a problem: its first compiled tile whose number of blocks is at most the
@@ -553,15 +561,32 @@ void make_reference(elb_ctx *c, double n_r, double u_r, double T_r, double *tabl
     }
 }
 
+// A copy between the pinned buffer and the workspace.  Up to 16 KB the runtime copies with a kernel,
+// about 3 us in the stream, beyond with a DMA engine, 11 us and more: up to 32 KB go in two pieces
+// (two reads of 24 and 16 KB, with the kernel before them and the wait, 27 and 37 us; of 48 and 32 KB in
+// pieces 34 and whole 38 us, 96 and 64 KB 74 and 42).
+hipError_t copy_pinned(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t st)
+{
+    constexpr size_t PIECE = size_t(1) << 14;
+    const size_t step = bytes <= 2 * PIECE ? PIECE : bytes;
+    hipError_t e = hipSuccess;
+    for (size_t at = 0; at < bytes && e == hipSuccess; at += step)
+        e = hipMemcpyAsync((char *)dst + at, (const char *)src + at, std::min(step, bytes - at), kind, st);
+    return e;
+}
+
 // Copies `bytes` from the host to the workspace in stream order: through the pinned buffer when it
 // holds them, else from the caller's memory.  The source may change after the return; with
 // wait = false only after the stream has been waited for.
 int upload(elb_ctx *c, size_t off, const void *src, size_t bytes, bool wait = true)
 {
     char *st = c->stage->take(bytes, c->stream);
-    if (st) std::memcpy(st, src, bytes);
-    hipError_t e = hipMemcpyAsync(c->dev<char>(off), st ? st : src, bytes, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess && !st && wait) e = hipStreamSynchronize(c->stream);
+    if (st) {
+        std::memcpy(st, src, bytes);
+        return hip_check(c, copy_pinned(c->dev<char>(off), st, bytes, hipMemcpyHostToDevice, c->stream), "copy to the device");
+    }
+    hipError_t e = hipMemcpyAsync(c->dev<char>(off), src, bytes, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess && wait) e = hipStreamSynchronize(c->stream);
     return hip_check(c, e, "copy to the device");
 }
 
@@ -667,7 +692,8 @@ int download(elb_ctx *c, std::initializer_list<Piece> pieces)
         char *&at = st[i++];
         if (!p.dst || e != hipSuccess) continue;
         if (c->stage->used + align256(p.bytes) <= c->stage->cap()) at = c->stage->take(p.bytes, c->stream);
-        e = hipMemcpyAsync(at ? at : p.dst, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream);
+        e = at ? copy_pinned(at, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream)
+               : hipMemcpyAsync(p.dst, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_check(c, e, "copy to the host");
