@@ -118,8 +118,9 @@ int elb_supported_q(int32_t *out, int32_t cap);
 
 /* Gauss-Hermite nodes (roots of He_q, ascending) and weights normalised to sum 1, i.e.
  * for the weight exp(-p^2/2)/sqrt(2 pi) (Sec. II.D).  Host function, pure; q in [1, 256].
- * Nodes come from the eigenvalues of the Jacobi matrix, refined by Newton's method; the
- * weights are the Christoffel numbers 1 / sum_{l<q} He_l(p_k)^2 / l!. */
+ * Nodes of the compiled counts come from a table, others from the sign counts of the Jacobi
+ * matrix's pivots, refined by Newton's method; the weights are the Christoffel numbers
+ * 1 / sum_{l<q} He_l(p_k)^2 / l!. */
 int elb_quadrature(int32_t q, double *nodes, double *weights);
 
 /* Device workspace needed by a context with these parameters, in bytes (< 0: invalid). */

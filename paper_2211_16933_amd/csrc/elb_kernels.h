@@ -107,8 +107,11 @@ ELB_SHAPE(double, 200, 2, 8)
 #undef ELB_SHAPE
 
 // Whether the projection onto Q nodes splits into even and odd orders (also the layout of the
-// table Bt): whole 16-wide halves, or in FP64 padded ones of at most 3/5 of the full product
-// (and Q > 64: smaller products are not what a block waits for).
+// table Bt): whole 16-wide halves, or in FP64 padded ones of at most 3/5 of the full product.  Of
+// the compiled Q, 20, 24 and 200 meet that; only 200 takes it.  Smaller products are not what a
+// block waits for, and where the blocks fill the chip the split is the slower form: us per launch
+// whole / split, at 128 and 65536 cells, Q = 20 5.8 / 5.6 and 26.3 / 27.1, Q = 24 5.7 / 5.6 and
+// 27.8 / 28.6; Q = 200, 160 cells, 18.8 / 15.6.
 constexpr bool split_projection(int Q, int elem)
 {
     const int h = Q / 2, hp = (h + 15) / 16 * 16, qp = (Q + 15) / 16 * 16;
@@ -199,7 +202,8 @@ __device__ inline double inv_tau(double mu_ref, double n, double T, double chi, 
 
 // reciprocal: FP32 the hardware's (1 ulp); FP64 the refinement of the hardware's reciprocal
 // that IEEE division makes, without the scaling and fix-up instructions around it (7
-// instructions, not 11): the same bits wherever x and 1 / x are normal
+// instructions, not 11): the same bits wherever x and 1 / x are normal.  Where 1 / x overflows or x
+// is infinite it gives NaN, where the division gives infinity or zero
 __device__ inline double recip(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
@@ -534,6 +538,9 @@ struct WenoMarch {
             // 1e50: a weight 1e-100 below the largest is zero at FP64 precision, and the
             // products stay below 1e200.  If some indicator vanishes, the weights are
             // delta_q on the zero set and 0 elsewhere (Table III limits).
+            // An indicator so small (below 5.6e-309) or infinite that the reciprocal is NaN has its
+            // products dropped by fmin, which returns its other argument: the clamp, as for the
+            // infinity that a division gives.
             // Waves without a vanishing indicator skip the selects (a branch of the wave: 8 of
             // some 70 instructions per interface).
             const R mn = fmin(s1, fmin(s2, s3));
