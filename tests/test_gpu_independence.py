@@ -73,3 +73,47 @@ def test_more_contexts_than_pinned_buffers():
             s.set_state_dist(*want[5:7])
             s.step(1)
             s.close()
+
+
+def test_contexts_of_several_threads():
+    """Eight threads, each with a stream of its own, make, run and close contexts and batches at the
+    same time: buffers that pass between them must not be shared."""
+    import threading
+    import torch
+    import paper_2211_16933_amd as elb
+    say("case contexts of several threads")
+    sizes = [64, 300, 1000, 2500, 4000, 6500, 7000, 12000]
+    want = {}
+    for nx in sizes:
+        _, s = _solver(nx, 12)
+        s.step(3)
+        want[nx] = s.moments() + s.dist()
+        s.close()
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(k):
+        try:
+            stream = torch.cuda.Stream()
+            for i in range(12):
+                nx = sizes[(k + i) % len(sizes)]
+                w, s = _solver(nx, 12, stream)
+                b = elb.BatchSolver([elb.params_from_workload(w)], stream=stream)
+                b.set_state_moments(0, w["n"], w["u"], w["T"])
+                b.set_graph(False)
+                s.step(3)
+                b.step(3)
+                for got in (s.moments() + s.dist(), b.moments(0) + b.dist(0)):
+                    if not all(np.array_equal(x, y) for x, y in zip(got, want[nx])):
+                        wrong.append((k, i, nx))
+                s.close()
+                b.close()
+        except Exception as e:  # noqa: BLE001
+            wrong.append((k, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
