@@ -138,8 +138,8 @@ struct Geometry {
     // The batched form of the large FP64 tiles that have no such constraint is held to 128 registers,
     // within which the single form stays by itself.  Left alone it took 132 at Q = 16, 32 and 64 and
     // lost the fourth wave per SIMD: 64 problems of 4000 cells 58.5, 121 and 252 us per stage; held
-    // 51.6, 104 and 214.
-    static constexpr int WVB = WV == 1 && W == WD && sizeof(R) == 8 ? 4 : WV;
+    // 51.6, 104 and 214.  (Q = 8: LDS allows two.)
+    static constexpr int WVB = WV == 1 && W == WD && sizeof(R) == 8 && Q > 8 ? 4 : WV;
     // with the learned closure inside (Q <= 16): at least two blocks per CU, and four waves
     // per SIMD for blocks of up to four waves (four or more blocks per CU)
     static constexpr int WVCL0 = NT <= 256 ? 4 : (2 * NT / 64 + 3) / 4;
