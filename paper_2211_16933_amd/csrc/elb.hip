@@ -138,10 +138,12 @@ constexpr size_t STAGE_MIN = size_t(1) << 14, STAGE_MAX = size_t(1) << 18;
 // largest buffers in use at once); contexts beyond them copy from pageable memory.  The buffers
 // that wait for reuse stay until the process ends.
 constexpr size_t PINNED_MAX = size_t(1) << 24;
+// Before the bytes that are taken piece by piece lies the failure flag that a kernel leaves for the host.
+constexpr size_t STAGE_HEAD = 256;
 
 struct PinnedBuffer {
     char *p = nullptr;
-    size_t cap = 0;
+    size_t cap = 0;  // without the head
     int device = -1;
 };
 
@@ -165,14 +167,14 @@ public:
             return b;
         }
         if (taken_ + cap > PINNED_MAX) return b;
-        if (hipHostMalloc(reinterpret_cast<void **>(&b.p), cap, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(reinterpret_cast<void **>(&b.p), STAGE_HEAD + cap, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             b.p = nullptr;
             return b;
         }
         b.cap = cap;
         taken_ += cap;
-        std::memset(b.p, 0, cap);  // first touch
+        std::memset(b.p, 0, STAGE_HEAD + cap);  // first touch
         return b;
     }
     // no enqueued copy or kernel may still use it
@@ -196,23 +198,19 @@ PinnedPool &pinned_pool()
     return *pool;
 }
 
-// The first bytes hold the failure flag that a kernel leaves for the host, the rest is taken piece
-// by piece.
-constexpr size_t STAGE_HEAD = 256;
-
 struct HostStage {
     PinnedBuffer buf;
     size_t used = 0;
     // the stream of its copies has been waited for (buf.p = NULL: without success, so that the
     // buffer must not be used again)
     ~HostStage() { if (buf.p) pinned_pool().give(buf); }
-    size_t cap() const { return buf.p ? buf.cap - STAGE_HEAD : 0; }
+    size_t cap() const { return buf.p ? buf.cap : 0; }
     int *flag() const { return reinterpret_cast<int *>(buf.p); }
     // a buffer of `n` bytes within the limits above (none: everything is copied directly)
     void reserve(size_t n)
     {
         size_t want = STAGE_MIN;
-        while (want < n + STAGE_HEAD && want < STAGE_MAX) want *= 2;
+        while (want < n && want < STAGE_MAX) want *= 2;
         buf = pinned_pool().take(want);
     }
     // n bytes that no enqueued copy uses; NULL: more than the buffer holds
@@ -388,7 +386,7 @@ size_t stage_bytes(const elb_params *p)
     if (p->closure) {
         n = std::max(n, align256(sizeof(double) * MAXQP * MLP_OUT));
         const size_t sample = align256(sizeof(float) * MLP_IN * nx) + align256(sizeof(float) * p->q * nx);
-        if (sample <= (size_t(1) << 16) - STAGE_HEAD) n = std::max(n, sample);
+        if (sample <= size_t(1) << 16) n = std::max(n, sample);
     }
     return n;
 }
@@ -671,7 +669,10 @@ int run_moments(elb_ctx *c, double *o, bool conserved = false)
 }
 
 // Copies pieces of the workspace to the host (dst = NULL: not wanted) with one wait for the stream:
-// through the pinned buffer as far as it holds them, the others directly.
+// through the pinned buffer as far as it holds them, the others directly, and so those of more than
+// 64 KB, which gain nothing from it.
+constexpr size_t PINNED_PIECE = size_t(1) << 16;
+
 struct Piece {
     void *dst;
     size_t off, bytes;
@@ -681,7 +682,7 @@ int download(elb_ctx *c, std::initializer_list<Piece> pieces)
 {
     char *st[6] = {};
     size_t all = 0;
-    for (const Piece &p : pieces) all += align256(p.dst ? p.bytes : 0);
+    for (const Piece &p : pieces) all += align256(p.dst && p.bytes <= PINNED_PIECE ? p.bytes : 0);
     hipError_t e = hipSuccess;
     if (c->stage->used && c->stage->used + all > c->stage->cap()) {
         e = hipStreamSynchronize(c->stream);
@@ -691,7 +692,7 @@ int download(elb_ctx *c, std::initializer_list<Piece> pieces)
     for (const Piece &p : pieces) {
         char *&at = st[i++];
         if (!p.dst || e != hipSuccess) continue;
-        if (c->stage->used + align256(p.bytes) <= c->stage->cap()) at = c->stage->take(p.bytes, c->stream);
+        if (p.bytes <= PINNED_PIECE && c->stage->used + align256(p.bytes) <= c->stage->cap()) at = c->stage->take(p.bytes, c->stream);
         e = at ? copy_pinned(at, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream)
                : hipMemcpyAsync(p.dst, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream);
     }

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(PLANE_THREADS) void k_dist_pack(const double *phi, 
 constexpr int MOM_LANES = 16, MOM_CELLS = 1 << 24;
 // Cells whose moments go straight to pinned memory.  us per readout, straight / by one copy: Q = 8
 // 512 cells 15 / 24, 2048 17 / 26, 6144 24 / 33; Q = 200 2048 21 / 31, 6144 30 / 42.  The line is no
-// crossing: to where the buffer ends (6546 cells) the copy is never the faster one.
+// crossing: to where the buffer ends (6553 cells) the copy is never the faster one.
 constexpr size_t MOM_DIRECT = 2048;
 
 __device__ inline double sum16(double v)

@@ -119,11 +119,11 @@ def test_no_state_is_set_under_capture(nx):
         assert all(np.array_equal(x, y) for x, y in zip(s.dist(), f.dist()))
 
 
-@pytest.mark.parametrize("nx,q", [(402, 40), (403, 8), (404, 8), (504, 40), (6546, 8), (6547, 8), (6547, 40), (33000, 8)])
+@pytest.mark.parametrize("nx,q", [(408, 40), (409, 8), (410, 8), (512, 40), (6552, 8), (6553, 8), (6554, 8), (6554, 40), (33000, 8)])
 @pytest.mark.parametrize("precision", [FP64, FP32])
 def test_copies_at_the_edges_of_the_pinned_buffer(nx, q, precision):
-    """Readouts and restores whose pieces fill the buffer (16 KB to 256 KB less its 256-byte head) to
-    the last value, one cell more or less, and whose pieces go part through it, part directly."""
+    """Readouts and restores whose pieces fill the buffer (16 to 256 KB) to the last value, one cell more
+    or less, and whose pieces go part through it, part directly."""
     import paper_2211_16933_amd as elb
     say(f"case copies nx={nx} q={q} precision={precision}")
     w, s = _tube(nx=nx, q=q, precision=precision)
