@@ -375,20 +375,16 @@ StageTable stage_table(int precision, int fixup)
     }
 }
 
-// bytes a context uploads to set a state, and downloads as moments; with the learned closure also the
-// projection table of a lift or a sample, and a sample that is small (a direct copy of up to 16 KB
-// costs 7 us more than one through the buffer; larger ones the same)
+// bytes a context uploads to set a state, and downloads as moments; with the learned closure also a
+// projection table and a sample, which go through the buffer one after the other
 size_t stage_bytes(const elb_params *p)
 {
     const size_t nx = p->nx;
-    size_t n = std::max(align256(sizeof(double) * (padded_q(p->q) + 3 * (size_t)p->q + 3 * nx)),
-                        align256(sizeof(double) * (5 * nx + 2)));
-    if (p->closure) {
-        n = std::max(n, align256(sizeof(double) * MAXQP * MLP_OUT));
-        const size_t sample = align256(sizeof(float) * MLP_IN * nx) + align256(sizeof(float) * p->q * nx);
-        if (sample <= size_t(1) << 16) n = std::max(n, sample);
-    }
-    return n;
+    const size_t n = std::max(align256(sizeof(double) * (padded_q(p->q) + 3 * (size_t)p->q + 3 * nx)),
+                              align256(sizeof(double) * (5 * nx + 2)));
+    if (!p->closure) return n;
+    return std::max(n, align256(sizeof(double) * MAXQP * MLP_OUT) + align256(sizeof(float) * MLP_IN * nx) +
+                           align256(sizeof(float) * p->q * nx));
 }
 
 // The stage kernel of a problem: its first compiled tile whose number of blocks is at most the
@@ -563,10 +559,11 @@ void make_reference(elb_ctx *c, double n_r, double u_r, double T_r, double *tabl
 // about 3 us in the stream, beyond with a DMA engine, 11 us and more: up to 32 KB go in two pieces
 // (two reads of 24 and 16 KB, with the kernel before them and the wait, 27 and 37 us; of 48 and 32 KB in
 // pieces 34 and whole 38 us, 96 and 64 KB 74 and 42).
+constexpr size_t PINNED_SMALL = size_t(1) << 15;
+
 hipError_t copy_pinned(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t st)
 {
-    constexpr size_t PIECE = size_t(1) << 14;
-    const size_t step = bytes <= 2 * PIECE ? PIECE : bytes;
+    const size_t step = bytes <= PINNED_SMALL ? PINNED_SMALL / 2 : bytes;
     hipError_t e = hipSuccess;
     for (size_t at = 0; at < bytes && e == hipSuccess; at += step)
         e = hipMemcpyAsync((char *)dst + at, (const char *)src + at, std::min(step, bytes - at), kind, st);
@@ -668,11 +665,11 @@ int run_moments(elb_ctx *c, double *o, bool conserved = false)
     return hip_check(c, hipGetLastError(), "moments kernel launch");
 }
 
-// Copies pieces of the workspace to the host (dst = NULL: not wanted) with one wait for the stream:
-// through the pinned buffer as far as it holds them, the others directly, and so those of more than
-// 64 KB, which gain nothing from it.
-constexpr size_t PINNED_PIECE = size_t(1) << 16;
-
+// Copies pieces of the workspace to the host (dst = NULL: not wanted) and waits for the stream:
+// small ones (PINNED_SMALL) through the pinned buffer, as many as it holds with one wait; larger
+// ones that it holds through it one by one; others directly.  Larger ones with one wait, or
+// through the buffer and directly by turns, were slower: moments of 16384 cells 95 us one by one,
+// 102 with two of the five in flight; samples of 2000 cells (96 and 64 KB) 99 and 123.
 struct Piece {
     void *dst;
     size_t off, bytes;
@@ -681,30 +678,32 @@ struct Piece {
 int download(elb_ctx *c, std::initializer_list<Piece> pieces)
 {
     char *st[6] = {};
-    size_t all = 0;
-    for (const Piece &p : pieces) all += align256(p.dst && p.bytes <= PINNED_PIECE ? p.bytes : 0);
     hipError_t e = hipSuccess;
-    if (c->stage->used && c->stage->used + all > c->stage->cap()) {
-        e = hipStreamSynchronize(c->stream);
-        c->stage->used = 0;
-    }
+    auto wait = [&]() {
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        int i = 0;
+        for (const Piece &p : pieces) {
+            if (st[i] && e == hipSuccess) std::memcpy(p.dst, st[i], p.bytes);
+            st[i++] = nullptr;
+        }
+        c->stage->used = 0;  // the stream has been waited for
+    };
     int i = 0;
+    bool pending = false;
     for (const Piece &p : pieces) {
         char *&at = st[i++];
         if (!p.dst || e != hipSuccess) continue;
-        if (p.bytes <= PINNED_PIECE && c->stage->used + align256(p.bytes) <= c->stage->cap()) at = c->stage->take(p.bytes, c->stream);
-        e = at ? copy_pinned(at, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream)
-               : hipMemcpyAsync(p.dst, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream);
+        const size_t n = align256(p.bytes);
+        if (n <= c->stage->cap() && c->stage->used + n > c->stage->cap()) wait();
+        if (n <= c->stage->cap()) at = c->stage->take(n, c->stream);
+        if (e == hipSuccess)
+            e = at ? copy_pinned(at, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream)
+                   : hipMemcpyAsync(p.dst, c->dev<char>(p.off), p.bytes, hipMemcpyDeviceToHost, c->stream);
+        pending = !(at && p.bytes > PINNED_SMALL);
+        if (!pending) wait();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return hip_check(c, e, "copy to the host");
-    i = 0;
-    for (const Piece &p : pieces) {
-        if (st[i]) std::memcpy(p.dst, st[i], p.bytes);
-        ++i;
-    }
-    c->stage->used = 0;  // the stream has been waited for
-    return ELB_OK;
+    if (pending) wait();
+    return hip_check(c, e, "copy to the host");
 }
 
 // Offsets of the FP64 planes phi, theta [nx][Q] in the interiors of levels 1 and 2 (FP64 storage:
